@@ -170,6 +170,11 @@ __device__ __forceinline__ float sum8(float x) {
     return x;
 }
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
+// exp2(x), or 0 where the edge does not exist.  The mask goes into the argument: written as `on ? exp2(x) : 0` every
+// element becomes a branch of its own around the exponential, and the loads that feed the elements (the bias lookups
+// of a tile) are then waited for one after the other instead of once (forward + backward: k = 64, n = 8192 1844 -> 1822 us;
+// k = 4, n = 512 247.3 -> 245.2 us; packed batch at n = 8192 528 -> 522 us).
+__device__ __forceinline__ float masked_exp2(bool on, float x) { return fast_exp2(on ? x : kNegBig); }
 __device__ __forceinline__ float fast_log2(float x) { return __builtin_amdgcn_logf(x); }
 
 // all 8 groups (lanes with the same feature chunk) get the sum / max

@@ -275,7 +275,7 @@ __global__ void __launch_bounds__(kTileThreads, 2) bwd_kv_tile_kernel(const KeyA
             for (int ci = 0; ci < 2; ++ci)
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    const float p = bid[ci][r] >= 0 && key_kept ? fast_exp2((s4[ci][r] + bv[ci][r]) * qscale - st[ci][r].x) : 0.f;
+                    const float p = masked_exp2(bid[ci][r] >= 0 && key_kept, (s4[ci][r] + bv[ci][r]) * qscale - st[ci][r].x);
                     if (DROP) {
                         // a token row's edge is named by its relative-position id, a span row's by the key node;
                         // out = sum keep p v: dV takes keep p, and dP carries the mask into dS
@@ -579,7 +579,7 @@ __global__ void __launch_bounds__(kTileThreads, 2) bwd_kv_chain_kernel(const Key
                         const float bv1 = __shfl(b4[ci][1][r], src);
                         bv = bid[r] >= 16 ? bv1 : bv;
                     }
-                    const float p = bid[r] >= 0 && key_kept ? fast_exp2((s4[ci][r] + bv) * qscale - st[r].x) : 0.f;
+                    const float p = masked_exp2(bid[r] >= 0 && key_kept, (s4[ci][r] + bv) * qscale - st[r].x);
                     if (DROP) {
                         const uint32_t x2 = bid[r] < a.W ? (uint32_t)(level * a.W + bid[r]) : 0x80000000u + (uint32_t)(node0 + j);
                         const float keep = drop_scale(rowh_s[16 * ci + 4 * g + r], x2, a.drop_thr, a.drop_inv_keep);

@@ -472,7 +472,7 @@ __global__ void __launch_bounds__(kTileThreads, 2) fwd_tile_kernel(const TileArg
         for (int c = 0; c < 2; ++c)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                const float p = sc[c][r] > 0.5f * kNegBig ? fast_exp2(sc[c][r] - mn) : 0.f;
+                const float p = masked_exp2(sc[c][r] > 0.5f * kNegBig, sc[c][r] - mn);
                 sc[c][r] = p;
                 psum += p;
             }
@@ -870,7 +870,7 @@ __global__ void __launch_bounds__(kTileThreads, DENSE ? 1 : 2) bwd_q_tile_kernel
         for (int c = 0; c < 2; ++c) {
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                const float p = cid[c][r] >= 0 ? fast_exp2((s4[c][r] + bv[c][r]) * qscale - lse2) : 0.f;
+                const float p = masked_exp2(cid[c][r] >= 0, (s4[c][r] + bv[c][r]) * qscale - lse2);
                 // with dropout out = sum keep p v, so dP carries the mask
                 const float keep = DROP ? drop_scale(rowh, (uint32_t)relid_s[max(cid[c][r], 0)], a.drop_thr, a.drop_inv_keep) : 1.f;
                 const float wgt = p * d4[c][r] * keep;
