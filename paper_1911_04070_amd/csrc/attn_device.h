@@ -50,6 +50,7 @@ struct AttnArgs {
     float drop_inv_keep;    // 1 / (1 - p)
     int32_t* queue;         // backward workspace: task counters of the key-tile kernel
     int32_t grad_bf16;      // dQ, dK, dV leave rounded to bf16 (the three pointers then address bf16 elements)
+    float* dq32;            // backward workspace: the token rows' key part of dQ on its way to rel_grad_tile_kernel, or null
     // packed batch on the tile kernels: delta[level][sequence] or null; lse of (bh, node u) at
     // (bh / H) * lse_sb + (bh % H) * lse_sh + row of u
     const int32_t* delta;

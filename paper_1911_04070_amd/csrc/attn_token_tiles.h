@@ -55,6 +55,7 @@ struct TileArgs {
     const int32_t *seq_len, *id_to_cid;
     int32_t leave_unkept;   // rows of nodes a shorter sequence does not keep: left unwritten instead of zero-filled
     int32_t grad_bf16;      // dQ leaves rounded to bf16
+    float* dq32;            // not null (grad_bf16 without DENSE): dQ so far as fp32 [batch*head][num_tiles * 16][64], not to dQ
     int32_t n, k, W, ctx_levels, causal;
     // packed batch: delta[level][sequence] (see attn_device.h) or null; lse of (batch*head index bh, node u) is at
     // (bh / H) * lse_sb + (bh % H) * lse_sh + row of u
@@ -983,7 +984,14 @@ __global__ void __launch_bounds__(kTileThreads, DENSE ? 1 : 2) bwd_q_tile_kernel
             // not stored.
             const int64_t qrow_out = base + (int64_t)(PACKED ? t0 + level_delta(cc.dvec, 0) : t0) * a.sn;
             const int live = PACKED ? len - t0 : 16;   // rows of the tile that may be stored
-            if (j < live) {
+            if (!DENSE && a.dq32) {   // rel_grad_tile_kernel adds its part to the fp32 sums and rounds once
+                float* dst = a.dq32 + (((int64_t)cc.bh * a.num_tiles + cc.tile) * 16 + j) * kD + 4 * g;
+#pragma unroll
+                for (int f = 0; f < 4; ++f)
+                    *reinterpret_cast<f32x4_t*>(dst + 16 * f) =
+                        f32x4_t{a.scale * (ow[f][0] - delta * op[f][0]), a.scale * (ow[f][1] - delta * op[f][1]),
+                                a.scale * (ow[f][2] - delta * op[f][2]), a.scale * (ow[f][3] - delta * op[f][3])};
+            } else if (j < live) {
                 if (a.grad_bf16) {
                     bf16_t* dst = reinterpret_cast<bf16_t*>(a.dQ) + qrow_out + (int64_t)j * a.sn + 4 * g;
 #pragma unroll
@@ -1040,6 +1048,7 @@ struct RelGradArgs {
     float scale;
     const int32_t* seq_len;   // [B] tokens of every sequence, or null
     int32_t grad_bf16;        // dQ holds bf16 elements
+    const float* dq32;        // the key part of dQ (see TileArgs), or null: it is in dQ
     const int32_t* delta;     // packed batch: delta[level][sequence] (only the token level is used here), or null
 };
 // tile slots per thread fetched one block ahead: 8 (512 threads: 16 chunks) with up to 256 ids, 24 with more --
@@ -1168,7 +1177,12 @@ __global__ void __launch_bounds__(kThreads, CPW == 2 ? 4 : 2) rel_grad_tile_kern
         const int live = PACKED ? seq_length_u(a.seq_len, bh / a.H, a.n) : a.n, tok0 = PACKED ? a.delta[bh / a.H] : 0;
         const int dq_row = row0 + 16 * mc + j;
         const int64_t dq_at = base + (int64_t)(dq_row + tok0) * a.sn + 16 * fc + 4 * g;
-        const float4 dq_old = dq_row < live ? load_grad4(a.dQ, dq_at, a.grad_bf16) : make_float4(0.f, 0.f, 0.f, 0.f);
+        // (rows of a token tile past the end of its sequence have no fp32 sums: what stands in dQ for them stays)
+        const bool dq_add = dq_row < live && (!a.dq32 || row0 + 16 * mc < seq_length_u(a.seq_len, bh / a.H, a.n));
+        float4 dq_old = make_float4(0.f, 0.f, 0.f, 0.f);
+        if (dq_add)
+            dq_old = a.dq32 ? *reinterpret_cast<const float4*>(a.dq32 + ((int64_t)bh * a.num_tiles * 16 + dq_row) * kD + 16 * fc + 4 * g)
+                            : load_grad4(a.dQ, dq_at, a.grad_bf16);
         const int blk_next = next_block(blk + gridDim.x);
         if (blk_next < total) prefetch(blk_next);
         __syncthreads();
@@ -1179,7 +1193,7 @@ __global__ void __launch_bounds__(kThreads, CPW == 2 ? 4 : 2) rel_grad_tile_kern
                 dq = __builtin_amdgcn_mfma_f32_16x16x32_bf16(rb, lds_tr8(ds_hi, kRgStride, ks + 8 * g, 16 * mc, j), dq, 0, 0, 0);
                 dq = __builtin_amdgcn_mfma_f32_16x16x32_bf16(rb, lds_tr8(ds_lo, kRgStride, ks + 8 * g, 16 * mc, j), dq, 0, 0, 0);
             }
-            if (dq_row < live)
+            if (dq_add)
                 store_grad4(a.dQ, dq_at,
                             make_float4(dq_old.x + a.scale * dq[0], dq_old.y + a.scale * dq[1], dq_old.z + a.scale * dq[2],
                                         dq_old.w + a.scale * dq[3]), a.grad_bf16);

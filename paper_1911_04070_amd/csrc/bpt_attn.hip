@@ -276,6 +276,7 @@ void fill_tile_args(TileArgs& t, const bpt_graph* g, const AttnArgs& a, const Ti
     t.seq_len = a.seq_len;
     t.leave_unkept = a.leave_unkept;
     t.grad_bf16 = a.grad_bf16;
+    t.dq32 = a.dq32;
     t.delta = a.delta;
     t.levels = g->num_levels;
     t.lg = g->num_levels - 1;
@@ -456,7 +457,7 @@ struct BwdPlan {
     int drel_block = 32;      // token rows per block
     int drel_grid_x = 8, drel_grid_y = 1;
     size_t drel_lds = 0;
-    size_t off_stat = 0, off_wp = 0, off_qpart = 0, off_kvpart = 0, off_drel = 0, off_queue = 0, total = 0;
+    size_t off_stat = 0, off_wp = 0, off_qpart = 0, off_kvpart = 0, off_drel = 0, off_queue = 0, off_dq32 = 0, total = 0;
 };
 
 int plan_bwd(const bpt_graph* g, const bpt_shape_t* s, BwdPlan* p) {
@@ -522,6 +523,10 @@ int plan_bwd(const bpt_graph* g, const bpt_shape_t* s, BwdPlan* p) {
     p->off_drel = off;
     if (!p->drel_tile) p->drel_part_rows = p->drel_rows;
     off += align_up((size_t)p->drel_grid_x * p->drel_part_rows * kD * sizeof(float));
+    // gradients rounded to bf16: dQ of the token rows stays fp32 until rel_grad_tile_kernel has added to it (sized for
+    // either type of gradients, so that one workspace serves both)
+    p->off_dq32 = off;
+    off += align_up(p->drel_tile && !p->dense_ds ? bh * g->tiles.num_tiles * 16 * kD * sizeof(float) : 0);
     p->off_queue = off;
     off += align_up(kQueueInts * sizeof(int32_t));   // task counters of the key-tile kernel
     p->total = off;
@@ -604,6 +609,7 @@ int run_bwd_q(const bpt_graph* g, const BwdPlan& p, AttnArgs& a, hipStream_t st)
         t.scale = a.scale;
         t.seq_len = a.seq_len;
         t.grad_bf16 = a.grad_bf16;
+        t.dq32 = a.dq32;
         t.delta = a.delta;
         if (p.dense_ds) {
             // bwd_q_tile_kernel has left the copies of d_rel
@@ -882,6 +888,7 @@ int backward(const bpt_graph_t* g, const bpt_shape_t* s, const void* Q, const vo
     a.e_tok = g->num_token_edges;
     a.drel_part = reinterpret_cast<float*>(ws + p.off_drel);
     a.queue = reinterpret_cast<int32_t*>(ws + p.off_queue);
+    a.dq32 = a.grad_bf16 && p.drel_tile && !p.dense_ds ? reinterpret_cast<float*>(ws + p.off_dq32) : nullptr;
     hipStream_t st = static_cast<hipStream_t>(stream);
     const bool bf = s->dtype == BPT_BF16;
     if (stages & kStageQ) {

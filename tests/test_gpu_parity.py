@@ -681,3 +681,32 @@ def test_forward_and_backward_replay_from_a_captured_graph():
         for name, a, b in zip(("out", "lse", "dQ", "dK", "dV", "d_rel"), got, [out, lse] + list(grads)):
             assert torch.equal(a, b), (replay, name)
     g.destroy()
+
+
+@pytest.mark.parametrize("n,k,causal,B,lengths,leave", [
+    (256, 3, False, 2, None, False),             # dQ complete in the tile kernel
+    (2048, 16, False, 1, None, False),           # more than 128 ids: the relative-position part is added by a second kernel
+    (2048, 16, False, 3, [1040, 17, 2048], False), (2048, 16, False, 3, [1040, 17, 1], True),
+])
+def test_bf16_gradients_are_rounded_once(n, k, causal, B, lengths, leave):
+    # whichever kernels form dQ, the fp32 sum is rounded once: bit for bit the fp32 call's result rounded
+    say("bf16 gradients, one rounding", n, k, causal, lengths, leave)
+    w = Workload("bf16_once", 32, n, k, causal, B, 1, 64, "bf16", True)
+    x = make_inputs(w)
+    g = bpt.bpt_build_graph(n, k, causal)
+    Q, K, V, R, dO = (to_dev(x[k_], "bf16") for k_ in ("Q", "K", "V", "Rel", "dO"))
+    lens_d = torch.tensor(lengths, dtype=torch.int32, device="cuda") if lengths else None
+    _, lse = bpt.bpt_attn_fwd(g, Q, K, V, R, seq_len=lens_d)
+    g32 = tuple(torch.full_like(Q, 3.0, dtype=torch.float32) for _ in range(3)) + (torch.empty_like(R, dtype=torch.float32),)
+    g16 = tuple(torch.full_like(Q, 3.0) for _ in range(3)) + (torch.empty_like(R, dtype=torch.float32),)
+    bpt.bpt_attn_bwd(g, Q, K, V, R, lse, dO, grads=g32, seq_len=lens_d, leave_unkept=leave)
+    bpt.bpt_attn_bwd(g, Q, K, V, R, lse, dO, grads=g16, seq_len=lens_d, leave_unkept=leave)
+    torch.cuda.synchronize()
+    for name, a32, a16 in zip(("dQ", "dK", "dV"), g32, g16):
+        assert torch.equal(a16, a32.to(torch.bfloat16)), name
+    if not leave:   # and what autograd hands out is that
+        leaves = [t.clone().requires_grad_(True) for t in (Q, K, V, R)]
+        bpt.graph_attention(g, *leaves, seq_len=lens_d).backward(dO)
+        for leaf, a32 in zip(leaves, g32):
+            assert torch.equal(leaf.grad, a32.to(torch.bfloat16))
+    g.destroy()
