@@ -21,7 +21,6 @@ namespace {
 // several tasks is summed by kv_tile_merge_kernel in task order.
 constexpr int kMaxBiasChunks = 10;   // 16-id chunks of the table a key tile can meet (W + levels - 1 ids <= 160)
 constexpr int kKvOutStride = 2 * kD + 4;   // floats per key row of the output staging in LDS (528 bytes)
-constexpr int kRegBiasChunks = 6;    // of which this many are register operands; the others are parked in LDS
 struct KeyArgs {
     const bf16_t *Q, *K, *V, *rel, *dout;
     const float2* stat;
@@ -34,6 +33,7 @@ struct KeyArgs {
     const int32_t *tile_node0, *tile_info, *cols, *task_tile, *task_c0, *task_nch, *task_part;
     const int32_t *task_ntiles, *chunk_ptr;   // chained tasks: tiles the task walks, first chunk of every tile
     const int16_t* map;
+    const int32_t* id_blocks;   // [chunks] bit b: an edge of the chunk carries one of the ids 16b .. 16b + 15
     int32_t num_tasks, num_part, num_chunks, nb_pad, W, zero;
     const int32_t* seq_len;   // [B] tokens of every sequence, or null
     int32_t leave_unkept;     // rows of nodes a shorter sequence does not keep: left unwritten instead of zero-filled
@@ -54,32 +54,37 @@ __global__ void zero_ints_kernel(int32_t* p, int count) {
 }
 
 // PACKED: the rows of the caller's tensors are those of a packed batch (KeyArgs.delta; see attn_device.h)
+// The bias costs the most here: a tile can meet 16 NBC ids, but the 16 queries of a chunk lie within 31 orders of one
+// level (queries on both sides of the keys, or ancestors among them, bring a second such run), so a mask per chunk
+// names the two to four blocks of 16 ids that its edges carry and only those are formed.  The bias of one chunk at a time
+// is in LDS, which together with the masks leaves room for a second workgroup per compute unit at any NBC.  Table
+// operands: up to four blocks stay in registers (five spill); tiles with more (NBC = 0, up to 10 blocks) hold the blocks
+// of the pair at hand in five register pairs and fetch what changes for the next pair behind this pair's bias, in time
+// with its rows: from level 2 on a pair's blocks are mostly those of the pair before.
+// k = 64, n = 8192, causal, 32 (batch, head)s: all nine blocks for every chunk, 32 rows of bias and one workgroup per
+// compute unit 0.615 ms, now 0.319; k = 16, n = 4096, dropout (NBC = 3): step -0.4 %.
 template <int NBC, bool DROP, bool PACKED = false>
 __global__ void __launch_bounds__(kTileThreads, 2) bwd_kv_tile_kernel(const KeyArgs a) {
+    constexpr int kRelRegs = NBC ? NBC : 5;        // blocks of table operands in registers
+    constexpr int kSlotBlocks = 0x21;              // NBC == 0: block b of the 10 goes into register pair b mod 5
     extern __shared__ __align__(16) unsigned char smem[];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int g = lane >> 4, j = lane & 15;
     const int r8 = lane >> 3, piece = lane & 7;   // coalesced row fetches: row of the instruction, 16-byte piece
     const int bstride = a.nb_pad + 1;
-    float* bias_s = reinterpret_cast<float*>(smem) + (size_t)wave * 32 * bstride;               // [32 queries][ids]
-    bf16_t* q_s = reinterpret_cast<bf16_t*>(smem + (size_t)kTileWaves * 32 * bstride * sizeof(float)) +
+    float* bias_s = reinterpret_cast<float*>(smem) + (size_t)wave * 16 * bstride;               // [16 queries][ids]
+    bf16_t* q_s = reinterpret_cast<bf16_t*>(smem + (size_t)kTileWaves * 16 * bstride * sizeof(float)) +
                   (size_t)wave * 64 * kRowStride;                                                // [32 queries][kRowStride]
     bf16_t* g_s = q_s + 32 * kRowStride;
-    float2* stat_s = reinterpret_cast<float2*>(smem + (size_t)kTileWaves * (32 * bstride * sizeof(float) +
+    float2* stat_s = reinterpret_cast<float2*>(smem + (size_t)kTileWaves * (16 * bstride * sizeof(float) +
                                                                             64 * kRowStride * sizeof(bf16_t))) +
                      (size_t)wave * 32;                                                          // [32 queries] (lse, delta)
-    // table operands beyond the kRegBiasChunks kept in registers: every lane parks and re-reads its own 32 bytes
-    constexpr int kParked = NBC > kRegBiasChunks ? NBC - kRegBiasChunks : 0;
     // DROP: hash of (seed, batch*head, query node) of the 32 queries, what the mask of their edges is drawn from
-    uint32_t* rowh_s = reinterpret_cast<uint32_t*>(smem + (size_t)kTileWaves * (32 * bstride * sizeof(float) +
+    uint32_t* rowh_s = reinterpret_cast<uint32_t*>(smem + (size_t)kTileWaves * (16 * bstride * sizeof(float) +
                                                                                 64 * kRowStride * sizeof(bf16_t) +
                                                                                 32 * sizeof(float2))) +
                        (size_t)wave * 32;
-    uint4* rb_s = reinterpret_cast<uint4*>(smem + (size_t)kTileWaves * (32 * bstride * sizeof(float) +
-                                                                        64 * kRowStride * sizeof(bf16_t) + 32 * sizeof(float2) +
-                                                                        32 * sizeof(uint32_t))) +
-                  ((size_t)wave * (kParked > 0 ? kParked : 1) * 64 + lane) * 2;
     const float qscale = a.scale * kLog2e;
     // The (batch*head, task) space is split into 8 contiguous shares, one per XCD (workgroup w runs on
     // XCD w mod 8).  The wavefronts of an XCD take the tasks of its share in order from a shared counter:
@@ -130,6 +135,7 @@ __global__ void __launch_bounds__(kTileThreads, 2) bwd_kv_tile_kernel(const KeyA
         // fetches a piece of row 16 ci + 8 h + r8 reads its id from there, and lane l fetches (lse, delta) of node l
         int colv;
         uint2 mpn[2];
+        int blkn[2];
         auto load_idx = [&](int c2) {   // a pair past the end repeats the last one (valid addresses, results unused)
             const int cc = c0 + min(c2, nch - 2);
             colv = buf_i32(rC, (cc * 16 + (lane & 31)) * 4);
@@ -137,6 +143,7 @@ __global__ void __launch_bounds__(kTileThreads, 2) bwd_kv_tile_kernel(const KeyA
             for (int ci = 0; ci < 2; ++ci) {
                 const u32x2 m2 = __builtin_amdgcn_raw_buffer_load_b64(rM, ((cc + ci) * 16 + j) * 32 + 8 * g, 0, 0);
                 mpn[ci] = make_uint2(m2.x, m2.y);
+                blkn[ci] = uniform_i32(a.id_blocks, cc + ci);
             }
         };
         // Row fetches are coalesced: 8 consecutive lanes take the 8 16-byte pieces of one row, an
@@ -168,27 +175,39 @@ __global__ void __launch_bounds__(kTileThreads, 2) bwd_kv_tile_kernel(const KeyA
         const bf16x8_t kb1 = load_once16<bf16x8_t>(a.K + krow + 8);
         const bf16x8_t vb0 = load_once16<bf16x8_t>(a.V + krow);
         const bf16x8_t vb1 = load_once16<bf16x8_t>(a.V + krow + 8);
-        constexpr int kInRegs = NBC < kRegBiasChunks ? NBC : kRegBiasChunks;
-        bf16x8_t rb[kInRegs][2];
-#pragma unroll
-        for (int bc = 0; bc < NBC; ++bc) {
+        // row of the table that stands for tile-local id 16 bc + j (ids no edge has: some row)
+        auto rel_row = [&](int bc) {
             const int bid = 16 * bc + j;
-            int row = 0;
-            if (bid < a.W)
-                row = level * a.W + bid;                        // (level, order)
-            else if (bid - a.W + 1 < a.num_levels)
-                row = (bid - a.W + 1) * a.W + a.zero;            // r_anc of the ancestor's level
-            const bf16_t* rr = a.rel + (int64_t)row * kD + 16 * g;
-            if (bc < kInRegs) {
-                rb[bc][0] = *reinterpret_cast<const bf16x8_t*>(rr);
-                rb[bc][1] = *reinterpret_cast<const bf16x8_t*>(rr + 8);
-            } else {
-                rb_s[(bc - kInRegs) * 128] = *reinterpret_cast<const uint4*>(rr);
-                rb_s[(bc - kInRegs) * 128 + 1] = *reinterpret_cast<const uint4*>(rr + 8);
+            const int row = bid < a.W ? level * a.W + bid                                                      // (level, order)
+                                      : bid - a.W + 1 < a.num_levels ? (bid - a.W + 1) * a.W + a.zero : 0;   // r_anc of the ancestor's level
+            return a.rel + (int64_t)row * kD + 16 * g;
+        };
+        bf16x8_t rb[kRelRegs][2];
+        int held[kRelRegs];   // NBC == 0: the block of ids every register pair holds (uniform)
+        auto load_rel = [&](int blocks) {   // NBC == 0: the operands of a pair's blocks that are not there yet
+#pragma unroll
+            for (int s = 0; s < kRelRegs; ++s) {
+                const int mine = blocks & (kSlotBlocks << s);
+                if (mine == 0 || (mine >> held[s] & 1)) continue;
+                held[s] = __builtin_ctz(mine);
+                const bf16_t* rr = rel_row(held[s]);
+                rb[s][0] = *reinterpret_cast<const bf16x8_t*>(rr);
+                rb[s][1] = *reinterpret_cast<const bf16x8_t*>(rr + 8);
+            }
+        };
+#pragma unroll
+        for (int s = 0; s < kRelRegs; ++s) {
+            held[s] = NBC ? s : 31;   // (31: no block, the masks have 10 bits)
+            if (NBC) {
+                const bf16_t* rr = rel_row(s);
+                rb[s][0] = *reinterpret_cast<const bf16x8_t*>(rr);
+                rb[s][1] = *reinterpret_cast<const bf16x8_t*>(rr + 8);
             }
         }
         load_rows();     // pair 0 (waits for its ids)
         uint2 mp[2] = {mpn[0], mpn[1]};
+        int blk[2] = {blkn[0], blkn[1]};
+        if (!NBC) load_rel(blk[0] | blk[1]);
         load_idx(2);     // ids of pair 1
 
         f32x4_t dk[4], dv[4];
@@ -210,63 +229,72 @@ __global__ void __launch_bounds__(kTileThreads, 2) bwd_kv_tile_kernel(const KeyA
             __builtin_amdgcn_sched_barrier(0);
             // the row registers are free: request the next pair's rows, then the ids of the pair after it
             const uint2 mpc[2] = {mp[0], mp[1]};
+            const int blkc[2] = {blk[0], blk[1]};
             load_rows();
             mp[0] = mpn[0];
             mp[1] = mpn[1];
+            blk[0] = blkn[0];
+            blk[1] = blkn[1];
             load_idx(c2 + 4);
             __builtin_amdgcn_sched_barrier(0);
             wave_lds_sync();
             f32x4_t s4[2], d4[2];
+            bf16x8_t q0[2], q1[2];
 #pragma unroll
             for (int ci = 0; ci < 2; ++ci) {
                 const bf16_t* qr = q_s + (16 * ci + j) * kRowStride + 16 * g;
                 const bf16_t* gr = g_s + (16 * ci + j) * kRowStride + 16 * g;
-                const bf16x8_t q0 = *reinterpret_cast<const bf16x8_t*>(qr), q1 = *reinterpret_cast<const bf16x8_t*>(qr + 8);
+                q0[ci] = *reinterpret_cast<const bf16x8_t*>(qr);
+                q1[ci] = *reinterpret_cast<const bf16x8_t*>(qr + 8);
                 const bf16x8_t g0 = *reinterpret_cast<const bf16x8_t*>(gr), g1 = *reinterpret_cast<const bf16x8_t*>(gr + 8);
                 s4[ci] = d4[ci] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-                s4[ci] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(q0, kb0, s4[ci], 0, 0, 0);
-                s4[ci] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(q1, kb1, s4[ci], 0, 0, 0);
+                s4[ci] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(q0[ci], kb0, s4[ci], 0, 0, 0);
+                s4[ci] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(q1[ci], kb1, s4[ci], 0, 0, 0);
                 d4[ci] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(g0, vb0, d4[ci], 0, 0, 0);
                 d4[ci] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(g1, vb1, d4[ci], 0, 0, 0);
-#pragma unroll
-                for (int bc = 0; bc < NBC; ++bc) {
-                    f32x4_t b4 = {0.f, 0.f, 0.f, 0.f};
-                    bf16x8_t r0, r1;
-                    if (bc < kInRegs) {
-                        r0 = rb[bc][0];
-                        r1 = rb[bc][1];
-                    } else {
-                        r0 = __builtin_bit_cast(bf16x8_t, rb_s[(bc - kInRegs) * 128]);
-                        r1 = __builtin_bit_cast(bf16x8_t, rb_s[(bc - kInRegs) * 128 + 1]);
-                    }
-                    b4 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(q0, r0, b4, 0, 0, 0);
-                    b4 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(q1, r1, b4, 0, 0, 0);
-#pragma unroll
-                    for (int r = 0; r < 4; ++r) bias_s[(16 * ci + 4 * g + r) * bstride + 16 * bc + j] = b4[r];
-                }
             }
-            wave_lds_sync();
             float ds[2][4], pp[2][4], bv[2][4];
             float2 st[2][4];
             int bid[2][4];
-#pragma unroll
-            for (int ci = 0; ci < 2; ++ci) {
-                const float4 x = *reinterpret_cast<const float4*>(stat_s + 16 * ci + 4 * g);
-                const float4 y = *reinterpret_cast<const float4*>(stat_s + 16 * ci + 4 * g + 2);
-                st[ci][0] = make_float2(x.x, x.y);
-                st[ci][1] = make_float2(x.z, x.w);
-                st[ci][2] = make_float2(y.x, y.y);
-                st[ci][3] = make_float2(y.z, y.w);
-            }
 #pragma unroll
             for (int ci = 0; ci < 2; ++ci) {
                 bid[ci][0] = (int)(short)(mpc[ci].x & 0xFFFFu);
                 bid[ci][1] = (int)(short)(mpc[ci].x >> 16);
                 bid[ci][2] = (int)(short)(mpc[ci].y & 0xFFFFu);
                 bid[ci][3] = (int)(short)(mpc[ci].y >> 16);
+                // the bias of (query, id), one chunk at a time through the same LDS rows, for the blocks of 16 ids that an
+                // edge of the chunk carries (the others keep what they held: nothing but masked slots reads them)
+                auto form_bias = [&](int bc, const bf16x8_t& r0, const bf16x8_t& r1) {
+                    f32x4_t b4 = {0.f, 0.f, 0.f, 0.f};
+                    b4 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(q0[ci], r0, b4, 0, 0, 0);
+                    b4 = __builtin_amdgcn_mfma_f32_16x16x32_bf16(q1[ci], r1, b4, 0, 0, 0);
 #pragma unroll
-                for (int r = 0; r < 4; ++r) bv[ci][r] = bias_s[(16 * ci + 4 * g + r) * bstride + max(bid[ci][r], 0)];
+                    for (int r = 0; r < 4; ++r) bias_s[(4 * g + r) * bstride + 16 * bc + j] = b4[r];
+                };
+                int rest = blkc[ci];
+#pragma unroll
+                for (int s = 0; s < kRelRegs; ++s) {
+                    if (!(rest >> held[s] & 1)) continue;   // uniform
+                    form_bias(held[s], rb[s][0], rb[s][1]);
+                    rest &= ~(1 << held[s]);
+                }
+                if (!NBC)   // two blocks of one slot in a pair (edges of both sides or ancestors meet in it)
+                    for (; rest; rest &= rest - 1) {
+                        const bf16_t* rr = rel_row(__builtin_ctz(rest));
+                        form_bias(__builtin_ctz(rest), *reinterpret_cast<const bf16x8_t*>(rr), *reinterpret_cast<const bf16x8_t*>(rr + 8));
+                    }
+                wave_lds_sync();
+#pragma unroll
+                for (int r = 0; r < 4; ++r) bv[ci][r] = bias_s[(4 * g + r) * bstride + max(bid[ci][r], 0)];
+                const float4 x = *reinterpret_cast<const float4*>(stat_s + 16 * ci + 4 * g);
+                const float4 y = *reinterpret_cast<const float4*>(stat_s + 16 * ci + 4 * g + 2);
+                st[ci][0] = make_float2(x.x, x.y);
+                st[ci][1] = make_float2(x.z, x.w);
+                st[ci][2] = make_float2(y.x, y.y);
+                st[ci][3] = make_float2(y.z, y.w);
+                wave_lds_sync();
             }
+            if (!NBC) load_rel(blk[0] | blk[1]);   // of the next pair
 #pragma unroll
             for (int ci = 0; ci < 2; ++ci)
 #pragma unroll

@@ -481,9 +481,8 @@ int plan_bwd(const bpt_graph* g, const bpt_shape_t* s, BwdPlan* p) {
             if (cids <= 16 * kDenseChunks && plan_tiles(g, lim, true).ok) p->dense_ds = true;
         }
         if (g->ktiles.num_tasks > 0 && g->ktiles.nb_pad <= 16 * kMaxBiasChunks) {
-            const int parked = std::max(0, g->ktiles.nb_pad / 16 - kRegBiasChunks);   // table operands kept in LDS
-            p->kv_lds = (size_t)kTileWaves * (32 * (g->ktiles.nb_pad + 1) * sizeof(float) + 64 * kRowStride * sizeof(bf16_t) +
-                                              32 * sizeof(float2) + 32 * sizeof(uint32_t) + (size_t)parked * 64 * 32);
+            p->kv_lds = (size_t)kTileWaves * (16 * (g->ktiles.nb_pad + 1) * sizeof(float) + 64 * kRowStride * sizeof(bf16_t) +
+                                              32 * sizeof(float2) + 32 * sizeof(uint32_t));
             p->kv_tiles = p->kv_lds <= lim.lds;
             const size_t chain_lds = (size_t)kTileWaves * (64 * kRowStride * sizeof(bf16_t) + 16 * kKvOutStride * sizeof(float) +
                                                             32 * sizeof(float2) + 32 * sizeof(uint32_t));
@@ -726,6 +725,7 @@ int run_bwd_kv_tiles(const bpt_graph* g, const BwdPlan& p, const AttnArgs& a, co
     t.task_ntiles = kt.task_ntiles;
     t.chunk_ptr = kt.chunk_ptr;
     t.map = kt.map;
+    t.id_blocks = kt.id_blocks;
     t.num_tasks = kt.num_tasks;
     t.num_part = kt.num_part;
     t.nb_pad = kt.nb_pad;
@@ -752,13 +752,7 @@ int run_bwd_kv_tiles(const bpt_graph* g, const BwdPlan& p, const AttnArgs& a, co
         case 2: rc = p.kv_chain ? launch_kv_chain<2>(t, p, lim, st) : launch_kv_tiles<2>(t, p, lim, st); break;
         case 3: rc = launch_kv_tiles<3>(t, p, lim, st); break;
         case 4: rc = launch_kv_tiles<4>(t, p, lim, st); break;
-        case 5: rc = launch_kv_tiles<5>(t, p, lim, st); break;
-        case 6: rc = launch_kv_tiles<6>(t, p, lim, st); break;
-        case 7: rc = launch_kv_tiles<7>(t, p, lim, st); break;
-        case 8: rc = launch_kv_tiles<8>(t, p, lim, st); break;
-        case 9: rc = launch_kv_tiles<9>(t, p, lim, st); break;
-        case 10: rc = launch_kv_tiles<10>(t, p, lim, st); break;
-        default: break;
+        default: rc = launch_kv_tiles<0>(t, p, lim, st); break;   // (at most kMaxBiasChunks, plan_bwd)
     }
     if (rc) return rc;
     // threads of the zero pass of kv_tile_merge_kernel: one per node it has to look at, in wavefronts of 64 nodes

@@ -712,6 +712,7 @@ void free_tiles(TokenTiles& t) {
 
 void free_key_tiles(KeyTiles& t) {
     (void)hipFree(t.chunk_ptr);
+    (void)hipFree(t.id_blocks);
     (void)hipFree(t.tile_node0);
     (void)hipFree(t.tile_info);
     (void)hipFree(t.cols);

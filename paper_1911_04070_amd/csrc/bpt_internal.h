@@ -69,6 +69,7 @@ struct KeyTiles {
     int32_t* tile_info = nullptr;   // [tiles] level | valid keys << 8
     int32_t* cols = nullptr;        // [chunks][16] query node of a column
     int16_t* map = nullptr;         // [chunks][16 keys][16 columns] tile-local relative-position id, or -1
+    int32_t* id_blocks = nullptr;   // [chunks] bit b: a slot of the chunk carries one of the ids 16b .. 16b + 15 (b < 31)
     int32_t* task_tile = nullptr;   // [tasks]
     int32_t* task_c0 = nullptr;     // [tasks] first chunk
     int32_t* task_nch = nullptr;    // [tasks] chunks (even)

@@ -343,6 +343,21 @@ __global__ void key_tile_map_ancestors(int num_levels, int W, int token_tiles, c
     }
 }
 
+// one wavefront per chunk: which blocks of 16 tile-local ids its slots carry (ids from 496 on are not recorded: the
+// kernel that reads the mask takes tiles of at most 160 ids)
+__global__ void key_tile_id_blocks(int64_t chunks, const int16_t* __restrict__ map, int32_t* __restrict__ id_blocks) {
+    const int64_t c = (int64_t)blockIdx.x * (kTB / 64) + (threadIdx.x >> 6);
+    if (c >= chunks) return;
+    const int lane = threadIdx.x & 63;
+    int mask = 0;
+    for (int i = lane; i < 256; i += 64) {
+        const int id = map[c * 256 + i];
+        if (id >= 0 && id < 31 * 16) mask |= 1 << (id >> 4);
+    }
+    for (int s = 32; s > 0; s >>= 1) mask |= __shfl_xor(mask, s);
+    if (lane == 0) id_blocks[c] = mask;
+}
+
 // one thread per key tile: its tasks; tiles with several tasks also enter the merge list
 __global__ void key_tile_tasks(int nkt, int ctx_levels, LevelBases lb, int task_chunks, int num_multi, int num_part,
                                const int32_t* __restrict__ kchunk_ptr, const int32_t* __restrict__ ntask,
@@ -544,6 +559,7 @@ int build_tile_metadata(bpt_graph* g, const int32_t* cnt_l, const int32_t* min_l
     if (want_keys && kchunks * 512 <= ((int64_t)512 << 20)) {
         const int num_tasks = h_tot[3], num_part = h_tot[4], num_multi = h_tot[5];
         if ((rc = device_alloc(&kt.cols, (size_t)kchunks * 16)) || (rc = device_alloc(&kt.map, (size_t)kchunks * 256)) ||
+            (rc = device_alloc(&kt.id_blocks, (size_t)kchunks)) ||
             (rc = device_alloc(&kt.task_tile, num_tasks)) || (rc = device_alloc(&kt.task_c0, num_tasks)) ||
             (rc = device_alloc(&kt.task_nch, num_tasks)) || (rc = device_alloc(&kt.task_part, num_tasks)) ||
             (rc = device_alloc(&kt.task_ntiles, num_tasks)) ||
@@ -557,6 +573,9 @@ int build_tile_metadata(bpt_graph* g, const int32_t* cnt_l, const int32_t* min_l
         const int token_tiles = lb.tile_base[1];
         hipLaunchKernelGGL(key_tile_map_ancestors, dim3((token_tiles * 16 + kTB - 1) / kTB), dim3(kTB), 0, st, num_levels, W,
                            token_tiles, kt.chunk_ptr, kt.tile_node0, kt.tile_info, anc_first.as<int32_t>(), kt.map);
+        if (kchunks > 0)
+            hipLaunchKernelGGL(key_tile_id_blocks, dim3((unsigned)((kchunks + kTB / 64 - 1) / (kTB / 64))), dim3(kTB), 0, st, kchunks,
+                               kt.map, kt.id_blocks);
         const bool reorder = n > kSegTokens && num_tasks <= kMaxSortedTasks;
         DeviceBuf ut_tile, ut_c0, ut_nch, ut_part, ut_ntiles;   // the tasks in tile order, when they are put in another one
         if (reorder) {

@@ -165,11 +165,23 @@ def test_rows_cut_into_several_segments():
 @pytest.mark.parametrize("n,k,causal", [(4096, 64, True), (1024, 72, False), (2048, 50, False)])
 def test_large_density_on_key_tiles(n, k, causal):
     # the paper's character-level density k = 64 (Sec. 4.2) and the largest the key tiles take:
-    # 7..10 chunks of 16 relative-position ids per level, the last ones parked in LDS
+    # 7..10 blocks of 16 relative-position ids per level
     run_case(Workload("dense_k", 11, n, k, causal, 1, 2, 64, "bf16", True))
 
 
 FULL = ["cls", "lm", "xl", "ksweep2", "ksweep4", "ksweep8", "ksweep16", "ksweep32", "charlm"]
+
+
+# key tiles that meet 64, 80, 160 and (gather kernels) 176 ids: the last size with all table operands in registers,
+# the first and last with the ones of the pair at hand; bidirectional tiles have pairs whose edges lie on both sides
+# and on ancestors, so that two blocks of ids want the same registers
+@pytest.mark.parametrize("causal", [False, True])
+@pytest.mark.parametrize("n,k", [(512, 26), (512, 27), (128, 40), (1024, 73), (1024, 74)])
+def test_key_tiles_of_many_ids(n, k, causal):
+    w = Workload("keys%d" % k, 9, n, k, causal, 1, 2, 64, "bf16", True)
+    x = make_inputs(w)
+    x["Rel"] = x["Rel"] * np.float32(16)   # exact in bf16; a wrong row of the table shifts a score by about its own size
+    run_case(w, x, scaled=True)
 
 
 @pytest.mark.parametrize("name", FULL)
