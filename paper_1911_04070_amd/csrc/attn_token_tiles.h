@@ -42,6 +42,7 @@ struct TileArgs {
     float scale;
     const int32_t *chunk_ptr, *cols, *cid_to_id;
     const int16_t* map;
+    const int32_t* pair_blocks;   // [chunks / 2] blocks of 16 compact ids a tile has met up to and with the pair
     int32_t num_tiles, num_chunks, num_cids, cid_pad, bias_stride;
     int32_t row_bytes;
     uint32_t slab_bytes;
@@ -125,19 +126,20 @@ __device__ __forceinline__ s16x4_t lds_tr4(const bf16_t* base, int stride, int r
 // p_0 = t + 1 and p_{l+1} = ceil((p_l + k) / 2) (Algorithm 1: k nodes, one more when the run would
 // not end on a parent boundary), and level l keeps ceil(len / 2^l) nodes.  Lane (g, j) works on
 // token j of the tile; the four lane groups share the ids.
+// c0, c1: the ids to look at (the others are not in the table yet, or no longer); the table holds id c at c & wrap.
 constexpr float kMaskBias = -1.0e30f;
-__device__ __forceinline__ void mask_bias(const TileArgs& a, float* bias_s, int t0, int len, int g, int j) {
+__device__ __forceinline__ void mask_bias(const TileArgs& a, float* bias_s, int t0, int len, int g, int j, int c0, int c1, int wrap) {
     const int t = t0 + j;
     float* row = bias_s + j * a.bias_stride;
     if (t >= len) {
-        for (int c = 4 * g; c < a.cid_pad; c += 16) *reinterpret_cast<f32x4_t*>(row + c) = f32x4_t{kMaskBias, kMaskBias, kMaskBias, kMaskBias};
+        for (int c = c0 + 4 * g; c < c1; c += 16) *reinterpret_cast<f32x4_t*>(row + (c & wrap)) = f32x4_t{kMaskBias, kMaskBias, kMaskBias, kMaskBias};
     } else if (!a.causal) {
         int p = t + 1;
         for (int l = 0; l < a.ctx_levels; ++l) {
             const int cnt = (len + (1 << l) - 1) >> l;            // nodes the level keeps
             for (int o = max(cnt - p + 1, 1) + g; o <= a.k + 1; o += 4) {
                 const int cid = a.id_to_cid[l * a.W + a.k + 1 + o];
-                if (cid >= 0) row[cid] = kMaskBias;
+                if (cid >= c0 && cid < c1) row[cid & wrap] = kMaskBias;
             }
             p = (p + a.k + 1) >> 1;
         }
@@ -189,6 +191,7 @@ __device__ __forceinline__ void nth_tile(const int* pref, int B, int H, int num_
 // Position of a wavefront in its sequence of (token tile, pair of chunks); wave-uniform.
 struct TileCursor {
     int t, pair, npairs, cp0, bh, tile;
+    int b0, b1;   // RING kernels: blocks of ids that enter the bias table with this pair
     int dvec;   // packed batch: this lane's delta of the sequence the tile belongs to (0 otherwise)
     bool valid;
 };
@@ -202,13 +205,62 @@ __device__ __forceinline__ void cursor_uniform(TileCursor& c) {
     c.cp0 = __builtin_amdgcn_readfirstlane(c.cp0);
     c.bh = __builtin_amdgcn_readfirstlane(c.bh);
     c.tile = __builtin_amdgcn_readfirstlane(c.tile);
+    c.b0 = __builtin_amdgcn_readfirstlane(c.b0);
+    c.b1 = __builtin_amdgcn_readfirstlane(c.b1);
     c.valid = __builtin_amdgcn_readfirstlane((int)c.valid) != 0;
 }
 
-// REL_LDS: the compact relative-position table is staged in LDS; otherwise (large tables) its rows
-// are read from memory when a tile forms its bias table.
+// The bias of a tile, [token][compact id], in one of two forms.  Without RING the whole table is formed at the start of
+// the tile, out of the relative-position table staged in LDS.  RING: a tile's columns run through its ids in ascending
+// order (level by level, from the far left to the far right of each; a pair of chunks spans at most about 50 ids), so
+// the table is a ring of kRingIds ids per token, and every pair forms the blocks of 16 ids that are new with it
+// (TileArgs.pair_blocks) out of rows of the relative-position table that were requested from memory with the pair's K and
+// V rows.  The same products in all, but the LDS of a wavefront no longer grows with the ids (k = 64: 8 instead of 31
+// KB), which is what lets a second workgroup onto every compute unit.  k = 64, n = 8192, causal, 32 (batch, head)s: this
+// kernel 356 -> 220 us, the query side 437 -> 374 us (the 1.2 GB of (w, p) it writes bound it); k = 16, n = 4096, 64 of
+// them, dropout: 200 -> 183 and 277 -> 262 us.
+constexpr int kRingIds = 16 * kRingBlocks;
+constexpr int kRingStride = kRingIds + 4;   // = 4 mod 32: the 16 token rows hit different banks
+constexpr int kRingAhead = 3;               // blocks of a pair requested ahead (the first pair of a tile may need more)
+struct RelAhead {
+    bf16x8_t r[kRingAhead][2];
+};
+__device__ __forceinline__ const bf16_t* ring_rel_row(const TileArgs& a, const int32_t* relid_s, int block, int g, int j) {
+    // (padding ids repeat the last real one; no column carries them)
+    return a.rel + (int64_t)relid_s[min(16 * block + j, a.num_cids - 1)] * kD + 16 * g;
+}
+__device__ __forceinline__ void ring_request(const TileArgs& a, const int32_t* relid_s, const TileCursor& c, int g, int j, RelAhead& x) {
+#pragma unroll
+    for (int i = 0; i < kRingAhead; ++i)
+        if (c.b0 + i < c.b1) {   // uniform
+            const bf16_t* rr = ring_rel_row(a, relid_s, c.b0 + i, g, j);
+            x.r[i][0] = *reinterpret_cast<const bf16x8_t*>(rr);
+            x.r[i][1] = *reinterpret_cast<const bf16x8_t*>(rr + 8);
+        }
+}
+__device__ __forceinline__ void ring_form(const TileArgs& a, const int32_t* relid_s, float* bias_s, const TileCursor& c,
+                                          const bf16x8_t& qb0, const bf16x8_t& qb1, int g, int j, const RelAhead& x) {
+    auto block = [&](int b, const bf16x8_t& r0, const bf16x8_t& r1) {
+        f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
+        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(r0, qb0, acc, 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(r1, qb1, acc, 0, 0, 0);
+        *reinterpret_cast<f32x4_t*>(bias_s + j * kRingStride + ((16 * b) & (kRingIds - 1)) + 4 * g) = acc;
+    };
+#pragma unroll
+    for (int i = 0; i < kRingAhead; ++i)
+        if (c.b0 + i < c.b1) block(c.b0 + i, x.r[i][0], x.r[i][1]);
+    for (int b = c.b0 + kRingAhead; b < c.b1; ++b) {
+        const bf16_t* rr = ring_rel_row(a, relid_s, b, g, j);
+        block(b, *reinterpret_cast<const bf16x8_t*>(rr), *reinterpret_cast<const bf16x8_t*>(rr + 8));
+    }
+    if (a.seq_len && c.b0 < c.b1) {   // uniform
+        wave_lds_sync();
+        mask_bias(a, bias_s, c.tile * 16, seq_length_u(a.seq_len, c.bh / a.H, a.n), g, j, 16 * c.b0, 16 * c.b1, kRingIds - 1);
+    }
+}
+
 // PACKED: the rows of the caller's tensors are those of a packed batch (TileArgs.delta; see attn_device.h)
-template <bool REL_LDS, bool DROP, bool PACKED = false>
+template <bool RING, bool DROP, bool PACKED = false>
 __global__ void __launch_bounds__(kTileThreads, 2) fwd_tile_kernel(const TileArgs a) {
     extern __shared__ __align__(16) unsigned char smem[];
     bf16_t* rel_s = reinterpret_cast<bf16_t*>(smem);                                   // [cid_pad][kRelStride]
@@ -216,19 +268,19 @@ __global__ void __launch_bounds__(kTileThreads, 2) fwd_tile_kernel(const TileArg
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int g = lane >> 4, j = lane & 15;
     const int r8 = lane >> 3, piece = lane & 7;   // coalesced row fetches: row of the instruction, 16-byte piece
-    const size_t rel_bytes = REL_LDS ? (size_t)a.cid_pad * kRelStride * sizeof(bf16_t) : 0;
+    const size_t rel_bytes = !RING ? (size_t)a.cid_pad * kRelStride * sizeof(bf16_t) : 0;
     float* bias_s = reinterpret_cast<float*>(smem + rel_bytes) +
                     (size_t)wave * 16 * a.bias_stride;                                  // [16 tokens][bias_stride]
     bf16_t* k_s = reinterpret_cast<bf16_t*>(smem + rel_bytes + (size_t)kTileWaves * 16 * a.bias_stride * sizeof(float)) +
                   (size_t)wave * 64 * kRowStride;                                       // [32 columns][kRowStride]: K rows
     bf16_t* v_s = k_s + 32 * kRowStride;                                                // the same for V rows
-    // DROP: relative-position id of every compact id, what the dropout mask of an edge is drawn from
+    // DROP, RING: relative-position id of every compact id, what the dropout mask of an edge is drawn from
     int32_t* relid_s = reinterpret_cast<int32_t*>(smem + rel_bytes + (size_t)kTileWaves * 16 * a.bias_stride * sizeof(float) +
                                                   (size_t)kTileWaves * 64 * kRowStride * sizeof(bf16_t));   // [cid_pad]
-    if (DROP)
+    if (DROP || RING)
         for (int i = threadIdx.x; i < a.cid_pad; i += blockDim.x) relid_s[i] = i < a.num_cids ? a.cid_to_id[i] : 0;
     // compact relative-position table, zero rows as padding
-    if (REL_LDS) {
+    if (!RING) {
         for (int i = threadIdx.x; i < a.cid_pad * 8; i += blockDim.x) {
             const int cid = i >> 3, c8 = (i & 7) * 8;
             uint4 w = make_uint4(0u, 0u, 0u, 0u);
@@ -238,6 +290,7 @@ __global__ void __launch_bounds__(kTileThreads, 2) fwd_tile_kernel(const TileArg
     }
     __syncthreads();
 
+    const int bias_stride = RING ? kRingStride : a.bias_stride;
     const float qscale = a.scale * kLog2e;
     const rsrc_t rC = make_rsrc(a.cols, (uint32_t)a.num_chunks * 64u);   // [chunks][16] int32
     const rsrc_t rM = make_rsrc(a.map, (uint32_t)a.num_chunks * 512u);   // [chunks][16][16] int16
@@ -279,6 +332,7 @@ __global__ void __launch_bounds__(kTileThreads, 2) fwd_tile_kernel(const TileArg
         c.valid = false;
         c.pair = 0;
         c.npairs = 1;
+        c.b0 = c.b1 = 0;
         c.dvec = 0;
         if (PACKED) c.t = __builtin_amdgcn_readfirstlane(c.t);   // (see cursor_uniform)
         if (compact) {   // the next tile that exists; the walk covers nothing else
@@ -313,6 +367,7 @@ __global__ void __launch_bounds__(kTileThreads, 2) fwd_tile_kernel(const TileArg
         }
     };
     auto advance = [&](TileCursor& c) {
+        c.b0 = c.b1;
         if (c.valid && ++c.pair == c.npairs) {
             c.t += w.step;
             enter_tile(c);
@@ -320,7 +375,8 @@ __global__ void __launch_bounds__(kTileThreads, 2) fwd_tile_kernel(const TileArg
     };
     int node_n[2][2];
     uint2 mp_n[2];
-    auto load_idx = [&](const TileCursor& c) {
+    auto load_idx = [&](TileCursor& c) {
+        if (RING) c.b1 = uniform_i32(a.pair_blocks, (c.cp0 >> 1) + c.pair);
 #pragma unroll
         for (int ci = 0; ci < 2; ++ci) {
             const int at = (c.cp0 + 2 * c.pair + ci) * 16;
@@ -332,6 +388,7 @@ __global__ void __launch_bounds__(kTileThreads, 2) fwd_tile_kernel(const TileArg
     };
     Row<bf16_t> kr[2][2], vr[2][2];   // [chunk][half of its rows]: this lane's 16-byte piece
     bf16x8_t qn0, qn1;                // Q^T operand of the tile whose first pair is in flight
+    RelAhead rel_n;                   // RING: the rows of the table that the pair in flight brings with it
     auto request_rows = [&](const TileCursor& c) {
         const int64_t base = (int64_t)(c.bh / a.H) * a.sb + (int64_t)(c.bh % a.H) * a.sh;
         const rsrc_t rK = make_rsrc(a.K + base, a.slab_bytes), rV = make_rsrc(a.V + base, a.slab_bytes);
@@ -352,6 +409,7 @@ __global__ void __launch_bounds__(kTileThreads, 2) fwd_tile_kernel(const TileArg
             qn0 = *reinterpret_cast<const bf16x8_t*>(a.Q + at);
             qn1 = *reinterpret_cast<const bf16x8_t*>(a.Q + at + 8);
         }
+        if (RING) ring_request(a, relid_s, c, g, j, rel_n);
     };
 
     TileCursor cc, cr, ci;
@@ -389,27 +447,20 @@ __global__ void __launch_bounds__(kTileThreads, 2) fwd_tile_kernel(const TileArg
 #pragma unroll
             for (int f = 0; f < 4; ++f) o[f] = f32x4_t{0.f, 0.f, 0.f, 0.f};
             // bias^T = Rel x Q^T, kept in LDS as [token][compact id]
-            for (int c = 0; c < a.cid_pad; c += 16) {
-                bf16x8_t r0, r1;
-                if (REL_LDS) {
-                    const bf16_t* rrow = rel_s + (c + j) * kRelStride + 16 * g;
-                    r0 = *reinterpret_cast<const bf16x8_t*>(rrow);
-                    r1 = *reinterpret_cast<const bf16x8_t*>(rrow + 8);
-                } else {   // padding ids repeat the last real one; no column carries them
-                    const bf16_t* rrow = a.rel + (int64_t)a.cid_to_id[min(c + j, a.num_cids - 1)] * kD + 16 * g;
-                    r0 = *reinterpret_cast<const bf16x8_t*>(rrow);
-                    r1 = *reinterpret_cast<const bf16x8_t*>(rrow + 8);
-                }
+            for (int c = 0; !RING && c < a.cid_pad; c += 16) {
+                const bf16_t* rrow = rel_s + (c + j) * kRelStride + 16 * g;
+                const bf16x8_t r0 = *reinterpret_cast<const bf16x8_t*>(rrow), r1 = *reinterpret_cast<const bf16x8_t*>(rrow + 8);
                 f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
                 acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(r0, qb0, acc, 0, 0, 0);
                 acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(r1, qb1, acc, 0, 0, 0);
                 *reinterpret_cast<f32x4_t*>(bias_s + j * a.bias_stride + c + 4 * g) = acc;
             }
-            if (a.seq_len) {   // uniform
+            if (!RING && a.seq_len) {   // uniform
                 wave_lds_sync();
-                mask_bias(a, bias_s, cc.tile * 16, seq_length_u(a.seq_len, cc.bh / a.H, a.n), g, j);
+                mask_bias(a, bias_s, cc.tile * 16, seq_length_u(a.seq_len, cc.bh / a.H, a.n), g, j, 0, a.cid_pad, ~0);
             }
         }
+        if (RING) ring_form(a, relid_s, bias_s, cc, qb0, qb1, g, j, rel_n);
         wave_lds_sync();  // the previous pair's reads of k_s, v_s (and the previous tile's of bias_s) are done
 #pragma unroll
         for (int ci2 = 0; ci2 < 2; ++ci2)
@@ -440,7 +491,7 @@ __global__ void __launch_bounds__(kTileThreads, 2) fwd_tile_kernel(const TileArg
             cid[c][2] = (int)(short)(mpc[c].y & 0xFFFFu);
             cid[c][3] = (int)(short)(mpc[c].y >> 16);
 #pragma unroll
-            for (int r = 0; r < 4; ++r) bv[c][r] = bias_s[j * a.bias_stride + max(cid[c][r], 0)];
+            for (int r = 0; r < 4; ++r) bv[c][r] = bias_s[j * bias_stride + (RING ? cid[c][r] & (kRingIds - 1) : max(cid[c][r], 0))];
         }
         f32x4_t s4[2];
 #pragma unroll
@@ -547,9 +598,8 @@ __global__ void __launch_bounds__(kTileThreads, 2) fwd_tile_kernel(const TileArg
 //   dQ_K = scale * (W K_U - delta * P K_U)       (the key part of dQ; lse is known, so
 // no online softmax and no second pass).  Without DENSE, (w, p) of every tile slot goes to `wp` in
 // tile order for rel_grad_tile_kernel, which also adds the relative-position part of dQ.
-// REL_LDS: the compact relative-position table is staged in LDS; otherwise (large tables) its rows
-// are read from memory when a tile forms its bias table.
-// DENSE (needs REL_LDS and cid_pad a multiple of 32): a tile's w = p dP and p are not stored per slot
+// RING: the bias table as in fwd_tile_kernel.
+// DENSE (needs the whole table, not RING, and cid_pad a multiple of 32): a tile's w = p dP and p are not stored per slot
 // for rel_grad_tile_kernel but scattered into two LDS tables [token][compact id] (the ids of a token
 // row are distinct).  When the tile is complete and delta is known, dS = w - delta p is there as a
 // dense 16 x cid_pad matrix (kept as bf16 hi + lo in the row buffers): the relative-position part of
@@ -558,16 +608,16 @@ __global__ void __launch_bounds__(kTileThreads, 2) fwd_tile_kernel(const TileArg
 // transposing reads, into accumulators the wavefront keeps over all its tiles (at most kDenseChunks
 // chunks of 16 ids).  Nothing per slot or per tile leaves for a d_rel kernel; every workgroup writes
 // one copy of d_rel at the end, and drel_reduce_kernel adds the copies in a fixed order.
-template <bool REL_LDS, bool DROP, bool DENSE = false, bool PACKED = false>
+template <bool RING, bool DROP, bool DENSE = false, bool PACKED = false>
 __global__ void __launch_bounds__(kTileThreads, DENSE ? 1 : 2) bwd_q_tile_kernel(const TileArgs a) {
-    static_assert(!DENSE || REL_LDS, "the dense variant multiplies by the staged table");
+    static_assert(!DENSE || !RING, "the dense variant multiplies by the staged table");
     extern __shared__ __align__(16) unsigned char smem[];
     bf16_t* rel_s = reinterpret_cast<bf16_t*>(smem);
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int g = lane >> 4, j = lane & 15;
     const int r8 = lane >> 3, piece = lane & 7;   // coalesced row fetches: row of the instruction, 16-byte piece
-    const size_t rel_bytes = REL_LDS ? (size_t)a.cid_pad * kRelStride * sizeof(bf16_t) : 0;
+    const size_t rel_bytes = !RING ? (size_t)a.cid_pad * kRelStride * sizeof(bf16_t) : 0;
     float* bias_s = reinterpret_cast<float*>(smem + rel_bytes) +
                     (size_t)wave * 16 * a.bias_stride;
     bf16_t* k_s = reinterpret_cast<bf16_t*>(smem + rel_bytes + (size_t)kTileWaves * 16 * a.bias_stride * sizeof(float)) +
@@ -580,9 +630,9 @@ __global__ void __launch_bounds__(kTileThreads, DENSE ? 1 : 2) bwd_q_tile_kernel
     float* w_s = reinterpret_cast<float*>(relid_s + a.cid_pad) + (size_t)wave * 32 * a.bias_stride;
     float2* wp_s = reinterpret_cast<float2*>(w_s);
     const int wp_stride = a.cid_pad + 2;
-    if (DROP)
+    if (DROP || RING)
         for (int i = threadIdx.x; i < a.cid_pad; i += blockDim.x) relid_s[i] = i < a.num_cids ? a.cid_to_id[i] : 0;
-    if (REL_LDS) {
+    if (!RING) {
         for (int i = threadIdx.x; i < a.cid_pad * 8; i += blockDim.x) {
             const int cid = i >> 3, c8 = (i & 7) * 8;
             uint4 w = make_uint4(0u, 0u, 0u, 0u);
@@ -592,6 +642,7 @@ __global__ void __launch_bounds__(kTileThreads, DENSE ? 1 : 2) bwd_q_tile_kernel
     }
     __syncthreads();
 
+    const int bias_stride = RING ? kRingStride : a.bias_stride;
     const float qscale = a.scale * kLog2e;
     const rsrc_t rC = make_rsrc(a.cols, (uint32_t)a.num_chunks * 64u);
     const rsrc_t rM = make_rsrc(a.map, (uint32_t)a.num_chunks * 512u);
@@ -638,6 +689,7 @@ __global__ void __launch_bounds__(kTileThreads, DENSE ? 1 : 2) bwd_q_tile_kernel
         c.valid = false;
         c.pair = 0;
         c.npairs = 1;
+        c.b0 = c.b1 = 0;
         c.dvec = 0;
         if (PACKED) c.t = __builtin_amdgcn_readfirstlane(c.t);   // (see cursor_uniform)
         if (compact) {   // the next tile that exists; the walk covers nothing else
@@ -672,6 +724,7 @@ __global__ void __launch_bounds__(kTileThreads, DENSE ? 1 : 2) bwd_q_tile_kernel
         }
     };
     auto advance = [&](TileCursor& c) {
+        c.b0 = c.b1;
         if (c.valid && ++c.pair == c.npairs) {
             c.t += w.step;
             enter_tile(c);
@@ -679,7 +732,8 @@ __global__ void __launch_bounds__(kTileThreads, DENSE ? 1 : 2) bwd_q_tile_kernel
     };
     int node_n[2][2];
     uint2 mp_n[2];
-    auto load_idx = [&](const TileCursor& c) {
+    auto load_idx = [&](TileCursor& c) {
+        if (RING) c.b1 = uniform_i32(a.pair_blocks, (c.cp0 >> 1) + c.pair);
 #pragma unroll
         for (int ci = 0; ci < 2; ++ci) {
             const int at = (c.cp0 + 2 * c.pair + ci) * 16;
@@ -692,6 +746,7 @@ __global__ void __launch_bounds__(kTileThreads, DENSE ? 1 : 2) bwd_q_tile_kernel
     Row<bf16_t> kr[2][2], vr[2][2];   // [chunk][half of its rows]: this lane's 16-byte piece
     bf16x8_t qn0, qn1, gn0, gn1;      // operands of the tile whose first pair is in flight
     float lse_n = 0.f;
+    RelAhead rel_n;                   // RING: the rows of the table that the pair in flight brings with it
     auto request_rows = [&](const TileCursor& c) {
         const int64_t base = (int64_t)(c.bh / a.H) * a.sb + (int64_t)(c.bh % a.H) * a.sh;
         const rsrc_t rK = make_rsrc(a.K + base, a.slab_bytes), rV = make_rsrc(a.V + base, a.slab_bytes);
@@ -715,6 +770,7 @@ __global__ void __launch_bounds__(kTileThreads, DENSE ? 1 : 2) bwd_q_tile_kernel
             gn1 = load_once16<bf16x8_t>(a.dout + at + 8);
             lse_n = a.lse_r[(PACKED ? (int64_t)(c.bh / a.H) * a.lse_sb + (int64_t)(c.bh % a.H) * a.lse_sh : (int64_t)c.bh * a.N) + tq];
         }
+        if (RING) ring_request(a, relid_s, c, g, j, rel_n);
     };
 
     // DENSE: this wavefront's d_rel sums over its tiles, [id chunk][feature chunk] in the C layout (id 4g + r
@@ -793,25 +849,17 @@ __global__ void __launch_bounds__(kTileThreads, DENSE ? 1 : 2) bwd_q_tile_kernel
 #pragma unroll
             for (int f = 0; f < 4; ++f) ow[f] = op[f] = f32x4_t{0.f, 0.f, 0.f, 0.f};
             // bias^T = Rel x Q^T, kept in LDS as [token][compact id]
-            for (int c = 0; c < a.cid_pad; c += 16) {
-                bf16x8_t r0, r1;
-                if (REL_LDS) {
-                    const bf16_t* rrow = rel_s + (c + j) * kRelStride + 16 * g;
-                    r0 = *reinterpret_cast<const bf16x8_t*>(rrow);
-                    r1 = *reinterpret_cast<const bf16x8_t*>(rrow + 8);
-                } else {   // padding ids repeat the last real one; no column carries them
-                    const bf16_t* rrow = a.rel + (int64_t)a.cid_to_id[min(c + j, a.num_cids - 1)] * kD + 16 * g;
-                    r0 = *reinterpret_cast<const bf16x8_t*>(rrow);
-                    r1 = *reinterpret_cast<const bf16x8_t*>(rrow + 8);
-                }
+            for (int c = 0; !RING && c < a.cid_pad; c += 16) {
+                const bf16_t* rrow = rel_s + (c + j) * kRelStride + 16 * g;
+                const bf16x8_t r0 = *reinterpret_cast<const bf16x8_t*>(rrow), r1 = *reinterpret_cast<const bf16x8_t*>(rrow + 8);
                 f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
                 acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(r0, qb0, acc, 0, 0, 0);
                 acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(r1, qb1, acc, 0, 0, 0);
                 *reinterpret_cast<f32x4_t*>(bias_s + j * a.bias_stride + c + 4 * g) = acc;
             }
-            if (a.seq_len) {   // uniform
+            if (!RING && a.seq_len) {   // uniform
                 wave_lds_sync();
-                mask_bias(a, bias_s, cc.tile * 16, seq_length_u(a.seq_len, cc.bh / a.H, a.n), g, j);
+                mask_bias(a, bias_s, cc.tile * 16, seq_length_u(a.seq_len, cc.bh / a.H, a.n), g, j, 0, a.cid_pad, ~0);
             }
             if (DENSE && !tables_clear) {   // the whole region once; later tiles find it cleared by the reads below
                 for (int i = lane * 4; i < 32 * a.bias_stride; i += 256)
@@ -819,6 +867,7 @@ __global__ void __launch_bounds__(kTileThreads, DENSE ? 1 : 2) bwd_q_tile_kernel
                 tables_clear = true;
             }
         }
+        if (RING) ring_form(a, relid_s, bias_s, cc, qb0, qb1, g, j, rel_n);
         wave_lds_sync();  // the previous pair's reads of k_s, v_s (and the previous tile's of bias_s) are done
 #pragma unroll
         for (int ci2 = 0; ci2 < 2; ++ci2)
@@ -849,7 +898,7 @@ __global__ void __launch_bounds__(kTileThreads, DENSE ? 1 : 2) bwd_q_tile_kernel
             cid[c][2] = (int)(short)(mpc[c].y & 0xFFFFu);
             cid[c][3] = (int)(short)(mpc[c].y >> 16);
 #pragma unroll
-            for (int r = 0; r < 4; ++r) bv[c][r] = bias_s[j * a.bias_stride + max(cid[c][r], 0)];
+            for (int r = 0; r < 4; ++r) bv[c][r] = bias_s[j * bias_stride + (RING ? cid[c][r] & (kRingIds - 1) : max(cid[c][r], 0))];
         }
         f32x4_t s4[2], d4[2];
 #pragma unroll

@@ -178,7 +178,7 @@ void use_schedule(AttnArgs& a, const Schedule& sc) {
 // LDS of fwd_tile_kernel for this graph, or 0 if the tile path does not apply
 struct TilePlan {
     bool ok = false;       // the token tile kernels apply
-    bool rel_lds = false;  // with the compact relative-position table staged in LDS
+    bool ring = false;     // with the bias table as a ring (else whole, out of the relative-position table in LDS)
     int cid_pad = 0, bias_stride = 0;
     size_t lds = 0;
 };
@@ -190,15 +190,23 @@ TilePlan plan_tiles(const bpt_graph* g, const DeviceLimits& lim, bool dense = fa
     t.cid_pad = dense ? (g->tiles.num_cids + 31) & ~31 : (g->tiles.num_cids + 15) & ~15;
     t.bias_stride = t.cid_pad + ((4 - t.cid_pad % 32) + 32) % 32;  // = 4 mod 32: the 16 token rows hit different banks
     const size_t rel = (size_t)t.cid_pad * kRelStride * sizeof(bf16_t);
-    const size_t rest = (size_t)kTileWaves * 16 * t.bias_stride * sizeof(float) +
-                        (size_t)kTileWaves * 64 * kRowStride * sizeof(bf16_t) +
-                        (size_t)t.cid_pad * sizeof(int32_t) +   // relative-position ids of the compact ids (dropout)
-                        (dense ? (size_t)kTileWaves * 32 * t.bias_stride * sizeof(float) : 0);
-    const size_t room = lim.lds - (kMaxLenBatch + 1) * sizeof(int32_t) - 16;   // the kernels' static LDS (prefix sums of a length mix)
-    t.rel_lds = rel + rest <= room;
-    t.lds = t.rel_lds ? rel + rest : rest;
-    // (dense: dS of a tile, bf16 hi and lo with 16 bytes of padding per row, has to fit a wavefront's row buffers)
-    t.ok = dense ? t.rel_lds && 64 * (t.cid_pad + 8) <= 64 * kRowStride * (int)sizeof(bf16_t) : t.lds <= room;
+    const size_t rows = (size_t)kTileWaves * 64 * kRowStride * sizeof(bf16_t) +
+                        (size_t)t.cid_pad * sizeof(int32_t);   // + the relative-position ids of the compact ids
+    const size_t table = (size_t)kTileWaves * 16 * t.bias_stride * sizeof(float);
+    const size_t prefix = (kMaxLenBatch + 1) * sizeof(int32_t) + 16;   // the kernels' static LDS (prefix sums of a length mix)
+    const size_t room = lim.lds - prefix;
+    t.lds = rel + table + rows + (dense ? 2 * table : 0);
+    if (dense) {   // (dS of a tile, bf16 hi and lo with 16 bytes of padding per row, has to fit a wavefront's row buffers)
+        t.ok = t.lds <= room && 64 * (t.cid_pad + 8) <= 64 * kRowStride * (int)sizeof(bf16_t);
+        return t;
+    }
+    // The whole table while two workgroups of it share a compute unit (up to about 100 ids), else the ring.
+    if (2 * (t.lds + prefix) > lim.lds_cu && g->tiles.ring_ok) {
+        t.ring = true;
+        t.bias_stride = kRingStride;
+        t.lds = (size_t)kTileWaves * 16 * kRingStride * sizeof(float) + rows;
+    }
+    t.ok = t.lds <= room;
     return t;
 }
 
@@ -229,17 +237,17 @@ int run_bwd_q_tiles(const bpt_graph* g, const AttnArgs& a, const DeviceLimits& l
     if (dense) {   // no (w, p) pairs: the kernel leaves one copy of d_rel per workgroup
         t.drel_part = a.drel_part;
         const int grid = dense_grid(lim);
-        if (a.delta) return launch_tiles("bwd_q_tile_kernel", bwd_q_tile_kernel<true, false, true, true>, t, lim, tp.lds, st, grid);
-        return a.drop_thr ? launch_tiles("bwd_q_tile_kernel", bwd_q_tile_kernel<true, true, true>, t, lim, tp.lds, st, grid)
-                          : launch_tiles("bwd_q_tile_kernel", bwd_q_tile_kernel<true, false, true>, t, lim, tp.lds, st, grid);
+        if (a.delta) return launch_tiles("bwd_q_tile_kernel", bwd_q_tile_kernel<false, false, true, true>, t, lim, tp.lds, st, grid);
+        return a.drop_thr ? launch_tiles("bwd_q_tile_kernel", bwd_q_tile_kernel<false, true, true>, t, lim, tp.lds, st, grid)
+                          : launch_tiles("bwd_q_tile_kernel", bwd_q_tile_kernel<false, false, true>, t, lim, tp.lds, st, grid);
     }
     if (a.delta)   // a packed batch (no dropout there)
-        return tp.rel_lds ? launch_tiles("bwd_q_tile_kernel", bwd_q_tile_kernel<true, false, false, true>, t, lim, tp.lds, st)
+        return tp.ring ? launch_tiles("bwd_q_tile_kernel", bwd_q_tile_kernel<true, false, false, true>, t, lim, tp.lds, st)
                           : launch_tiles("bwd_q_tile_kernel", bwd_q_tile_kernel<false, false, false, true>, t, lim, tp.lds, st);
     if (a.drop_thr)
-        return tp.rel_lds ? launch_tiles("bwd_q_tile_kernel", bwd_q_tile_kernel<true, true>, t, lim, tp.lds, st)
+        return tp.ring ? launch_tiles("bwd_q_tile_kernel", bwd_q_tile_kernel<true, true>, t, lim, tp.lds, st)
                           : launch_tiles("bwd_q_tile_kernel", bwd_q_tile_kernel<false, true>, t, lim, tp.lds, st);
-    return tp.rel_lds ? launch_tiles("bwd_q_tile_kernel", bwd_q_tile_kernel<true, false>, t, lim, tp.lds, st)
+    return tp.ring ? launch_tiles("bwd_q_tile_kernel", bwd_q_tile_kernel<true, false>, t, lim, tp.lds, st)
                       : launch_tiles("bwd_q_tile_kernel", bwd_q_tile_kernel<false, false>, t, lim, tp.lds, st);
 }
 
@@ -266,6 +274,7 @@ void fill_tile_args(TileArgs& t, const bpt_graph* g, const AttnArgs& a, const Ti
     t.cols = g->tiles.cols;
     t.cid_to_id = g->tiles.cid_to_id;
     t.map = g->tiles.map;
+    t.pair_blocks = g->tiles.pair_blocks;
     t.num_tiles = g->tiles.num_tiles;
     t.num_chunks = g->tiles.num_chunks;
     t.num_cids = g->tiles.num_cids;
@@ -395,12 +404,12 @@ int run_fwd_tiles(const bpt_graph* g, AttnArgs& a, const DeviceLimits& lim, cons
     TileArgs t = {};
     fill_tile_args(t, g, a, tp);
     if (a.delta)   // a packed batch (no dropout there)
-        return tp.rel_lds ? launch_tiles("fwd_tile_kernel", fwd_tile_kernel<true, false, true>, t, lim, tp.lds, st)
+        return tp.ring ? launch_tiles("fwd_tile_kernel", fwd_tile_kernel<true, false, true>, t, lim, tp.lds, st)
                           : launch_tiles("fwd_tile_kernel", fwd_tile_kernel<false, false, true>, t, lim, tp.lds, st);
     if (a.drop_thr)
-        return tp.rel_lds ? launch_tiles("fwd_tile_kernel", fwd_tile_kernel<true, true>, t, lim, tp.lds, st)
+        return tp.ring ? launch_tiles("fwd_tile_kernel", fwd_tile_kernel<true, true>, t, lim, tp.lds, st)
                           : launch_tiles("fwd_tile_kernel", fwd_tile_kernel<false, true>, t, lim, tp.lds, st);
-    return tp.rel_lds ? launch_tiles("fwd_tile_kernel", fwd_tile_kernel<true, false>, t, lim, tp.lds, st)
+    return tp.ring ? launch_tiles("fwd_tile_kernel", fwd_tile_kernel<true, false>, t, lim, tp.lds, st)
                       : launch_tiles("fwd_tile_kernel", fwd_tile_kernel<false, false>, t, lim, tp.lds, st);
 }
 

@@ -36,6 +36,7 @@ struct Schedule {
 // consecutive token rows; its columns are the union of the rows' key nodes in
 // ascending node id, cut into chunks of 16 (an even number of chunks per tile;
 // padding slots repeat a real node and are masked).
+constexpr int kRingBlocks = 8;   // blocks of 16 ids the bias ring of the token-tile kernels holds
 struct TokenTiles {
     int32_t num_tiles = 0;   // n / 16; 0 when the tile path is not built
     int32_t num_chunks = 0;  // chunks of all tiles together
@@ -43,6 +44,9 @@ struct TokenTiles {
     int32_t* chunk_ptr = nullptr;  // [num_tiles+1] first chunk of a tile
     int32_t* cols = nullptr;       // [chunks][16] node id of a column
     int16_t* map = nullptr;        // [chunks][16 rows][16 columns] compact id of the edge, or -1
+    int32_t* pair_blocks = nullptr;   // [chunks / 2] (behind cols) blocks of 16 compact ids the tile's pairs up to this one
+                                      // carry: 1 + the largest id / 16
+    bool ring_ok = false;          // every pair's ids lie within the last kRingBlocks of those blocks
     int32_t* cid_to_id = nullptr;  // [num_cids] compact id -> row of the relative-position table
     int32_t* id_to_cid = nullptr;  // [rows of the table] the inverse, -1 for ids no token row uses
 };
@@ -69,7 +73,7 @@ struct KeyTiles {
     int32_t* tile_info = nullptr;   // [tiles] level | valid keys << 8
     int32_t* cols = nullptr;        // [chunks][16] query node of a column
     int16_t* map = nullptr;         // [chunks][16 keys][16 columns] tile-local relative-position id, or -1
-    int32_t* id_blocks = nullptr;   // [chunks] bit b: a slot of the chunk carries one of the ids 16b .. 16b + 15 (b < 31)
+    int32_t* id_blocks = nullptr;   // [chunks] (behind cols) bit b: a slot of the chunk carries one of the ids 16b .. 16b + 15 (b < 31)
     int32_t* task_tile = nullptr;   // [tasks]
     int32_t* task_c0 = nullptr;     // [tasks] first chunk
     int32_t* task_nch = nullptr;    // [tasks] chunks (even)

@@ -206,6 +206,34 @@ __global__ void token_tile_map(int n, int nb, int W, int zero, const int32_t* __
     }
 }
 
+// one wavefront per tile: for every pair of chunks, the blocks of 16 compact ids met so far (the largest id decides: a
+// tile's columns run through its ids in ascending order, up to the shift between its rows); *too_wide is set when an id
+// of a pair lies more than kRingBlocks blocks before that
+__global__ void token_tile_pair_blocks(int tiles, const int32_t* __restrict__ chunk_ptr, const int16_t* __restrict__ map,
+                                       int32_t* __restrict__ pair_blocks, int32_t* __restrict__ too_wide) {
+    const int t = blockIdx.x, lane = threadIdx.x;
+    if (t >= tiles) return;
+    int blocks = 0;
+    for (int c = chunk_ptr[t]; c < chunk_ptr[t + 1]; c += 2) {
+        int lo = INT32_MAX, hi = -1;
+        const int4 w = *reinterpret_cast<const int4*>(map + (int64_t)c * 256 + 8 * lane);
+        for (const int two : {w.x, w.y, w.z, w.w})
+            for (const int id : {(int)(int16_t)(two & 0xFFFF), two >> 16}) {
+                hi = max(hi, id);
+                if (id >= 0) lo = min(lo, id);
+            }
+        for (int s = 32; s > 0; s >>= 1) {
+            lo = min(lo, __shfl_xor(lo, s));
+            hi = max(hi, __shfl_xor(hi, s));
+        }
+        blocks = max(blocks, (hi >> 4) + 1);   // (hi = -1: no edge, no block)
+        if (lane == 0) {
+            pair_blocks[c >> 1] = blocks;
+            if (hi >= 0 && blocks - (lo >> 4) > kRingBlocks) *too_wide = 1;   // every writer stores the same value
+        }
+    }
+}
+
 // ---- key tiles -----------------------------------------------------------------------------
 struct LevelBases {
     int32_t tile_base[kMaxLevels + 1];   // first tile of every level that has contextual edges
@@ -350,10 +378,10 @@ __global__ void key_tile_id_blocks(int64_t chunks, const int16_t* __restrict__ m
     if (c >= chunks) return;
     const int lane = threadIdx.x & 63;
     int mask = 0;
-    for (int i = lane; i < 256; i += 64) {
-        const int id = map[c * 256 + i];
-        if (id >= 0 && id < 31 * 16) mask |= 1 << (id >> 4);
-    }
+    const int2 w = *reinterpret_cast<const int2*>(map + c * 256 + 4 * lane);
+    for (const int two : {w.x, w.y})
+        for (const int id : {(int)(int16_t)(two & 0xFFFF), two >> 16})
+            if (id >= 0 && id < 31 * 16) mask |= 1 << (id >> 4);
     for (int s = 32; s > 0; s >>= 1) mask |= __shfl_xor(mask, s);
     if (lane == 0) id_blocks[c] = mask;
 }
@@ -544,13 +572,17 @@ int build_tile_metadata(bpt_graph* g, const int32_t* cnt_l, const int32_t* min_l
     const int64_t chunks = h_tot[1];
     const bool token_ok = num_cids <= 32767 && chunks * 512 <= ((int64_t)256 << 20);
     if (!token_ok) return BPT_OK;   // num_tiles stays 0: no tile path (the destroy call frees what was allocated)
-    if ((rc = device_alloc(&tt.cols, (size_t)chunks * 16)) || (rc = device_alloc(&tt.map, (size_t)chunks * 256))) return rc;
+    if ((rc = device_alloc(&tt.cols, (size_t)chunks * 16 + chunks / 2)) || (rc = device_alloc(&tt.map, (size_t)chunks * 256))) return rc;
+    tt.pair_blocks = tt.cols + chunks * 16;
     BPT_HIP(hipMemsetAsync(tt.map, 0xFF, sizeof(int16_t) * (size_t)chunks * 256, st));
     hipLaunchKernelGGL(token_tile_cols, dim3(tiles), dim3(64), 0, st, nb, tt.chunk_ptr, tile_lo.as<int32_t>(),
                        tile_hi.as<int32_t>(), tile_first.as<int32_t>(), tt.cols);
     hipLaunchKernelGGL(token_tile_map, dim3((n + kTB - 1) / kTB), dim3(kTB), 0, st, n, nb, W, zero, g->row_ptr, g->col,
                        g->rel, tt.chunk_ptr, tile_lo.as<int32_t>(), tile_first.as<int32_t>(), tt.id_to_cid, tt.map);
+    hipLaunchKernelGGL(token_tile_pair_blocks, dim3(tiles), dim3(64), 0, st, tiles, tt.chunk_ptr, tt.map, tt.pair_blocks, d_tot + 6);
+    int32_t too_wide = 0;
     BPT_HIP(hipGetLastError());
+    BPT_HIP(hipMemcpyAsync(&too_wide, d_tot + 6, sizeof too_wide, hipMemcpyDeviceToHost, st));   // (read behind the last synchronisation)
     tt.num_cids = num_cids;
     tt.num_chunks = (int32_t)chunks;
     tt.num_tiles = tiles;
@@ -558,13 +590,13 @@ int build_tile_metadata(bpt_graph* g, const int32_t* cnt_l, const int32_t* min_l
     const int64_t kchunks = h_tot[2];
     if (want_keys && kchunks * 512 <= ((int64_t)512 << 20)) {
         const int num_tasks = h_tot[3], num_part = h_tot[4], num_multi = h_tot[5];
-        if ((rc = device_alloc(&kt.cols, (size_t)kchunks * 16)) || (rc = device_alloc(&kt.map, (size_t)kchunks * 256)) ||
-            (rc = device_alloc(&kt.id_blocks, (size_t)kchunks)) ||
+        if ((rc = device_alloc(&kt.cols, (size_t)kchunks * 17)) || (rc = device_alloc(&kt.map, (size_t)kchunks * 256)) ||
             (rc = device_alloc(&kt.task_tile, num_tasks)) || (rc = device_alloc(&kt.task_c0, num_tasks)) ||
             (rc = device_alloc(&kt.task_nch, num_tasks)) || (rc = device_alloc(&kt.task_part, num_tasks)) ||
             (rc = device_alloc(&kt.task_ntiles, num_tasks)) ||
             (rc = device_alloc(&kt.multi_tile, num_multi)) || (rc = device_alloc(&kt.multi_ptr, (size_t)num_multi + 1)))
             return rc;
+        kt.id_blocks = kt.cols + kchunks * 16;
         BPT_HIP(hipMemsetAsync(kt.map, 0xFF, sizeof(int16_t) * (size_t)kchunks * 256, st));
         hipLaunchKernelGGL(key_tile_cols, dim3(nkt), dim3(64), 0, st, n, num_levels, kt.chunk_ptr, kt.tile_node0, kt.tile_info,
                            klo.as<int32_t>(), khi.as<int32_t>(), anc_first.as<int32_t>(), kt.cols);
@@ -607,6 +639,7 @@ int build_tile_metadata(bpt_graph* g, const int32_t* cnt_l, const int32_t* min_l
     }
     // the temporaries are freed when this function returns: wait for the kernels that read them
     BPT_HIP(hipStreamSynchronize(st));
+    tt.ring_ok = too_wide == 0;
     return BPT_OK;
 }
 

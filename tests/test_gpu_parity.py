@@ -184,6 +184,21 @@ def test_key_tiles_of_many_ids(n, k, causal):
     run_case(w, x, scaled=True)
 
 
+# the bias table of a token tile whole (up to 96 ids) and as a ring of 128: the last and first k of either, a whole turn of
+# the ring and many, ids that end inside a block of 16, levels narrower than a pair of chunks (k = 6) and the largest table
+@pytest.mark.parametrize("n,k,causal,lengths", [
+    (4096, 10, True, None), (4096, 11, True, None), (1024, 5, False, None), (1024, 6, False, None), (256, 63, False, None), (8192, 15, True, None),
+    (512, 33, False, [512, 400, 17]), (1024, 20, True, [1000, 1024]), (2048, 72, False, None), (64, 31, False, [40, 64, 1])])
+def test_bias_table_whole_and_as_a_ring(n, k, causal, lengths):
+    w = Workload("ring%d" % k, 9, n, k, causal, len(lengths) if lengths else 1, 2, 64, "bf16", True)
+    if lengths:
+        run_lengths_case(w, lengths)
+        return
+    x = make_inputs(w)
+    x["Rel"] = x["Rel"] * np.float32(16)   # exact in bf16; a wrong row of the table shifts a score by about its own size
+    run_case(w, x, scaled=True)
+
+
 @pytest.mark.parametrize("name", FULL)
 def test_full_size_configuration(name):
     # configurations 2-5 at their full sizes, every output element against the oracle
