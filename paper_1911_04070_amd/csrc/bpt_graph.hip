@@ -323,10 +323,10 @@ __global__ void t_fill_tokens(int n, int k, const int32_t* __restrict__ row_ptr,
                               const int32_t* __restrict__ cnt_l, const int32_t* __restrict__ min_l,
                               const int32_t* __restrict__ min_r, int32_t* __restrict__ t_src,
                               int32_t* __restrict__ t_eid, int32_t* __restrict__ t_rel) {
-    int i = blockIdx.x * blockDim.x + threadIdx.x;
+    const int i = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);   // one wavefront per token row
     if (i >= n) return;
     const int W = 2 * (k + 1) + 1, zero = k + 1;
-    for (int e = row_ptr[i]; e < row_ptr[i + 1]; ++e) {
+    for (int e = row_ptr[i] + (int)(threadIdx.x & 63); e < row_ptr[i + 1]; e += 64) {
         int r = rel[e];
         int order = r % W - zero;
         int v = col[e];
@@ -712,7 +712,6 @@ void free_tiles(TokenTiles& t) {
 
 void free_key_tiles(KeyTiles& t) {
     (void)hipFree(t.chunk_ptr);
-    (void)hipFree(t.id_blocks);
     (void)hipFree(t.tile_node0);
     (void)hipFree(t.tile_info);
     (void)hipFree(t.cols);
@@ -806,7 +805,7 @@ int build(int32_t n, int32_t k, int32_t causal, hipStream_t st, bpt_graph* g) {
     BPT_HIP(hipGetLastError());
     rc = exclusive_scan(deg.as<int32_t>(), g->t_ptr, num_nodes, (int32_t)e_all, block_sums.as<int32_t>(), st);
     if (rc) return rc;
-    hipLaunchKernelGGL(t_fill_tokens, dim3(token_blocks), dim3(tb), 0, st, n, k, g->row_ptr, g->col, g->rel, g->t_ptr,
+    hipLaunchKernelGGL(t_fill_tokens, dim3((n + tb / 64 - 1) / (tb / 64)), dim3(tb), 0, st, n, k, g->row_ptr, g->col, g->rel, g->t_ptr,
                        cnt_l.as<int32_t>(), min_l.as<int32_t>(), min_r.as<int32_t>(), g->t_src, g->t_eid, g->t_rel);
     if (aff > 0)
         hipLaunchKernelGGL(t_fill_spans, dim3((int)((aff + tb - 1) / tb)), dim3(tb), 0, st, n, num_levels,
@@ -973,7 +972,7 @@ int build_batch(int32_t n, int32_t k, int32_t causal, const int32_t* lengths, in
     BPT_HIP(hipGetLastError());
     rc = exclusive_scan(deg.as<int32_t>(), g->t_ptr, num_nodes, (int32_t)e_all, block_sums.as<int32_t>(), st);
     if (rc) return rc;
-    hipLaunchKernelGGL(t_fill_tokens, dim3(token_blocks), dim3(tb), 0, st, T, k, g->row_ptr, g->col, g->rel, g->t_ptr,
+    hipLaunchKernelGGL(t_fill_tokens, dim3((T + tb / 64 - 1) / (tb / 64)), dim3(tb), 0, st, T, k, g->row_ptr, g->col, g->rel, g->t_ptr,
                        cnt_l.as<int32_t>(), min_l.as<int32_t>(), min_r.as<int32_t>(), g->t_src, g->t_eid, g->t_rel);
     if (aff > 0)
         hipLaunchKernelGGL(batch_t_fill_spans, dim3((unsigned)((aff + tb - 1) / tb)), dim3(tb), 0, st, T, B, num_levels,

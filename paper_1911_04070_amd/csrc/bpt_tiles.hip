@@ -188,18 +188,20 @@ __global__ void token_tile_cols(int nb, const int32_t* __restrict__ chunk_ptr, c
     }
 }
 
-// one thread per token row: the compact relative-position id of each of its edges at its (row, column) slot
+// one wavefront per token row (a thread per row walks up to hundreds of edges, with less than one wavefront per compute unit:
+// k = 64, n = 8192 took this kernel and key_tile_map_tokens 0.4 ms each): the compact relative-position id of each of
+// its edges at its (row, column) slot
 __global__ void token_tile_map(int n, int nb, int W, int zero, const int32_t* __restrict__ row_ptr,
                                const int32_t* __restrict__ col, const int32_t* __restrict__ rel,
                                const int32_t* __restrict__ chunk_ptr, const int32_t* __restrict__ tile_lo,
                                const int32_t* __restrict__ tile_first, const int32_t* __restrict__ id_to_cid,
                                int16_t* __restrict__ map) {
-    const int u = blockIdx.x * blockDim.x + threadIdx.x;
+    const int u = blockIdx.x * (kTB / 64) + (threadIdx.x >> 6), lane = threadIdx.x & 63;
     if (u >= n) return;
     const int t = u >> 4, r = u & 15;
     const int64_t m0 = (int64_t)chunk_ptr[t] * 256;
     const int e1 = row_ptr[u + 1];
-    for (int e = row_ptr[u]; e < e1; ++e) {
+    for (int e = row_ptr[u] + lane; e < e1; e += 64) {
         const int id = rel[e], q = token_bucket(id, W, zero);
         const int slot = tile_first[(int64_t)t * nb + q] + col[e] - tile_lo[(int64_t)t * nb + q];
         map[m0 + ((int64_t)(slot >> 4) * 16 + r) * 16 + (slot & 15)] = (int16_t)id_to_cid[id];
@@ -333,17 +335,17 @@ __global__ void key_tile_cols(int n, int num_levels, const int32_t* __restrict__
     }
 }
 
-// one thread per token row: tile-local relative-position id (order + k + 1) of each of its edges
+// one wavefront per token row: tile-local relative-position id (order + k + 1) of each of its edges
 __global__ void key_tile_map_tokens(int n, int W, LevelBases lb, const int32_t* __restrict__ row_ptr,
                                     const int32_t* __restrict__ col, const int32_t* __restrict__ rel,
                                     const int32_t* __restrict__ kchunk_ptr, const int32_t* __restrict__ tile_node0,
                                     const int32_t* __restrict__ klo, const int32_t* __restrict__ kfirst,
                                     int16_t* __restrict__ map) {
-    const int u = blockIdx.x * blockDim.x + threadIdx.x;
+    const int u = blockIdx.x * (kTB / 64) + (threadIdx.x >> 6), lane = threadIdx.x & 63;
     if (u >= n) return;
     const int zero = (W - 1) / 2;
     const int e1 = row_ptr[u + 1];
-    for (int e = row_ptr[u]; e < e1; ++e) {
+    for (int e = row_ptr[u] + lane; e < e1; e += 64) {
         const int l = rel[e] / W, w = rel[e] % W;
         const int kt = lb.tile_base[l] + ((col[e] - level_off(n, l)) >> 4);
         const int b = 2 * kt + ((l > 0 && w - zero < 0) ? 1 : 0);
@@ -577,7 +579,7 @@ int build_tile_metadata(bpt_graph* g, const int32_t* cnt_l, const int32_t* min_l
     BPT_HIP(hipMemsetAsync(tt.map, 0xFF, sizeof(int16_t) * (size_t)chunks * 256, st));
     hipLaunchKernelGGL(token_tile_cols, dim3(tiles), dim3(64), 0, st, nb, tt.chunk_ptr, tile_lo.as<int32_t>(),
                        tile_hi.as<int32_t>(), tile_first.as<int32_t>(), tt.cols);
-    hipLaunchKernelGGL(token_tile_map, dim3((n + kTB - 1) / kTB), dim3(kTB), 0, st, n, nb, W, zero, g->row_ptr, g->col,
+    hipLaunchKernelGGL(token_tile_map, dim3((n + kTB / 64 - 1) / (kTB / 64)), dim3(kTB), 0, st, n, nb, W, zero, g->row_ptr, g->col,
                        g->rel, tt.chunk_ptr, tile_lo.as<int32_t>(), tile_first.as<int32_t>(), tt.id_to_cid, tt.map);
     hipLaunchKernelGGL(token_tile_pair_blocks, dim3(tiles), dim3(64), 0, st, tiles, tt.chunk_ptr, tt.map, tt.pair_blocks, d_tot + 6);
     int32_t too_wide = 0;
@@ -600,7 +602,7 @@ int build_tile_metadata(bpt_graph* g, const int32_t* cnt_l, const int32_t* min_l
         BPT_HIP(hipMemsetAsync(kt.map, 0xFF, sizeof(int16_t) * (size_t)kchunks * 256, st));
         hipLaunchKernelGGL(key_tile_cols, dim3(nkt), dim3(64), 0, st, n, num_levels, kt.chunk_ptr, kt.tile_node0, kt.tile_info,
                            klo.as<int32_t>(), khi.as<int32_t>(), anc_first.as<int32_t>(), kt.cols);
-        hipLaunchKernelGGL(key_tile_map_tokens, dim3((n + kTB - 1) / kTB), dim3(kTB), 0, st, n, W, lb, g->row_ptr, g->col,
+        hipLaunchKernelGGL(key_tile_map_tokens, dim3((n + kTB / 64 - 1) / (kTB / 64)), dim3(kTB), 0, st, n, W, lb, g->row_ptr, g->col,
                            g->rel, kt.chunk_ptr, kt.tile_node0, klo.as<int32_t>(), kfirst.as<int32_t>(), kt.map);
         const int token_tiles = lb.tile_base[1];
         hipLaunchKernelGGL(key_tile_map_ancestors, dim3((token_tiles * 16 + kTB - 1) / kTB), dim3(kTB), 0, st, num_levels, W,
