@@ -37,7 +37,8 @@ struct AttnArgs {
     const int32_t *ptr, *ia, *ib;
     // schedule
     const int32_t *seg_row, *seg_begin, *seg_part, *tile_ptr;
-    int32_t num_tiles, num_part;
+    int32_t num_tiles, num_segs, num_part;
+    int32_t split;          // workgroups that share a tile of the schedule (gather kernels)
     int32_t rel_rows_lds;   // rows of the r table staged in LDS (0: read it from global memory)
     int32_t drel_rows;      // rows of d_rel that token rows can touch (levels with contextual edges)
     int32_t drel_block;     // token rows per block of rel_grad_kernel

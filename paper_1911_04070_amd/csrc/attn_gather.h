@@ -186,6 +186,9 @@ template <typename T, bool REL_LDS>
 __global__ void __launch_bounds__(kThreads) fwd_kernel(const AttnArgs a) {
     extern __shared__ __align__(16) unsigned char smem[];
     T* rel_s = reinterpret_cast<T*>(smem);
+    const int units = a.num_tiles * a.split;
+    TileWalk w(a.BH * units);
+    if (w.t >= w.t_end) return;   // (the whole workgroup: nothing to do)
     if (REL_LDS) {
         stage_table(rel_s, static_cast<const T*>(a.rel), a.rel_rows_lds * kD);
         __syncthreads();
@@ -194,14 +197,14 @@ __global__ void __launch_bounds__(kThreads) fwd_kernel(const AttnArgs a) {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // wave-uniform: row bookkeeping stays scalar
     const int nwaves = blockDim.x >> 6;
     const rsrc_t rIa = make_rsrc(a.ia, a.idx_bytes), rIb = make_rsrc(a.ib, a.idx_bytes);
-    for (TileWalk w(a.BH * a.num_tiles); w.t < w.t_end; w.t += w.step) {
-        const int bh = w.t / a.num_tiles, tile = w.t - bh * a.num_tiles;
+    for (; w.t < w.t_end; w.t += w.step) {
+        const int bh = w.t / units, unit = w.t - bh * units, tile = unit / a.split, sub_tile = unit - tile * a.split;
         const int64_t base = (int64_t)(bh / a.H) * a.sb + (int64_t)(bh % a.H) * a.sh;
         const rsrc_t rK = make_rsrc(static_cast<const T*>(a.K) + base, a.slab_bytes);
         const rsrc_t rV = make_rsrc(static_cast<const T*>(a.V) + base, a.slab_bytes);
         const int len = seq_length(a.seq_len, bh / a.H, a.n_tokens);
         const int s1 = a.tile_ptr[tile + 1];
-        for (int s = a.tile_ptr[tile] + wave; s < s1; s += nwaves) {
+        for (int s = a.tile_ptr[tile] + sub_tile * nwaves + wave; s < s1; s += nwaves * a.split) {
             const int u = a.seg_row[s];
             const int e0 = a.seg_begin[s];
             const int e1 = min(e0 + kSeg, a.ptr[u + 1]);
@@ -413,6 +416,9 @@ template <typename T, bool REL_LDS>
 __global__ void __launch_bounds__(kThreads) bwd_q_kernel(const AttnArgs a) {
     extern __shared__ __align__(16) unsigned char smem[];
     T* rel_s = reinterpret_cast<T*>(smem);
+    const int units = a.num_tiles * a.split;
+    TileWalk w(a.BH * units);
+    if (w.t >= w.t_end) return;   // (the whole workgroup: nothing to do)
     if (REL_LDS) {
         stage_table(rel_s, static_cast<const T*>(a.rel), a.rel_rows_lds * kD);
         __syncthreads();
@@ -421,14 +427,14 @@ __global__ void __launch_bounds__(kThreads) bwd_q_kernel(const AttnArgs a) {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int nwaves = blockDim.x >> 6;
     const rsrc_t rIa = make_rsrc(a.ia, a.idx_bytes), rIb = make_rsrc(a.ib, a.idx_bytes);
-    for (TileWalk w(a.BH * a.num_tiles); w.t < w.t_end; w.t += w.step) {
-        const int bh = w.t / a.num_tiles, tile = w.t - bh * a.num_tiles;
+    for (; w.t < w.t_end; w.t += w.step) {
+        const int bh = w.t / units, unit = w.t - bh * units, tile = unit / a.split, sub_tile = unit - tile * a.split;
         const int64_t base = (int64_t)(bh / a.H) * a.sb + (int64_t)(bh % a.H) * a.sh;
         const rsrc_t rK = make_rsrc(static_cast<const T*>(a.K) + base, a.slab_bytes);
         const rsrc_t rV = make_rsrc(static_cast<const T*>(a.V) + base, a.slab_bytes);
         const int len = seq_length(a.seq_len, bh / a.H, a.n_tokens);
         const int s1 = a.tile_ptr[tile + 1];
-        for (int s = a.tile_ptr[tile] + wave; s < s1; s += nwaves) {
+        for (int s = a.tile_ptr[tile] + sub_tile * nwaves + wave; s < s1; s += nwaves * a.split) {
             const int u = a.seg_row[s];
             const int e0 = a.seg_begin[s];
             const int e1 = min(e0 + kSeg, a.ptr[u + 1]);
@@ -552,6 +558,9 @@ template <typename T, bool REL_LDS>
 __global__ void __launch_bounds__(kThreads) bwd_kv_kernel(const AttnArgs a) {
     extern __shared__ __align__(16) unsigned char smem[];
     T* rel_s = reinterpret_cast<T*>(smem);
+    const int units = a.num_tiles * a.split;
+    TileWalk w(a.BH * units);
+    if (w.t >= w.t_end) return;   // (the whole workgroup: nothing to do)
     if (REL_LDS) {
         stage_table(rel_s, static_cast<const T*>(a.rel), a.rel_rows_lds * kD);
         __syncthreads();
@@ -560,14 +569,14 @@ __global__ void __launch_bounds__(kThreads) bwd_kv_kernel(const AttnArgs a) {
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int nwaves = blockDim.x >> 6;
     const rsrc_t rIa = make_rsrc(a.ia, a.idx_bytes), rIb = make_rsrc(a.ib, a.idx_bytes);
-    for (TileWalk w(a.BH * a.num_tiles); w.t < w.t_end; w.t += w.step) {
-        const int bh = w.t / a.num_tiles, tile = w.t - bh * a.num_tiles;
+    for (; w.t < w.t_end; w.t += w.step) {
+        const int bh = w.t / units, unit = w.t - bh * units, tile = unit / a.split, sub_tile = unit - tile * a.split;
         const int64_t base = (int64_t)(bh / a.H) * a.sb + (int64_t)(bh % a.H) * a.sh;
         const rsrc_t rQ = make_rsrc(static_cast<const T*>(a.Q) + base, a.slab_bytes);
         const rsrc_t rG = make_rsrc(static_cast<const T*>(a.dout) + base, a.slab_bytes);
         const rsrc_t rS = make_rsrc(a.stat + (int64_t)bh * a.N, (uint32_t)a.N * 8u);
         const int s1 = a.tile_ptr[tile + 1];
-        for (int s = a.tile_ptr[tile] + wave; s < s1; s += nwaves) {
+        for (int s = a.tile_ptr[tile] + sub_tile * nwaves + wave; s < s1; s += nwaves * a.split) {
             const int v = a.seg_row[s];
             const int e0 = a.seg_begin[s];
             const int e1 = min(e0 + kSeg, a.ptr[v + 1]);
