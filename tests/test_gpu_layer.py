@@ -253,3 +253,43 @@ def test_misaligned_tensors_are_refused():
     bpt.bpt_layer_fwd(g, flat[8:8 + X.size].view(X.shape), Rd, pd, heads)     # 16 bytes off: fine
     torch.cuda.synchronize()
     g.destroy()
+
+
+# With Wo = 0 the attention leaves no trace in Z, and Y and the gradients of the feed-forward net and both
+# normalisations are those of a chain of row-wise maps, which torch differentiates in 64 bits.  The shapes are the
+# edges of the row kernels: more rows than wavefronts in flight, a width that fills a lane's chunks only in part (9
+# and 17 heads), hidden widths that are no multiple of 16, and contractions over the rows whose equal slices leave
+# rows over -- there dY is zero on all other rows, so that the sums consist of the left-over rows alone.  The bounds
+# are those of test_layer_forward and of the decisive cases of test_layer_backward: the same roundings to bf16.
+@pytest.mark.parametrize("n,B,heads,d_ff,last_rows", [
+    (8192, 1, 1, 72, 3), (4096, 1, 1, 72, 1), (2048, 3, 1, 64, 0), (64, 1, 9, 264, 0), (32, 2, 17, 1096, 0), (16, 1, 3, 8, 0),
+])
+def test_row_kernels_at_their_edges(n, B, heads, d_ff, last_rows):
+    print("row kernels", n, B, heads, d_ff, last_rows, flush=True)
+    X, Rel, p = make_case(n, 2, True, B, heads, d_ff, 500 + n + heads, False)
+    p["Wo"] = np.zeros_like(p["Wo"])
+    p["b1"] = np.where(np.arange(d_ff) % 2 == 0, 6.0, -6.0).astype(np.float32)
+    dY = round_to_bf16(np.random.Generator(np.random.PCG64(9)).standard_normal(X.shape).astype(np.float32))[0]
+    if last_rows:
+        dY[:, :-last_rows] = 0
+    g = bpt.bpt_build_graph(n, 2, True)
+    fws, bws = bpt.layer_workspace_bytes(g, B, heads, d_ff)
+    ws_f = torch.empty(fws, dtype=torch.uint8, device="cuda")
+    ws_b = torch.empty(bws, dtype=torch.uint8, device="cuda")
+    Xd, Rd, pd = torch.from_numpy(X).to(torch.bfloat16).cuda(), torch.from_numpy(Rel).to(torch.bfloat16).cuda(), to_dev(p)
+    Y = bpt.bpt_layer_fwd(g, Xd, Rd, pd, heads, workspace=ws_f)
+    dX, _, grads = bpt.bpt_layer_bwd(g, Xd, Rd, pd, heads, ws_f, torch.from_numpy(dY).to(torch.bfloat16).cuda(), workspace=ws_b)
+    torch.cuda.synchronize()
+    leaf = {w: torch.from_numpy(v).double().requires_grad_() for w, v in p.items() if w not in ("Wq", "Wk", "Wv", "Wo")}
+    x = torch.from_numpy(X).double().requires_grad_()
+    norm = torch.nn.functional.layer_norm
+    z = norm(x, x.shape[-1:], leaf["g1"], leaf["beta1"], 1e-5)
+    y = norm(z + torch.relu(z @ leaf["W1"] + leaf["b1"]) @ leaf["W2"] + leaf["b2"], x.shape[-1:], leaf["g2"], leaf["beta2"], 1e-5)
+    y.backward(torch.from_numpy(dY).double())
+    assert float((Y.double().cpu() - y).abs().max()) <= TOL
+    worst = {"dX": (dX, x.grad)}
+    worst.update({"d" + w: (grads["d" + w], v.grad) for w, v in leaf.items()})
+    worst = {w: float((a.double().cpu() - ref).abs().max() / ref.abs().max()) for w, (a, ref) in worst.items()}
+    print("   relative max-abs errors", {w: float("%.2g" % v) for w, v in worst.items()}, flush=True)
+    assert all(v <= BWD_TOL_DECISIVE for v in worst.values()), worst
+    g.destroy()
