@@ -846,20 +846,31 @@ int batch_tables(int32_t n, int32_t k, int32_t causal, const int32_t* lengths, i
         if ((rc = build(n, k, causal, st, g->tree))) return rc;
     }
     g->ctx_levels = g->tree->ctx_levels;
-    std::vector<int32_t> h_delta((size_t)num_levels * B);
-    for (int l = 0; l < num_levels; ++l)
-        for (int b = 0; b < B; ++b) h_delta[(size_t)l * B + b] = g->first_row[(size_t)l * B + b] - (int32_t)level_offset(n, l);
-    std::vector<int32_t> h_len(lengths, lengths + B);
-    if ((rc = upload(h_delta, &g->d_delta)) || (rc = upload(h_len, &g->d_lengths))) return rc;
-    // the roots (the last level keeps one node of every sequence that has a token)
-    std::vector<int32_t> h_root_row((size_t)B), h_root_seq;
+    // the four small tables as one block: one allocation, one copy and one free per batch instead of four of each (a
+    // step that builds its graph waits for every one of them: two layers on 32 packed sentences, 355 -> 243 us from the
+    // end of one step to the first kernel of the next)
     const size_t top = (size_t)(num_levels - 1) * B;
+    std::vector<int32_t> h((size_t)num_levels * B);
+    for (int l = 0; l < num_levels; ++l)
+        for (int b = 0; b < B; ++b) h[(size_t)l * B + b] = g->first_row[(size_t)l * B + b] - (int32_t)level_offset(n, l);
+    auto append = [&](size_t count) {   // every table starts on a 256-byte boundary
+        const size_t at = (h.size() + 63) / 64 * 64;
+        h.resize(at + count, 0);
+        return at;
+    };
+    const size_t len_at = append((size_t)B), row_at = append((size_t)B), seq_at = append((size_t)B);
+    std::copy(lengths, lengths + B, h.begin() + len_at);
+    // the roots (the last level keeps one node of every sequence that has a token)
     g->first_root = g->first_row[top];
+    size_t roots = 0;
     for (int b = 0; b < B; ++b) {
-        h_root_row[b] = g->row_count[top + b] > 0 ? g->first_row[top + b] : -1;
-        if (g->row_count[top + b] > 0) h_root_seq.push_back(b);
+        h[row_at + b] = g->row_count[top + b] > 0 ? g->first_row[top + b] : -1;
+        if (g->row_count[top + b] > 0) h[seq_at + roots++] = b;
     }
-    if ((rc = upload(h_root_row, &g->d_root_row)) || (rc = upload(h_root_seq, &g->d_root_seq))) return rc;
+    if ((rc = upload(h, &g->d_delta))) return rc;
+    g->d_lengths = g->d_delta + len_at;
+    g->d_root_row = g->d_delta + row_at;
+    g->d_root_seq = g->d_delta + seq_at;
     return BPT_OK;
 }
 
@@ -1135,10 +1146,7 @@ void bpt_graph_destroy(bpt_graph_t* g) {
     bpt::free_schedule(g->fwd_span);
     bpt::free_tiles(g->tiles);
     bpt::free_key_tiles(g->ktiles);
-    (void)hipFree(g->d_lengths);
-    (void)hipFree(g->d_delta);
-    (void)hipFree(g->d_root_row);
-    (void)hipFree(g->d_root_seq);
+    (void)hipFree(g->d_delta);   // with the lengths and the roots' tables behind it
     if (g->owns_tree) bpt_graph_destroy(g->tree);
     delete g;
 }

@@ -92,7 +92,8 @@ struct bpt_graph {
     int32_t batch = 0;            // sequences packed into this graph (bpt_build_batch_graph); 0: the graph of one sequence
     std::vector<int32_t> first_row, row_count;   // batch graph: [level][sequence] first node row and node count
     // batch graph, for the matrix-core kernels: the graph of one sequence of n tokens (their tile metadata), and on the
-    // device the lengths [sequence] and delta[level][sequence] = first_row - first id of the level in that tree
+    // device the lengths [sequence] and delta[level][sequence] = first_row - first id of the level in that tree (one
+    // allocation, d_delta, holds these and the roots' tables)
     bpt_graph* tree = nullptr;
     bool owns_tree = false;       // built by this graph (else shared with the caller, who keeps it alive)
     int32_t *d_lengths = nullptr, *d_delta = nullptr;
