@@ -32,8 +32,8 @@ __device__ __forceinline__ void fwd_segment(const AttnArgs& a, const T* rel_s, r
                                             rsrc_t rIb, int bh, int64_t base, int u, int e0, int e1, int part,
                                             int lane, int len) {
     const int slot = lane >> 3, sub = lane & 7;
-    const int lane_off = sub * 8 * (int)sizeof(T);
-    const T* relg = static_cast<const T*>(a.rel) + sub * 8;
+    const int lane_off = first_feature<T>(sub) * (int)sizeof(T);
+    const T* relg = static_cast<const T*>(a.rel) + first_feature<T>(sub);
     const bool row_kept = node_kept(a, u, len);
     const uint32_t rowh = drop_row_hash(drop_bh_hash(a.drop_seed, bh), u);
 
@@ -51,7 +51,7 @@ __device__ __forceinline__ void fwd_segment(const AttnArgs& a, const T* rel_s, r
     }
     Row<T> k0 = gather_row<T>(rK, c0, a.row_bytes, lane_off), v0 = gather_row<T>(rV, c0, a.row_bytes, lane_off);
 
-    const Row<T> q = load_row(static_cast<const T*>(a.Q) + base + (int64_t)u * a.sn + sub * 8);
+    const Row<T> q = load_row(static_cast<const T*>(a.Q) + base + (int64_t)u * a.sn + first_feature<T>(sub));
     const float qscale = a.scale * kLog2e;
     float shift = 0.f;
     if (SPAN)  // r_anc(level) is common to the whole row
@@ -77,7 +77,7 @@ __device__ __forceinline__ void fwd_segment(const AttnArgs& a, const T* rel_s, r
         float vv[8], d = 0.f;
         if (!SPAN) {
             const int rid = valid ? r0 : 0;  // a masked lane may hold an id of some other row
-            d = dot8(q, REL_LDS ? load_row(rel_s + rid * kD + sub * 8) : load_row(relg + (int64_t)rid * kD), 0.f);
+            d = dot8(q, REL_LDS ? load_row(rel_s + rid * kD + first_feature<T>(sub)) : load_row(relg + (int64_t)rid * kD), 0.f);
         }
         d = dot8(q, kc, d);
         float sc = sum8(d) * qscale + shift;
@@ -114,7 +114,7 @@ __device__ __forceinline__ void fwd_segment(const AttnArgs& a, const T* rel_s, r
 #pragma unroll
     for (int i = 0; i < 8; ++i) acc[i] *= c;
     const float mine = reduce_slots8(acc, lane);
-    const int col = sub * 8 + slot_elem(lane);
+    const int col = feature_of<T>(sub, slot_elem(lane));
     if (part < 0) {
         store1(static_cast<T*>(a.out) + base + (int64_t)u * a.sn + col, l > 0.f ? mine / l : 0.f);
         if (lane == 0) a.lse_w[(int64_t)bh * a.N + u] = l > 0.f ? (mall + fast_log2(l)) * kLn2 : 0.f;
@@ -137,14 +137,14 @@ template <typename T>
 __device__ __forceinline__ void fwd_span8(const AttnArgs& a, rsrc_t rK, rsrc_t rV, int bh, int64_t base, int u0, int e0,
                                           int deg, int lane, int len) {
     const int slot = lane >> 3, sub = lane & 7;
-    const int lane_off = sub * 8 * (int)sizeof(T);
+    const int lane_off = first_feature<T>(sub) * (int)sizeof(T);
     const int u = u0 + slot;
     const int tok0 = a.ia[e0 + slot * deg];  // first token of this group's span
     Row<T> k0 = gather_row<T>(rK, tok0, a.row_bytes, lane_off), v0 = gather_row<T>(rV, tok0, a.row_bytes, lane_off);
-    const Row<T> q = load_row(static_cast<const T*>(a.Q) + base + (int64_t)u * a.sn + sub * 8);
+    const Row<T> q = load_row(static_cast<const T*>(a.Q) + base + (int64_t)u * a.sn + first_feature<T>(sub));
     const float qscale = a.scale * kLog2e;
     const float shift =
-        sum8(dot8(q, load_row(static_cast<const T*>(a.rel) + (int64_t)a.ib[e0] * kD + sub * 8), 0.f)) * qscale;
+        sum8(dot8(q, load_row(static_cast<const T*>(a.rel) + (int64_t)a.ib[e0] * kD + first_feature<T>(sub)), 0.f)) * qscale;
     const uint32_t rowh = drop_row_hash(drop_bh_hash(a.drop_seed, bh), u);
     float m = kNegBig, l = 0.f, acc[8];
 #pragma unroll
@@ -178,7 +178,7 @@ __device__ __forceinline__ void fwd_span8(const AttnArgs& a, rsrc_t rK, rsrc_t r
     const float inv = l > 0.f ? 1.f / l : 0.f;   // l == 0: a span past the end of a shorter sequence
 #pragma unroll
     for (int x = 0; x < 8; ++x) acc[x] *= inv;
-    store8(static_cast<T*>(a.out) + base + (int64_t)u * a.sn + sub * 8, acc);
+    store8(static_cast<T*>(a.out) + base + (int64_t)u * a.sn + first_feature<T>(sub), acc);
     if (sub == 0) a.lse_w[(int64_t)bh * a.N + u] = l > 0.f ? (m + fast_log2(l)) * kLn2 : 0.f;
 }
 
@@ -255,8 +255,8 @@ __device__ __forceinline__ void bwd_q_segment(const AttnArgs& a, const T* rel_s,
                                               rsrc_t rIb, int bh, int64_t base, int u, int e0, int e1, int part,
                                               int lane, int len) {
     const int slot = lane >> 3, sub = lane & 7;
-    const int lane_off = sub * 8 * (int)sizeof(T);
-    const T* relg = static_cast<const T*>(a.rel) + sub * 8;
+    const int lane_off = first_feature<T>(sub) * (int)sizeof(T);
+    const T* relg = static_cast<const T*>(a.rel) + first_feature<T>(sub);
     const bool row_kept = node_kept(a, u, len);
     const uint32_t rowh = drop_row_hash(drop_bh_hash(a.drop_seed, bh), u);
 
@@ -272,8 +272,8 @@ __device__ __forceinline__ void bwd_q_segment(const AttnArgs& a, const T* rel_s,
     Row<T> k0 = gather_row<T>(rK, c0, a.row_bytes, lane_off), v0 = gather_row<T>(rV, c0, a.row_bytes, lane_off);
 
     float qs[8];
-    load8(static_cast<const T*>(a.Q) + base + (int64_t)u * a.sn + sub * 8, qs);
-    const Row<T> g = load_row(static_cast<const T*>(a.dout) + base + (int64_t)u * a.sn + sub * 8);
+    load8(static_cast<const T*>(a.Q) + base + (int64_t)u * a.sn + first_feature<T>(sub), qs);
+    const Row<T> g = load_row(static_cast<const T*>(a.dout) + base + (int64_t)u * a.sn + first_feature<T>(sub));
     const float qscale = a.scale * kLog2e;
 #pragma unroll
     for (int i = 0; i < 8; ++i) qs[i] *= qscale;
@@ -307,7 +307,7 @@ __device__ __forceinline__ void bwd_q_segment(const AttnArgs& a, const T* rel_s,
             float r[8];
             const int rid = inside ? r0 : 0;  // a lane past the end may hold an id of some other row
             if (REL_LDS)
-                load8(rel_s + rid * kD + sub * 8, r);
+                load8(rel_s + rid * kD + first_feature<T>(sub), r);
             else
                 load8(relg + (int64_t)rid * kD, r);
 #pragma unroll
@@ -340,7 +340,7 @@ __device__ __forceinline__ void bwd_q_segment(const AttnArgs& a, const T* rel_s,
         step(eb + 8, k1, v1, k0, v0);
     }
     dl = slots_sum(dl);
-    const int col = sub * 8 + slot_elem(lane);
+    const int col = feature_of<T>(sub, slot_elem(lane));
     if (part < 0) {
 #pragma unroll
         for (int i = 0; i < 8; ++i) A[i] -= dl * Bv[i];
@@ -359,13 +359,13 @@ template <typename T>
 __device__ __forceinline__ void bwd_q_span8(const AttnArgs& a, rsrc_t rK, rsrc_t rV, int bh, int64_t base, int u0,
                                             int e0, int deg, int lane, int len) {
     const int slot = lane >> 3, sub = lane & 7;
-    const int lane_off = sub * 8 * (int)sizeof(T);
+    const int lane_off = first_feature<T>(sub) * (int)sizeof(T);
     const int u = u0 + slot;
     const int tok0 = a.ia[e0 + slot * deg];
     Row<T> k0 = gather_row<T>(rK, tok0, a.row_bytes, lane_off), v0 = gather_row<T>(rV, tok0, a.row_bytes, lane_off);
     float qs[8];
-    load8(static_cast<const T*>(a.Q) + base + (int64_t)u * a.sn + sub * 8, qs);
-    const Row<T> g = load_row(static_cast<const T*>(a.dout) + base + (int64_t)u * a.sn + sub * 8);
+    load8(static_cast<const T*>(a.Q) + base + (int64_t)u * a.sn + first_feature<T>(sub), qs);
+    const Row<T> g = load_row(static_cast<const T*>(a.dout) + base + (int64_t)u * a.sn + first_feature<T>(sub));
     const float qscale = a.scale * kLog2e;
 #pragma unroll
     for (int i = 0; i < 8; ++i) qs[i] *= qscale;
@@ -374,7 +374,7 @@ __device__ __forceinline__ void bwd_q_span8(const AttnArgs& a, rsrc_t rK, rsrc_t
     float shift;
     {
         float r[8], d = 0.f;
-        load8(static_cast<const T*>(a.rel) + (int64_t)a.ib[e0] * kD + sub * 8, r);
+        load8(static_cast<const T*>(a.rel) + (int64_t)a.ib[e0] * kD + first_feature<T>(sub), r);
 #pragma unroll
         for (int i = 0; i < 8; ++i) d += qs[i] * r[i];
         shift = sum8(d);
@@ -407,8 +407,8 @@ __device__ __forceinline__ void bwd_q_span8(const AttnArgs& a, rsrc_t rK, rsrc_t
     }
 #pragma unroll
     for (int x = 0; x < 8; ++x) A[x] = a.scale * (A[x] - dl * Bv[x]);
-    store_grad4(a.dQ, base + (int64_t)u * a.sn + sub * 8, make_float4(A[0], A[1], A[2], A[3]), a.grad_bf16);
-    store_grad4(a.dQ, base + (int64_t)u * a.sn + sub * 8 + 4, make_float4(A[4], A[5], A[6], A[7]), a.grad_bf16);
+    store_grad4(a.dQ, base + (int64_t)u * a.sn + first_feature<T>(sub), make_float4(A[0], A[1], A[2], A[3]), a.grad_bf16);
+    store_grad4(a.dQ, base + (int64_t)u * a.sn + feature_of<T>(sub, 4), make_float4(A[4], A[5], A[6], A[7]), a.grad_bf16);
     if (sub == 0) a.stat[(int64_t)bh * a.N + u] = make_float2(tok0 < len ? lse2 : kLseGone, dl);
 }
 
@@ -480,8 +480,8 @@ __device__ __forceinline__ void bwd_kv_segment(const AttnArgs& a, const T* rel_s
                                                rsrc_t rIa, rsrc_t rIb, int bh, int64_t base, int v, int e0, int e1,
                                                int part, int lane, int len) {
     const int slot = lane >> 3, sub = lane & 7;
-    const int lane_off = sub * 8 * (int)sizeof(T);
-    const T* relg = static_cast<const T*>(a.rel) + sub * 8;
+    const int lane_off = first_feature<T>(sub) * (int)sizeof(T);
+    const T* relg = static_cast<const T*>(a.rel) + first_feature<T>(sub);
     const float qscale = a.scale * kLog2e;
 
     float dk[8], dv[8];
@@ -498,8 +498,8 @@ __device__ __forceinline__ void bwd_kv_segment(const AttnArgs& a, const T* rel_s
         int r0 = buf_i32(rIb, eo), r1 = buf_i32(rIb, eo + 32);
         Row<T> q0 = gather_row<T>(rQ, u0, a.row_bytes, lane_off), g0 = gather_row<T>(rG, u0, a.row_bytes, lane_off);
         float2 st0 = buf_f2(rS, u0 * 8);
-        const Row<T> kk = load_row(static_cast<const T*>(a.K) + base + (int64_t)v * a.sn + sub * 8);
-        const Row<T> vv = load_row(static_cast<const T*>(a.V) + base + (int64_t)v * a.sn + sub * 8);
+        const Row<T> kk = load_row(static_cast<const T*>(a.K) + base + (int64_t)v * a.sn + first_feature<T>(sub));
+        const Row<T> vv = load_row(static_cast<const T*>(a.V) + base + (int64_t)v * a.sn + first_feature<T>(sub));
 
         auto step = [&](int eb, const Row<T>& qc, const Row<T>& gc, const float2& stc, Row<T>& qn, Row<T>& gn,
                         float2& stn) {
@@ -512,7 +512,7 @@ __device__ __forceinline__ void bwd_kv_segment(const AttnArgs& a, const T* rel_s
 
             const bool valid = eb + slot < e1;
             float q[8], g[8];
-            float d = dot8(qc, REL_LDS ? load_row(rel_s + r0 * kD + sub * 8) : load_row(relg + (int64_t)r0 * kD), 0.f);
+            float d = dot8(qc, REL_LDS ? load_row(rel_s + r0 * kD + first_feature<T>(sub)) : load_row(relg + (int64_t)r0 * kD), 0.f);
             d = dot8(qc, kk, d);
             const float sc = sum8(d) * qscale;
             const float keep = a.drop_thr ? drop_scale(drop_row_hash(bhh, unow), drop_edge_x(unow < a.n_tokens, r0, v), a.drop_thr,
@@ -543,7 +543,7 @@ __device__ __forceinline__ void bwd_kv_segment(const AttnArgs& a, const T* rel_s
         }
     }
     const float tk = reduce_slots8(dk, lane), tv = reduce_slots8(dv, lane);
-    const int col = sub * 8 + slot_elem(lane);
+    const int col = feature_of<T>(sub, slot_elem(lane));
     if (part < 0) {
         store_grad(a.dK, base + (int64_t)v * a.sn + col, tk * a.scale, a.grad_bf16);
         store_grad(a.dV, base + (int64_t)v * a.sn + col, tv, a.grad_bf16);
@@ -620,16 +620,16 @@ __global__ void __launch_bounds__(kThreads) rel_grad_kernel(const AttnArgs a) {
         {   // Q rows of the block: 8 lanes per row
             const T* Qb = static_cast<const T*>(a.Q) + base;
             for (int i = threadIdx.x; i < R * 8; i += blockDim.x) {
-                const int r = i >> 3, c = (i & 7) * 8;
+                const int r = i >> 3, sub = i & 7;
                 float x[8];
                 if (row0 + r < a.n_tokens) {
-                    load8(Qb + (int64_t)(row0 + r) * a.sn + c, x);
+                    load8(Qb + (int64_t)(row0 + r) * a.sn + first_feature<T>(sub), x);
                 } else {
 #pragma unroll
                     for (int j = 0; j < 8; ++j) x[j] = 0.f;
                 }
 #pragma unroll
-                for (int j = 0; j < 8; ++j) q_s[r * kD + c + j] = x[j];
+                for (int j = 0; j < 8; ++j) q_s[r * kD + feature_of<T>(sub, j)] = x[j];
             }
         }
         __syncthreads();
