@@ -194,7 +194,8 @@ struct TilePlan {
 };
 // dense: the plan of bwd_q_tile_kernel<.., DENSE> -- ids padded to 32, two more [16][bias_stride] fp32
 // tables per wavefront, and the relative-position table must be in LDS
-TilePlan plan_tiles(const bpt_graph* g, const DeviceLimits& lim, bool dense = false) {
+// shorter: the call has sequences shorter than n (t.ok does not depend on it)
+TilePlan plan_tiles(const bpt_graph* g, const DeviceLimits& lim, bool dense = false, bool shorter = false) {
     TilePlan t;
     if (g->tiles.num_tiles == 0) return t;
     t.cid_pad = dense ? (g->tiles.num_cids + 31) & ~31 : (g->tiles.num_cids + 15) & ~15;
@@ -210,8 +211,13 @@ TilePlan plan_tiles(const bpt_graph* g, const DeviceLimits& lim, bool dense = fa
         t.ok = t.lds <= room && 64 * (t.cid_pad + 8) <= 64 * kRowStride * (int)sizeof(bf16_t);
         return t;
     }
-    // The whole table while two workgroups of it share a compute unit (up to about 100 ids), else the ring.
-    if (2 * (t.lds + prefix) > lim.lds_cu && g->tiles.ring_ok) {
+    // The whole table while two workgroups of it share a compute unit (up to about 100 ids), else the ring -- but where
+    // sequences end before n and tokens look to the right, the nodes past the end are masked as the table is formed, level
+    // by level: once per tile in the whole table, with every pair in the ring, which costs more than the second workgroup
+    // brings (packed, H = 8, bidirectional, whole against ring, forward and query-side kernels together: n = 4096, k = 7, 3
+    // sequences 87 / 126 us, 16 sequences 371 / 463 us; k = 12, 3 sequences 108 / 190 us; causal, k = 16, 80 / 72 us).
+    const bool mask_right = shorter && !g->causal && t.lds <= room;
+    if (2 * (t.lds + prefix) > lim.lds_cu && g->tiles.ring_ok && !mask_right) {
         t.ring = true;
         t.bias_stride = kRingStride;
         t.lds = (size_t)kTileWaves * 16 * kRingStride * sizeof(float) + rows;
@@ -241,7 +247,7 @@ int dense_grid(const DeviceLimits& lim) { return std::max(8, lim.cus / 8 * 8); }
 
 // bf16 backward, query side of the token rows on dense tiles
 int run_bwd_q_tiles(const bpt_graph* g, const AttnArgs& a, const DeviceLimits& lim, bool dense, hipStream_t st) {
-    const TilePlan tp = plan_tiles(g, lim, dense);
+    const TilePlan tp = plan_tiles(g, lim, dense, a.seq_len != nullptr);
     TileArgs t = {};
     fill_tile_args(t, g, a, tp);
     if (dense) {   // no (w, p) pairs: the kernel leaves one copy of d_rel per workgroup
@@ -429,7 +435,7 @@ int run_fwd(const bpt_graph* g, AttnArgs& a, hipStream_t st) {
     int rc = device_limits(g, &lim);
     if (rc) return rc;
     if (sizeof(T) == 2) {
-        const TilePlan tp = plan_tiles(g, lim);
+        const TilePlan tp = plan_tiles(g, lim, false, a.seq_len != nullptr);
         if (tp.ok) {
             if ((rc = run_fwd_tiles(g, a, lim, tp, st))) return rc;
             if (span_tiles_ok(g)) return run_span_tiles(g, a, true, st);
