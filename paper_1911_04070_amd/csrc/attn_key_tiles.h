@@ -607,7 +607,11 @@ __global__ void __launch_bounds__(kTileThreads, 2) bwd_kv_chain_kernel(const Key
                         const float bv1 = __shfl(b4[ci][1][r], src);
                         bv = bid[r] >= 16 ? bv1 : bv;
                     }
-                    const float p = masked_exp2(bid[r] >= 0 && key_kept, (s4[ci][r] + bv) * qscale - st[r].x);
+                    // with dropout the branch is the better form: this kernel, n = 512, k = 4, 32 x 8 heads, 111 -> 108 us
+                    // (without dropout, 8 sequences, one head: 33.2 with the branch, 31.8 us without)
+                    const bool on = bid[r] >= 0 && key_kept;
+                    const float arg = (s4[ci][r] + bv) * qscale - st[r].x;
+                    const float p = DROP ? (on ? fast_exp2(arg) : 0.f) : masked_exp2(on, arg);
                     if (DROP) {
                         const uint32_t x2 = bid[r] < a.W ? (uint32_t)(level * a.W + bid[r]) : 0x80000000u + (uint32_t)(node0 + j);
                         const float keep = drop_scale(rowh_s[16 * ci + 4 * g + r], x2, a.drop_thr, a.drop_inv_keep);
