@@ -126,7 +126,8 @@ __device__ __forceinline__ s16x4_t lds_tr4(const bf16_t* base, int stride, int r
 // p_0 = t + 1 and p_{l+1} = ceil((p_l + k) / 2) (Algorithm 1: k nodes, one more when the run would
 // not end on a parent boundary), and level l keeps ceil(len / 2^l) nodes.  Lane (g, j) works on
 // token j of the tile; the four lane groups share the ids.
-// c0, c1: the ids to look at (the others are not in the table yet, or no longer); the table holds id c at c & wrap.
+// c0, c1: the ids to look at (the others are not in the table yet, or no longer); the table holds id c at c & wrap, so
+// with a wrap there are at most as many of them as the table holds.
 constexpr float kMaskBias = -1.0e30f;
 __device__ __forceinline__ void mask_bias(const TileArgs& a, float* bias_s, int t0, int len, int g, int j, int c0, int c1, int wrap) {
     const int t = t0 + j;
@@ -376,7 +377,10 @@ __global__ void __launch_bounds__(kTileThreads, 2) fwd_tile_kernel(const TileArg
     int node_n[2][2];
     uint2 mp_n[2];
     auto load_idx = [&](TileCursor& c) {
-        if (RING) c.b1 = uniform_i32(a.pair_blocks, (c.cp0 >> 1) + c.pair);
+        if (RING) {
+            c.b1 = uniform_i32(a.pair_blocks, (c.cp0 >> 1) + c.pair);
+            c.b0 = max(c.b0, c.b1 - kRingBlocks);   // (a pair can jump over more ids than the ring holds: none of them has an edge)
+        }
 #pragma unroll
         for (int ci = 0; ci < 2; ++ci) {
             const int at = (c.cp0 + 2 * c.pair + ci) * 16;
@@ -733,7 +737,10 @@ __global__ void __launch_bounds__(kTileThreads, DENSE ? 1 : 2) bwd_q_tile_kernel
     int node_n[2][2];
     uint2 mp_n[2];
     auto load_idx = [&](TileCursor& c) {
-        if (RING) c.b1 = uniform_i32(a.pair_blocks, (c.cp0 >> 1) + c.pair);
+        if (RING) {
+            c.b1 = uniform_i32(a.pair_blocks, (c.cp0 >> 1) + c.pair);
+            c.b0 = max(c.b0, c.b1 - kRingBlocks);   // (a pair can jump over more ids than the ring holds: none of them has an edge)
+        }
 #pragma unroll
         for (int ci = 0; ci < 2; ++ci) {
             const int at = (c.cp0 + 2 * c.pair + ci) * 16;

@@ -199,6 +199,40 @@ def test_bias_table_whole_and_as_a_ring(n, k, causal, lengths):
     run_case(w, x, scaled=True)
 
 
+# bidirectional sequences that end before n: the nodes past their end are masked as the blocks of ids enter the ring.  n =
+# 256, k = 240: a last tile's second pair of chunks goes from the left side of level 0 to the left side of level 1, over
+# more ids than the ring holds, all of them right-side ids past the end; masks of ids that the ring no longer holds would fall
+# on the level-1 nodes.  Those (every span node) have values eight times as large here, so that a lost edge shows: the 7 of 250
+# edges that token 250 then loses change `out` by sqrt(7) * 8 / 250 = 0.08 and lse by 0.03.
+@pytest.mark.parametrize("n,k,lengths", [(256, 240, [255, 250]), (256, 300, [255, 241])])
+def test_ring_masks_past_the_end_of_a_sequence(n, k, lengths):
+    say("ring masks", n, k, lengths)
+    w = Workload("ring_masks", 13, n, k, False, len(lengths), 2, 64, "bf16", True)
+    x = make_inputs(w)
+    x["V"][:, :, n:] *= np.float32(8)      # exact in bf16
+    g = bpt.bpt_build_graph(n, k, False)
+    Q, K, V, dO, R = (to_dev(x[k_], "bf16") for k_ in ("Q", "K", "V", "dO", "Rel"))
+    lens_d = torch.tensor(lengths, dtype=torch.int32, device="cuda")
+    bpt.bpt_profile_enable(True)
+    out_d, lse_d = bpt.bpt_attn_fwd(g, Q, K, V, R, scale=w.scale, seq_len=lens_d)
+    grads = bpt.bpt_attn_bwd(g, Q, K, V, R, lse_d, dO, scale=w.scale, seq_len=lens_d)
+    torch.cuda.synchronize()
+    ran = set(bpt.bpt_profile_report())
+    bpt.bpt_profile_enable(False)
+    assert {"fwd_tile_kernel", "bwd_q_tile_kernel"} <= ran, ran
+    o, l, _ = oracle.attn_fwd_lengths(n, k, False, lengths, x["Q"], x["K"], x["V"], x["Rel"], w.scale)
+    refs = oracle.attn_bwd_lengths(n, k, False, lengths, x["Q"], x["K"], x["V"], x["Rel"], x["dO"], w.scale)
+    res = {}
+    for name, got_t, ref in zip(("out", "lse", "dQ", "dK", "dV", "d_rel"), (out_d, lse_d) + tuple(grads), (o, l) + refs):
+        got = host(got_t)
+        assert np.isfinite(got).all(), name
+        res[name] = (float(np.abs(got - ref).max()), float(np.abs(ref).max()))
+    say("   max-abs errors, largest entries", res)
+    for name, (err, most) in res.items():
+        assert err <= 2e-2 * max(1.0, most / 4.0), (name, err, most)
+    g.destroy()
+
+
 @pytest.mark.parametrize("name", FULL)
 def test_full_size_configuration(name):
     # configurations 2-5 at their full sizes, every output element against the oracle
