@@ -42,7 +42,9 @@ struct TileArgs {
     float scale;
     const int32_t *chunk_ptr, *cols, *cid_to_id;
     const int16_t* map;
-    const int32_t* pair_blocks;   // [chunks / 2] blocks of 16 compact ids a tile has met up to and with the pair
+    // Bias::kRing, kMemory: [chunks / 2] blocks of 16 compact ids a tile has met up to and with the pair, or null: all of
+    // them with the first
+    const int32_t* pair_blocks;
     int32_t num_tiles, num_chunks, num_cids, cid_pad, bias_stride;
     int32_t row_bytes;
     uint32_t slab_bytes;
@@ -126,21 +128,28 @@ __device__ __forceinline__ s16x4_t lds_tr4(const bf16_t* base, int stride, int r
 // p_0 = t + 1 and p_{l+1} = ceil((p_l + k) / 2) (Algorithm 1: k nodes, one more when the run would
 // not end on a parent boundary), and level l keeps ceil(len / 2^l) nodes.  Lane (g, j) works on
 // token j of the tile; the four lane groups share the ids.
-// c0, c1: the ids to look at (the others are not in the table yet, or no longer); the table holds id c at c & wrap, so
-// with a wrap there are at most as many of them as the table holds.
+// c0, c1: the ids to look at (the others are not in the table yet, or no longer): in a ring at most as many as it holds.
 constexpr float kMaskBias = -1.0e30f;
-__device__ __forceinline__ void mask_bias(const TileArgs& a, float* bias_s, int t0, int len, int g, int j, int c0, int c1, int wrap) {
+enum class Bias { kStaged, kRing, kMemory };   // (see ring_form)
+constexpr int kRingIds = 16 * kRingBlocks;
+constexpr int kRingStride = kRingIds + 4;   // = 4 mod 32: the 16 token rows hit different banks
+template <Bias BIAS>
+__device__ __forceinline__ int bias_slot(int cid) {   // where a token's row of the table holds an id
+    return BIAS == Bias::kRing ? cid & (kRingIds - 1) : cid;
+}
+template <Bias BIAS>
+__device__ __forceinline__ void mask_bias(const TileArgs& a, float* bias_s, int t0, int len, int g, int j, int c0, int c1) {
     const int t = t0 + j;
     float* row = bias_s + j * a.bias_stride;
     if (t >= len) {
-        for (int c = c0 + 4 * g; c < c1; c += 16) *reinterpret_cast<f32x4_t*>(row + (c & wrap)) = f32x4_t{kMaskBias, kMaskBias, kMaskBias, kMaskBias};
+        for (int c = c0 + 4 * g; c < c1; c += 16) *reinterpret_cast<f32x4_t*>(row + bias_slot<BIAS>(c)) = f32x4_t{kMaskBias, kMaskBias, kMaskBias, kMaskBias};
     } else if (!a.causal) {
         int p = t + 1;
         for (int l = 0; l < a.ctx_levels; ++l) {
             const int cnt = (len + (1 << l) - 1) >> l;            // nodes the level keeps
             for (int o = max(cnt - p + 1, 1) + g; o <= a.k + 1; o += 4) {
                 const int cid = a.id_to_cid[l * a.W + a.k + 1 + o];
-                if (cid >= c0 && cid < c1) row[cid & wrap] = kMaskBias;
+                if (BIAS == Bias::kStaged ? cid >= 0 : cid >= c0 && cid < c1) row[bias_slot<BIAS>(cid)] = kMaskBias;
             }
             p = (p + a.k + 1) >> 1;
         }
@@ -192,7 +201,7 @@ __device__ __forceinline__ void nth_tile(const int* pref, int B, int H, int num_
 // Position of a wavefront in its sequence of (token tile, pair of chunks); wave-uniform.
 struct TileCursor {
     int t, pair, npairs, cp0, bh, tile;
-    int b0, b1;   // RING kernels: blocks of ids that enter the bias table with this pair
+    int b0, b1;   // Bias::kRing, kMemory: blocks of ids that enter the bias table with this pair
     int dvec;   // packed batch: this lane's delta of the sequence the tile belongs to (0 otherwise)
     bool valid;
 };
@@ -211,17 +220,18 @@ __device__ __forceinline__ void cursor_uniform(TileCursor& c) {
     c.valid = __builtin_amdgcn_readfirstlane((int)c.valid) != 0;
 }
 
-// The bias of a tile, [token][compact id], in one of two forms.  Without RING the whole table is formed at the start of
-// the tile, out of the relative-position table staged in LDS.  RING: a tile's columns run through its ids in ascending
-// order (level by level, from the far left to the far right of each; a pair of chunks spans at most about 50 ids), so
-// the table is a ring of kRingIds ids per token, and every pair forms the blocks of 16 ids that are new with it
-// (TileArgs.pair_blocks) out of rows of the relative-position table that were requested from memory with the pair's K and
-// V rows.  The same products in all, but the LDS of a wavefront no longer grows with the ids (k = 64: 8 instead of 31
-// KB), which is what lets a second workgroup onto every compute unit.  k = 64, n = 8192, causal, 32 (batch, head)s: this
-// kernel 356 -> 220 us, the query side 437 -> 374 us (the 1.2 GB of (w, p) it writes bound it); k = 16, n = 4096, 64 of
-// them, dropout: 200 -> 183 and 277 -> 262 us.
-constexpr int kRingIds = 16 * kRingBlocks;
-constexpr int kRingStride = kRingIds + 4;   // = 4 mod 32: the 16 token rows hit different banks
+// The bias of a tile, [token][compact id], in one of three forms.
+//   kStaged: the whole table is formed at the start of the tile, out of the relative-position table staged in LDS.
+//   kRing: a tile's columns run through its ids in ascending order (level by level, from the far left to the far right of
+//     each), so the table is a ring of kRingIds ids per token, and every pair of chunks forms the blocks of 16 ids that are
+//     new with it (TileArgs.pair_blocks) out of rows of the relative-position table that were requested from memory with
+//     the pair's K and V rows.  A pair whose columns end on one level and begin on the next spans the ids between them,
+//     also those of a side that the tile does not use (93 ids at n = 8192, k = 64, causal); graphs with pairs of more than
+//     kRingBlocks blocks (TokenTiles.ring_ok) do not take this form.  The LDS of a wavefront does not grow with the ids (k =
+//     64: 8 instead of 31 KB), which lets a second workgroup onto every compute unit.  k = 64, n = 8192, causal, 32 (batch,
+//     head)s: this kernel 356 -> 220 us, the query side 437 -> 374 us (the 1.2 GB of (w, p) it writes bound it); k = 16, n =
+//     4096, 64 of them, dropout: 200 -> 183 and 277 -> 262 us.
+//   kMemory: the whole table, formed as in the ring, or all of it with a tile's first pair (pair_blocks null).
 constexpr int kRingAhead = 3;               // blocks of a pair requested ahead (the first pair of a tile may need more)
 struct RelAhead {
     bf16x8_t r[kRingAhead][2];
@@ -239,13 +249,14 @@ __device__ __forceinline__ void ring_request(const TileArgs& a, const int32_t* r
             x.r[i][1] = *reinterpret_cast<const bf16x8_t*>(rr + 8);
         }
 }
+template <Bias BIAS>
 __device__ __forceinline__ void ring_form(const TileArgs& a, const int32_t* relid_s, float* bias_s, const TileCursor& c,
                                           const bf16x8_t& qb0, const bf16x8_t& qb1, int g, int j, const RelAhead& x) {
     auto block = [&](int b, const bf16x8_t& r0, const bf16x8_t& r1) {
         f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
         acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(r0, qb0, acc, 0, 0, 0);
         acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(r1, qb1, acc, 0, 0, 0);
-        *reinterpret_cast<f32x4_t*>(bias_s + j * kRingStride + ((16 * b) & (kRingIds - 1)) + 4 * g) = acc;
+        *reinterpret_cast<f32x4_t*>(bias_s + j * (BIAS == Bias::kRing ? kRingStride : a.bias_stride) + bias_slot<BIAS>(16 * b) + 4 * g) = acc;
     };
 #pragma unroll
     for (int i = 0; i < kRingAhead; ++i)
@@ -256,32 +267,35 @@ __device__ __forceinline__ void ring_form(const TileArgs& a, const int32_t* reli
     }
     if (a.seq_len && c.b0 < c.b1) {   // uniform
         wave_lds_sync();
-        mask_bias(a, bias_s, c.tile * 16, seq_length_u(a.seq_len, c.bh / a.H, a.n), g, j, 16 * c.b0, 16 * c.b1, kRingIds - 1);
+        // (a pair can jump over more ids than the ring holds; no edge carries those, and their entries are others' by now)
+        const int b0 = BIAS == Bias::kRing ? max(c.b0, c.b1 - kRingBlocks) : c.b0;
+        mask_bias<BIAS>(a, bias_s, c.tile * 16, seq_length_u(a.seq_len, c.bh / a.H, a.n), g, j, 16 * b0, 16 * c.b1);
     }
 }
 
 // PACKED: the rows of the caller's tensors are those of a packed batch (TileArgs.delta; see attn_device.h)
-template <bool RING, bool DROP, bool PACKED = false>
+template <Bias BIAS, bool DROP, bool PACKED = false>
 __global__ void __launch_bounds__(kTileThreads, 2) fwd_tile_kernel(const TileArgs a) {
+    constexpr bool kFromMemory = BIAS != Bias::kStaged;
     extern __shared__ __align__(16) unsigned char smem[];
     bf16_t* rel_s = reinterpret_cast<bf16_t*>(smem);                                   // [cid_pad][kRelStride]
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int g = lane >> 4, j = lane & 15;
     const int r8 = lane >> 3, piece = lane & 7;   // coalesced row fetches: row of the instruction, 16-byte piece
-    const size_t rel_bytes = !RING ? (size_t)a.cid_pad * kRelStride * sizeof(bf16_t) : 0;
+    const size_t rel_bytes = !kFromMemory ? (size_t)a.cid_pad * kRelStride * sizeof(bf16_t) : 0;
     float* bias_s = reinterpret_cast<float*>(smem + rel_bytes) +
                     (size_t)wave * 16 * a.bias_stride;                                  // [16 tokens][bias_stride]
     bf16_t* k_s = reinterpret_cast<bf16_t*>(smem + rel_bytes + (size_t)kTileWaves * 16 * a.bias_stride * sizeof(float)) +
                   (size_t)wave * 64 * kRowStride;                                       // [32 columns][kRowStride]: K rows
     bf16_t* v_s = k_s + 32 * kRowStride;                                                // the same for V rows
-    // DROP, RING: relative-position id of every compact id, what the dropout mask of an edge is drawn from
+    // DROP, kFromMemory: relative-position id of every compact id, what the dropout mask of an edge is drawn from
     int32_t* relid_s = reinterpret_cast<int32_t*>(smem + rel_bytes + (size_t)kTileWaves * 16 * a.bias_stride * sizeof(float) +
                                                   (size_t)kTileWaves * 64 * kRowStride * sizeof(bf16_t));   // [cid_pad]
-    if (DROP || RING)
+    if (DROP || kFromMemory)
         for (int i = threadIdx.x; i < a.cid_pad; i += blockDim.x) relid_s[i] = i < a.num_cids ? a.cid_to_id[i] : 0;
     // compact relative-position table, zero rows as padding
-    if (!RING) {
+    if (!kFromMemory) {
         for (int i = threadIdx.x; i < a.cid_pad * 8; i += blockDim.x) {
             const int cid = i >> 3, c8 = (i & 7) * 8;
             uint4 w = make_uint4(0u, 0u, 0u, 0u);
@@ -291,7 +305,7 @@ __global__ void __launch_bounds__(kTileThreads, 2) fwd_tile_kernel(const TileArg
     }
     __syncthreads();
 
-    const int bias_stride = RING ? kRingStride : a.bias_stride;
+    const int bias_stride = BIAS == Bias::kRing ? kRingStride : a.bias_stride;
     const float qscale = a.scale * kLog2e;
     const rsrc_t rC = make_rsrc(a.cols, (uint32_t)a.num_chunks * 64u);   // [chunks][16] int32
     const rsrc_t rM = make_rsrc(a.map, (uint32_t)a.num_chunks * 512u);   // [chunks][16][16] int16
@@ -377,10 +391,7 @@ __global__ void __launch_bounds__(kTileThreads, 2) fwd_tile_kernel(const TileArg
     int node_n[2][2];
     uint2 mp_n[2];
     auto load_idx = [&](TileCursor& c) {
-        if (RING) {
-            c.b1 = uniform_i32(a.pair_blocks, (c.cp0 >> 1) + c.pair);
-            c.b0 = max(c.b0, c.b1 - kRingBlocks);   // (a pair can jump over more ids than the ring holds: none of them has an edge)
-        }
+        if (kFromMemory) c.b1 = BIAS == Bias::kRing || a.pair_blocks ? uniform_i32(a.pair_blocks, (c.cp0 >> 1) + c.pair) : a.cid_pad >> 4;
 #pragma unroll
         for (int ci = 0; ci < 2; ++ci) {
             const int at = (c.cp0 + 2 * c.pair + ci) * 16;
@@ -392,7 +403,7 @@ __global__ void __launch_bounds__(kTileThreads, 2) fwd_tile_kernel(const TileArg
     };
     Row<bf16_t> kr[2][2], vr[2][2];   // [chunk][half of its rows]: this lane's 16-byte piece
     bf16x8_t qn0, qn1;                // Q^T operand of the tile whose first pair is in flight
-    RelAhead rel_n;                   // RING: the rows of the table that the pair in flight brings with it
+    RelAhead rel_n;                   // kFromMemory: the rows of the table that the pair in flight brings with it
     auto request_rows = [&](const TileCursor& c) {
         const int64_t base = (int64_t)(c.bh / a.H) * a.sb + (int64_t)(c.bh % a.H) * a.sh;
         const rsrc_t rK = make_rsrc(a.K + base, a.slab_bytes), rV = make_rsrc(a.V + base, a.slab_bytes);
@@ -413,7 +424,7 @@ __global__ void __launch_bounds__(kTileThreads, 2) fwd_tile_kernel(const TileArg
             qn0 = *reinterpret_cast<const bf16x8_t*>(a.Q + at);
             qn1 = *reinterpret_cast<const bf16x8_t*>(a.Q + at + 8);
         }
-        if (RING) ring_request(a, relid_s, c, g, j, rel_n);
+        if (kFromMemory) ring_request(a, relid_s, c, g, j, rel_n);
     };
 
     TileCursor cc, cr, ci;
@@ -451,7 +462,7 @@ __global__ void __launch_bounds__(kTileThreads, 2) fwd_tile_kernel(const TileArg
 #pragma unroll
             for (int f = 0; f < 4; ++f) o[f] = f32x4_t{0.f, 0.f, 0.f, 0.f};
             // bias^T = Rel x Q^T, kept in LDS as [token][compact id]
-            for (int c = 0; !RING && c < a.cid_pad; c += 16) {
+            for (int c = 0; !kFromMemory && c < a.cid_pad; c += 16) {
                 const bf16_t* rrow = rel_s + (c + j) * kRelStride + 16 * g;
                 const bf16x8_t r0 = *reinterpret_cast<const bf16x8_t*>(rrow), r1 = *reinterpret_cast<const bf16x8_t*>(rrow + 8);
                 f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
@@ -459,12 +470,12 @@ __global__ void __launch_bounds__(kTileThreads, 2) fwd_tile_kernel(const TileArg
                 acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(r1, qb1, acc, 0, 0, 0);
                 *reinterpret_cast<f32x4_t*>(bias_s + j * a.bias_stride + c + 4 * g) = acc;
             }
-            if (!RING && a.seq_len) {   // uniform
+            if (!kFromMemory && a.seq_len) {   // uniform
                 wave_lds_sync();
-                mask_bias(a, bias_s, cc.tile * 16, seq_length_u(a.seq_len, cc.bh / a.H, a.n), g, j, 0, a.cid_pad, ~0);
+                mask_bias<BIAS>(a, bias_s, cc.tile * 16, seq_length_u(a.seq_len, cc.bh / a.H, a.n), g, j, 0, a.cid_pad);
             }
         }
-        if (RING) ring_form(a, relid_s, bias_s, cc, qb0, qb1, g, j, rel_n);
+        if (kFromMemory) ring_form<BIAS>(a, relid_s, bias_s, cc, qb0, qb1, g, j, rel_n);
         wave_lds_sync();  // the previous pair's reads of k_s, v_s (and the previous tile's of bias_s) are done
 #pragma unroll
         for (int ci2 = 0; ci2 < 2; ++ci2)
@@ -495,7 +506,7 @@ __global__ void __launch_bounds__(kTileThreads, 2) fwd_tile_kernel(const TileArg
             cid[c][2] = (int)(short)(mpc[c].y & 0xFFFFu);
             cid[c][3] = (int)(short)(mpc[c].y >> 16);
 #pragma unroll
-            for (int r = 0; r < 4; ++r) bv[c][r] = bias_s[j * bias_stride + (RING ? cid[c][r] & (kRingIds - 1) : max(cid[c][r], 0))];
+            for (int r = 0; r < 4; ++r) bv[c][r] = bias_s[j * bias_stride + (BIAS == Bias::kRing ? bias_slot<BIAS>(cid[c][r]) : max(cid[c][r], 0))];
         }
         f32x4_t s4[2];
 #pragma unroll
@@ -602,8 +613,8 @@ __global__ void __launch_bounds__(kTileThreads, 2) fwd_tile_kernel(const TileArg
 //   dQ_K = scale * (W K_U - delta * P K_U)       (the key part of dQ; lse is known, so
 // no online softmax and no second pass).  Without DENSE, (w, p) of every tile slot goes to `wp` in
 // tile order for rel_grad_tile_kernel, which also adds the relative-position part of dQ.
-// RING: the bias table as in fwd_tile_kernel.
-// DENSE (needs the whole table, not RING, and cid_pad a multiple of 32): a tile's w = p dP and p are not stored per slot
+// BIAS: the bias table as in fwd_tile_kernel.
+// DENSE (needs Bias::kStaged, and cid_pad a multiple of 32): a tile's w = p dP and p are not stored per slot
 // for rel_grad_tile_kernel but scattered into two LDS tables [token][compact id] (the ids of a token
 // row are distinct).  When the tile is complete and delta is known, dS = w - delta p is there as a
 // dense 16 x cid_pad matrix (kept as bf16 hi + lo in the row buffers): the relative-position part of
@@ -612,16 +623,17 @@ __global__ void __launch_bounds__(kTileThreads, 2) fwd_tile_kernel(const TileArg
 // transposing reads, into accumulators the wavefront keeps over all its tiles (at most kDenseChunks
 // chunks of 16 ids).  Nothing per slot or per tile leaves for a d_rel kernel; every workgroup writes
 // one copy of d_rel at the end, and drel_reduce_kernel adds the copies in a fixed order.
-template <bool RING, bool DROP, bool DENSE = false, bool PACKED = false>
+template <Bias BIAS, bool DROP, bool DENSE = false, bool PACKED = false>
 __global__ void __launch_bounds__(kTileThreads, DENSE ? 1 : 2) bwd_q_tile_kernel(const TileArgs a) {
-    static_assert(!DENSE || !RING, "the dense variant multiplies by the staged table");
+    constexpr bool kFromMemory = BIAS != Bias::kStaged;
+    static_assert(!DENSE || !kFromMemory, "the dense variant multiplies by the staged table");
     extern __shared__ __align__(16) unsigned char smem[];
     bf16_t* rel_s = reinterpret_cast<bf16_t*>(smem);
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int g = lane >> 4, j = lane & 15;
     const int r8 = lane >> 3, piece = lane & 7;   // coalesced row fetches: row of the instruction, 16-byte piece
-    const size_t rel_bytes = !RING ? (size_t)a.cid_pad * kRelStride * sizeof(bf16_t) : 0;
+    const size_t rel_bytes = !kFromMemory ? (size_t)a.cid_pad * kRelStride * sizeof(bf16_t) : 0;
     float* bias_s = reinterpret_cast<float*>(smem + rel_bytes) +
                     (size_t)wave * 16 * a.bias_stride;
     bf16_t* k_s = reinterpret_cast<bf16_t*>(smem + rel_bytes + (size_t)kTileWaves * 16 * a.bias_stride * sizeof(float)) +
@@ -634,9 +646,9 @@ __global__ void __launch_bounds__(kTileThreads, DENSE ? 1 : 2) bwd_q_tile_kernel
     float* w_s = reinterpret_cast<float*>(relid_s + a.cid_pad) + (size_t)wave * 32 * a.bias_stride;
     float2* wp_s = reinterpret_cast<float2*>(w_s);
     const int wp_stride = a.cid_pad + 2;
-    if (DROP || RING)
+    if (DROP || kFromMemory)
         for (int i = threadIdx.x; i < a.cid_pad; i += blockDim.x) relid_s[i] = i < a.num_cids ? a.cid_to_id[i] : 0;
-    if (!RING) {
+    if (!kFromMemory) {
         for (int i = threadIdx.x; i < a.cid_pad * 8; i += blockDim.x) {
             const int cid = i >> 3, c8 = (i & 7) * 8;
             uint4 w = make_uint4(0u, 0u, 0u, 0u);
@@ -646,7 +658,7 @@ __global__ void __launch_bounds__(kTileThreads, DENSE ? 1 : 2) bwd_q_tile_kernel
     }
     __syncthreads();
 
-    const int bias_stride = RING ? kRingStride : a.bias_stride;
+    const int bias_stride = BIAS == Bias::kRing ? kRingStride : a.bias_stride;
     const float qscale = a.scale * kLog2e;
     const rsrc_t rC = make_rsrc(a.cols, (uint32_t)a.num_chunks * 64u);
     const rsrc_t rM = make_rsrc(a.map, (uint32_t)a.num_chunks * 512u);
@@ -737,10 +749,7 @@ __global__ void __launch_bounds__(kTileThreads, DENSE ? 1 : 2) bwd_q_tile_kernel
     int node_n[2][2];
     uint2 mp_n[2];
     auto load_idx = [&](TileCursor& c) {
-        if (RING) {
-            c.b1 = uniform_i32(a.pair_blocks, (c.cp0 >> 1) + c.pair);
-            c.b0 = max(c.b0, c.b1 - kRingBlocks);   // (a pair can jump over more ids than the ring holds: none of them has an edge)
-        }
+        if (kFromMemory) c.b1 = BIAS == Bias::kRing || a.pair_blocks ? uniform_i32(a.pair_blocks, (c.cp0 >> 1) + c.pair) : a.cid_pad >> 4;
 #pragma unroll
         for (int ci = 0; ci < 2; ++ci) {
             const int at = (c.cp0 + 2 * c.pair + ci) * 16;
@@ -753,7 +762,7 @@ __global__ void __launch_bounds__(kTileThreads, DENSE ? 1 : 2) bwd_q_tile_kernel
     Row<bf16_t> kr[2][2], vr[2][2];   // [chunk][half of its rows]: this lane's 16-byte piece
     bf16x8_t qn0, qn1, gn0, gn1;      // operands of the tile whose first pair is in flight
     float lse_n = 0.f;
-    RelAhead rel_n;                   // RING: the rows of the table that the pair in flight brings with it
+    RelAhead rel_n;                   // kFromMemory: the rows of the table that the pair in flight brings with it
     auto request_rows = [&](const TileCursor& c) {
         const int64_t base = (int64_t)(c.bh / a.H) * a.sb + (int64_t)(c.bh % a.H) * a.sh;
         const rsrc_t rK = make_rsrc(a.K + base, a.slab_bytes), rV = make_rsrc(a.V + base, a.slab_bytes);
@@ -777,7 +786,7 @@ __global__ void __launch_bounds__(kTileThreads, DENSE ? 1 : 2) bwd_q_tile_kernel
             gn1 = load_once16<bf16x8_t>(a.dout + at + 8);
             lse_n = a.lse_r[(PACKED ? (int64_t)(c.bh / a.H) * a.lse_sb + (int64_t)(c.bh % a.H) * a.lse_sh : (int64_t)c.bh * a.N) + tq];
         }
-        if (RING) ring_request(a, relid_s, c, g, j, rel_n);
+        if (kFromMemory) ring_request(a, relid_s, c, g, j, rel_n);
     };
 
     // DENSE: this wavefront's d_rel sums over its tiles, [id chunk][feature chunk] in the C layout (id 4g + r
@@ -856,7 +865,7 @@ __global__ void __launch_bounds__(kTileThreads, DENSE ? 1 : 2) bwd_q_tile_kernel
 #pragma unroll
             for (int f = 0; f < 4; ++f) ow[f] = op[f] = f32x4_t{0.f, 0.f, 0.f, 0.f};
             // bias^T = Rel x Q^T, kept in LDS as [token][compact id]
-            for (int c = 0; !RING && c < a.cid_pad; c += 16) {
+            for (int c = 0; !kFromMemory && c < a.cid_pad; c += 16) {
                 const bf16_t* rrow = rel_s + (c + j) * kRelStride + 16 * g;
                 const bf16x8_t r0 = *reinterpret_cast<const bf16x8_t*>(rrow), r1 = *reinterpret_cast<const bf16x8_t*>(rrow + 8);
                 f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
@@ -864,9 +873,9 @@ __global__ void __launch_bounds__(kTileThreads, DENSE ? 1 : 2) bwd_q_tile_kernel
                 acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(r1, qb1, acc, 0, 0, 0);
                 *reinterpret_cast<f32x4_t*>(bias_s + j * a.bias_stride + c + 4 * g) = acc;
             }
-            if (!RING && a.seq_len) {   // uniform
+            if (!kFromMemory && a.seq_len) {   // uniform
                 wave_lds_sync();
-                mask_bias(a, bias_s, cc.tile * 16, seq_length_u(a.seq_len, cc.bh / a.H, a.n), g, j, 0, a.cid_pad, ~0);
+                mask_bias<BIAS>(a, bias_s, cc.tile * 16, seq_length_u(a.seq_len, cc.bh / a.H, a.n), g, j, 0, a.cid_pad);
             }
             if (DENSE && !tables_clear) {   // the whole region once; later tiles find it cleared by the reads below
                 for (int i = lane * 4; i < 32 * a.bias_stride; i += 256)
@@ -874,7 +883,7 @@ __global__ void __launch_bounds__(kTileThreads, DENSE ? 1 : 2) bwd_q_tile_kernel
                 tables_clear = true;
             }
         }
-        if (RING) ring_form(a, relid_s, bias_s, cc, qb0, qb1, g, j, rel_n);
+        if (kFromMemory) ring_form<BIAS>(a, relid_s, bias_s, cc, qb0, qb1, g, j, rel_n);
         wave_lds_sync();  // the previous pair's reads of k_s, v_s (and the previous tile's of bias_s) are done
 #pragma unroll
         for (int ci2 = 0; ci2 < 2; ++ci2)
@@ -905,7 +914,7 @@ __global__ void __launch_bounds__(kTileThreads, DENSE ? 1 : 2) bwd_q_tile_kernel
             cid[c][2] = (int)(short)(mpc[c].y & 0xFFFFu);
             cid[c][3] = (int)(short)(mpc[c].y >> 16);
 #pragma unroll
-            for (int r = 0; r < 4; ++r) bv[c][r] = bias_s[j * bias_stride + (RING ? cid[c][r] & (kRingIds - 1) : max(cid[c][r], 0))];
+            for (int r = 0; r < 4; ++r) bv[c][r] = bias_s[j * bias_stride + (BIAS == Bias::kRing ? bias_slot<BIAS>(cid[c][r]) : max(cid[c][r], 0))];
         }
         f32x4_t s4[2], d4[2];
 #pragma unroll

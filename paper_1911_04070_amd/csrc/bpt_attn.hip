@@ -188,7 +188,8 @@ void use_schedule(AttnArgs& a, const Schedule& sc) {
 // LDS of fwd_tile_kernel for this graph, or 0 if the tile path does not apply
 struct TilePlan {
     bool ok = false;       // the token tile kernels apply
-    bool ring = false;     // with the bias table as a ring (else whole, out of the relative-position table in LDS)
+    Bias bias = Bias::kStaged;
+    bool by_pairs = true;  // Bias::kMemory: formed pair by pair (else all of it with a tile's first pair)
     int cid_pad = 0, bias_stride = 0;
     size_t lds = 0;
 };
@@ -211,16 +212,27 @@ TilePlan plan_tiles(const bpt_graph* g, const DeviceLimits& lim, bool dense = fa
         t.ok = t.lds <= room && 64 * (t.cid_pad + 8) <= 64 * kRowStride * (int)sizeof(bf16_t);
         return t;
     }
-    // The whole table while two workgroups of it share a compute unit (up to about 100 ids), else the ring -- but where
-    // sequences end before n and tokens look to the right, the nodes past the end are masked as the table is formed, level
-    // by level: once per tile in the whole table, with every pair in the ring, which costs more than the second workgroup
-    // brings (packed, H = 8, bidirectional, whole against ring, forward and query-side kernels together: n = 4096, k = 7, 3
-    // sequences 87 / 126 us, 16 sequences 371 / 463 us; k = 12, 3 sequences 108 / 190 us; causal, k = 16, 80 / 72 us).
-    const bool mask_right = shorter && !g->causal && t.lds <= room;
-    if (2 * (t.lds + prefix) > lim.lds_cu && g->tiles.ring_ok && !mask_right) {
-        t.ring = true;
+    // Formed out of LDS while two workgroups of that share a compute unit (up to about 100 ids), else the ring, where it
+    // can hold every pair (ring_ok); up to 480 ids that are too many to be staged, out of memory.  But where sequences end
+    // before n and tokens look to the right, the nodes past the end are masked as the table is formed, level by level: once
+    // per tile where it is formed at once, with every pair in the ring, which costs more than the second workgroup brings.
+    // B * H = 128, n = 512, bidirectional, forward + backward (us):
+    //   k = 80 (459 ids, no ring)            gather kernels 1293, out of memory at once 783, by pairs 757
+    //   the same with sequences of 33 - 512  1282, 714, 968
+    //   k = 45 (325 ids)                     ring 272, out of memory at once 350
+    //   the same with sequences of 33 - 512  ring 409, out of memory at once 318
+    // Packed, H = 8, bidirectional, staged against ring, forward and query-side kernels together: n = 4096, k = 7, 3
+    // sequences 87 / 126 us, 16 sequences 371 / 463 us; k = 12, 3 sequences 108 / 190 us; causal, k = 16, 80 / 72 us.
+    const bool mask_right = shorter && !g->causal;
+    const bool staged = t.lds <= room, two = 2 * (t.lds + prefix) <= lim.lds_cu, memory = table + rows <= room;
+    if (!two && g->tiles.ring_ok && !(mask_right && memory)) {
+        t.bias = Bias::kRing;
         t.bias_stride = kRingStride;
         t.lds = (size_t)kTileWaves * 16 * kRingStride * sizeof(float) + rows;
+    } else if (!staged) {
+        t.bias = Bias::kMemory;
+        t.by_pairs = !mask_right;
+        t.lds = table + rows;
     }
     t.ok = t.lds <= room;
     return t;
@@ -245,6 +257,19 @@ int launch_tiles(const char* name, K kernel, const TileArgs& t, const DeviceLimi
 // workgroup leaves a copy of d_rel and the workspace is sized for them
 int dense_grid(const DeviceLimits& lim) { return std::max(8, lim.cus / 8 * 8); }
 
+template <Bias BIAS>
+int launch_fwd_tiles(const TileArgs& t, const DeviceLimits& lim, size_t lds, hipStream_t st) {
+    if (t.delta) return launch_tiles("fwd_tile_kernel", fwd_tile_kernel<BIAS, false, true>, t, lim, lds, st);   // a packed batch (no dropout there)
+    return t.drop_thr ? launch_tiles("fwd_tile_kernel", fwd_tile_kernel<BIAS, true>, t, lim, lds, st)
+                      : launch_tiles("fwd_tile_kernel", fwd_tile_kernel<BIAS, false>, t, lim, lds, st);
+}
+template <Bias BIAS>
+int launch_bwd_q_tiles(const TileArgs& t, const DeviceLimits& lim, size_t lds, hipStream_t st) {
+    if (t.delta) return launch_tiles("bwd_q_tile_kernel", bwd_q_tile_kernel<BIAS, false, false, true>, t, lim, lds, st);
+    return t.drop_thr ? launch_tiles("bwd_q_tile_kernel", bwd_q_tile_kernel<BIAS, true>, t, lim, lds, st)
+                      : launch_tiles("bwd_q_tile_kernel", bwd_q_tile_kernel<BIAS, false>, t, lim, lds, st);
+}
+
 // bf16 backward, query side of the token rows on dense tiles
 int run_bwd_q_tiles(const bpt_graph* g, const AttnArgs& a, const DeviceLimits& lim, bool dense, hipStream_t st) {
     const TilePlan tp = plan_tiles(g, lim, dense, a.seq_len != nullptr);
@@ -253,18 +278,15 @@ int run_bwd_q_tiles(const bpt_graph* g, const AttnArgs& a, const DeviceLimits& l
     if (dense) {   // no (w, p) pairs: the kernel leaves one copy of d_rel per workgroup
         t.drel_part = a.drel_part;
         const int grid = dense_grid(lim);
-        if (a.delta) return launch_tiles("bwd_q_tile_kernel", bwd_q_tile_kernel<false, false, true, true>, t, lim, tp.lds, st, grid);
-        return a.drop_thr ? launch_tiles("bwd_q_tile_kernel", bwd_q_tile_kernel<false, true, true>, t, lim, tp.lds, st, grid)
-                          : launch_tiles("bwd_q_tile_kernel", bwd_q_tile_kernel<false, false, true>, t, lim, tp.lds, st, grid);
+        if (a.delta) return launch_tiles("bwd_q_tile_kernel", bwd_q_tile_kernel<Bias::kStaged, false, true, true>, t, lim, tp.lds, st, grid);
+        return a.drop_thr ? launch_tiles("bwd_q_tile_kernel", bwd_q_tile_kernel<Bias::kStaged, true, true>, t, lim, tp.lds, st, grid)
+                          : launch_tiles("bwd_q_tile_kernel", bwd_q_tile_kernel<Bias::kStaged, false, true>, t, lim, tp.lds, st, grid);
     }
-    if (a.delta)   // a packed batch (no dropout there)
-        return tp.ring ? launch_tiles("bwd_q_tile_kernel", bwd_q_tile_kernel<true, false, false, true>, t, lim, tp.lds, st)
-                          : launch_tiles("bwd_q_tile_kernel", bwd_q_tile_kernel<false, false, false, true>, t, lim, tp.lds, st);
-    if (a.drop_thr)
-        return tp.ring ? launch_tiles("bwd_q_tile_kernel", bwd_q_tile_kernel<true, true>, t, lim, tp.lds, st)
-                          : launch_tiles("bwd_q_tile_kernel", bwd_q_tile_kernel<false, true>, t, lim, tp.lds, st);
-    return tp.ring ? launch_tiles("bwd_q_tile_kernel", bwd_q_tile_kernel<true, false>, t, lim, tp.lds, st)
-                      : launch_tiles("bwd_q_tile_kernel", bwd_q_tile_kernel<false, false>, t, lim, tp.lds, st);
+    switch (tp.bias) {
+        case Bias::kRing: return launch_bwd_q_tiles<Bias::kRing>(t, lim, tp.lds, st);
+        case Bias::kMemory: return launch_bwd_q_tiles<Bias::kMemory>(t, lim, tp.lds, st);
+        default: return launch_bwd_q_tiles<Bias::kStaged>(t, lim, tp.lds, st);
+    }
 }
 
 void fill_tile_args(TileArgs& t, const bpt_graph* g, const AttnArgs& a, const TilePlan& tp) {
@@ -290,7 +312,7 @@ void fill_tile_args(TileArgs& t, const bpt_graph* g, const AttnArgs& a, const Ti
     t.cols = g->tiles.cols;
     t.cid_to_id = g->tiles.cid_to_id;
     t.map = g->tiles.map;
-    t.pair_blocks = g->tiles.pair_blocks;
+    t.pair_blocks = tp.by_pairs ? g->tiles.pair_blocks : nullptr;
     t.num_tiles = g->tiles.num_tiles;
     t.num_chunks = g->tiles.num_chunks;
     t.num_cids = g->tiles.num_cids;
@@ -419,14 +441,11 @@ int run_span_tiles(const bpt_graph* g, const AttnArgs& a, bool forward, hipStrea
 int run_fwd_tiles(const bpt_graph* g, AttnArgs& a, const DeviceLimits& lim, const TilePlan& tp, hipStream_t st) {
     TileArgs t = {};
     fill_tile_args(t, g, a, tp);
-    if (a.delta)   // a packed batch (no dropout there)
-        return tp.ring ? launch_tiles("fwd_tile_kernel", fwd_tile_kernel<true, false, true>, t, lim, tp.lds, st)
-                          : launch_tiles("fwd_tile_kernel", fwd_tile_kernel<false, false, true>, t, lim, tp.lds, st);
-    if (a.drop_thr)
-        return tp.ring ? launch_tiles("fwd_tile_kernel", fwd_tile_kernel<true, true>, t, lim, tp.lds, st)
-                          : launch_tiles("fwd_tile_kernel", fwd_tile_kernel<false, true>, t, lim, tp.lds, st);
-    return tp.ring ? launch_tiles("fwd_tile_kernel", fwd_tile_kernel<true, false>, t, lim, tp.lds, st)
-                      : launch_tiles("fwd_tile_kernel", fwd_tile_kernel<false, false>, t, lim, tp.lds, st);
+    switch (tp.bias) {
+        case Bias::kRing: return launch_fwd_tiles<Bias::kRing>(t, lim, tp.lds, st);
+        case Bias::kMemory: return launch_fwd_tiles<Bias::kMemory>(t, lim, tp.lds, st);
+        default: return launch_fwd_tiles<Bias::kStaged>(t, lim, tp.lds, st);
+    }
 }
 
 template <typename T>

@@ -196,10 +196,34 @@ ATTENTION = [
     ("bf16", 16, 1, False, 2, [16, 9, 1]), ("bf16", 64, 2, False, 1, [33, 64, 2, 48]),
     ("bf16", 512, 4, False, 2, [512, 300, 33, 1, 0]), ("bf16", 1024, 3, True, 2, [1000, 17, 1024]),
     ("bf16", 2048, 16, False, 1, [2047, 1025]), ("bf16", 4096, 8, True, 1, [3000, 4096, 129]),
-    ("bf16", 1024, 40, False, 1, [700, 90]),
+    # the bias table out of memory, all of it with a tile's first pair of chunks; as a ring
+    ("bf16", 1024, 40, False, 1, [700, 90]), ("bf16", 512, 45, False, 2, [512, 300, 33]), ("bf16", 1024, 40, True, 2, [1000, 1024, 5]),
     # eight sequences of three tokens: eight consecutive span rows of degree 3 (no power of two)
     ("f32", 16, 1, False, 1, [3] * 9), ("bf16", 16, 2, False, 1, [3] * 9 + [6] * 8),
 ]
+
+
+# a batch graph without edge lists on a tree whose table is formed out of memory: accepted, and the rows of the graph that
+# has them (whose forward runs the same kernels; the key tiles of k = 80 have too many ids, so its backward is refused)
+@pytest.mark.parametrize("n,k,causal,lengths", [(512, 80, False, [512, 300, 33]), (1024, 120, True, [1000, 77])])
+def test_shared_tree_with_the_table_out_of_memory(n, k, causal, lengths):
+    say("shared tree", n, k, causal, lengths)
+    tree = bpt.bpt_build_graph(n, k, causal)
+    g = bpt.bpt_build_batch_graph_on(tree, lengths)
+    _, b_of, node_of = oracle.batch_rows(n, lengths)
+    gen = torch.Generator().manual_seed(3)
+    rows = {key: torch.randn((1, 2, g.num_nodes, 64), generator=gen).to(torch.bfloat16) for key in ("Q", "K", "V")}
+    Rel = (0.5 * torch.randn((tree.num_levels, tree.rel_width, 64), generator=gen)).to(torch.bfloat16)
+    out, lse = bpt.bpt_attn_fwd(g, *(rows[key].cuda() for key in ("Q", "K", "V")), Rel.cuda(), scale=0.125)
+    torch.cuda.synchronize()
+    padded = {key: np.zeros((len(lengths), 2, 2 * n - 1, 64), dtype=np.float32) for key in rows}
+    for key in rows:
+        padded[key][b_of, :, node_of] = np.transpose(rows[key][0].float().numpy(), (1, 0, 2))
+    o, l, _ = oracle.attn_fwd_lengths(n, k, causal, lengths, padded["Q"], padded["K"], padded["V"], Rel.float().numpy(), 0.125)
+    assert np.abs(host(out)[0] - np.transpose(o[b_of, :, node_of], (1, 0, 2))).max() <= TOL["bf16"]
+    assert np.abs(host(lse)[0] - np.transpose(l[b_of, :, node_of], (1, 0))).max() <= TOL["bf16"]
+    g.destroy()
+    tree.destroy()
 
 
 @pytest.mark.parametrize("dtype,n,k,causal,H,lengths", ATTENTION)

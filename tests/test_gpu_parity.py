@@ -204,33 +204,55 @@ def test_bias_table_whole_and_as_a_ring(n, k, causal, lengths):
 # more ids than the ring holds, all of them right-side ids past the end; masks of ids that the ring no longer holds would fall
 # on the level-1 nodes.  Those (every span node) have values eight times as large here, so that a lost edge shows: the 7 of 250
 # edges that token 250 then loses change `out` by sqrt(7) * 8 / 250 = 0.08 and lse by 0.03.
-@pytest.mark.parametrize("n,k,lengths", [(256, 240, [255, 250]), (256, 300, [255, 241])])
+@pytest.mark.parametrize("n,k,lengths", [(256, 240, [255, 250]), (256, 300, [255, 241]), (1024, 60, [1024, 700]), (1024, 60, [1000, 33])])
 def test_ring_masks_past_the_end_of_a_sequence(n, k, lengths):
-    say("ring masks", n, k, lengths)
-    w = Workload("ring_masks", 13, n, k, False, len(lengths), 2, 64, "bf16", True)
+    run_token_tiles(n, k, False, lengths, v_times=8)
+
+
+def run_token_tiles(n, k, causal, lengths, p=0.0, v_times=1, rel_times=1):
+    """Forward and backward against the oracle with values of span nodes and a table that are larger than usual (powers
+    of two: exact in bf16), so that a lost edge or a wrong row of the table shows; the token rows must run on tiles."""
+    say("token tiles", n, k, causal, lengths, p)
+    B = len(lengths) if lengths else 1
+    w = Workload("token_tiles", 13, n, k, causal, B, 2, 64, "bf16", True)
     x = make_inputs(w)
-    x["V"][:, :, n:] *= np.float32(8)      # exact in bf16
-    g = bpt.bpt_build_graph(n, k, False)
+    x["V"][:, :, n:] *= np.float32(v_times)
+    x["Rel"] = x["Rel"] * np.float32(rel_times)
+    seed = 20191104 + n + k
+    drop = (p, seed) if p > 0 else None
+    g = bpt.bpt_build_graph(n, k, causal)
     Q, K, V, dO, R = (to_dev(x[k_], "bf16") for k_ in ("Q", "K", "V", "dO", "Rel"))
-    lens_d = torch.tensor(lengths, dtype=torch.int32, device="cuda")
+    lens_d = torch.tensor(lengths, dtype=torch.int32, device="cuda") if lengths else None
     bpt.bpt_profile_enable(True)
-    out_d, lse_d = bpt.bpt_attn_fwd(g, Q, K, V, R, scale=w.scale, seq_len=lens_d)
-    grads = bpt.bpt_attn_bwd(g, Q, K, V, R, lse_d, dO, scale=w.scale, seq_len=lens_d)
+    out_d, lse_d = bpt.bpt_attn_fwd(g, Q, K, V, R, scale=w.scale, seq_len=lens_d, dropout=drop)
+    grads = bpt.bpt_attn_bwd(g, Q, K, V, R, lse_d, dO, scale=w.scale, seq_len=lens_d, dropout=drop)
     torch.cuda.synchronize()
     ran = set(bpt.bpt_profile_report())
     bpt.bpt_profile_enable(False)
-    assert {"fwd_tile_kernel", "bwd_q_tile_kernel"} <= ran, ran
-    o, l, _ = oracle.attn_fwd_lengths(n, k, False, lengths, x["Q"], x["K"], x["V"], x["Rel"], w.scale)
-    refs = oracle.attn_bwd_lengths(n, k, False, lengths, x["Q"], x["K"], x["V"], x["Rel"], x["dO"], w.scale)
+    assert {"fwd_tile_kernel", "bwd_q_tile_kernel"} <= ran and not ran & {"fwd_kernel", "bwd_q_kernel"}, ran
+    ll = lengths if lengths else [n] * B
+    o, l, _ = oracle.attn_fwd_lengths(n, k, causal, ll, x["Q"], x["K"], x["V"], x["Rel"], w.scale, dropout=p, seed=seed)
+    refs = oracle.attn_bwd_lengths(n, k, causal, ll, x["Q"], x["K"], x["V"], x["Rel"], x["dO"], w.scale, dropout=p, seed=seed)
     res = {}
     for name, got_t, ref in zip(("out", "lse", "dQ", "dK", "dV", "d_rel"), (out_d, lse_d) + tuple(grads), (o, l) + refs):
         got = host(got_t)
         assert np.isfinite(got).all(), name
-        res[name] = (float(np.abs(got - ref).max()), float(np.abs(ref).max()))
-    say("   max-abs errors, largest entries", res)
-    for name, (err, most) in res.items():
-        assert err <= 2e-2 * max(1.0, most / 4.0), (name, err, most)
+        res[name] = (float(np.abs(got - ref).max()), tol_for("bf16", ref, scaled=True) / ((1.0 - p) if name == "out" else 1.0))
+    say("   max-abs errors", {k_: float("%.3g" % v[0]) for k_, v in res.items()})
+    for name, (err, tol) in res.items():
+        assert err <= tol, (name, err, tol)
     g.destroy()
+
+
+# graphs whose ids are too many for a staged table (more than about 300) and too far apart within a pair of chunks for the
+# ring: the whole table out of memory, by pairs or (bidirectional sequences that end before n) at once.  459, 359, 436, 289 and
+# 345 ids, k = 45: the ring without lengths, out of memory with them; the last: the largest number of ids, 479
+@pytest.mark.parametrize("n,k,causal,lengths,p", [
+    (512, 80, False, None, 0.0), (512, 80, False, [512, 300, 33], 0.0), (512, 80, False, [400, 511], 0.1), (1024, 120, True, None, 0.0),
+    (1024, 120, True, [1000, 77], 0.0), (2048, 100, True, None, 0.2), (512, 127, True, None, 0.0), (256, 87, False, [255, 100, 1], 0.0),
+    (512, 45, False, [512, 300, 33], 0.0), (512, 45, False, [450, 511], 0.1), (512, 88, False, [511], 0.0)])
+def test_token_tiles_with_the_table_out_of_memory(n, k, causal, lengths, p):
+    run_token_tiles(n, k, causal, lengths, p, rel_times=16)
 
 
 @pytest.mark.parametrize("name", FULL)
