@@ -33,7 +33,6 @@ struct KeyArgs {
     const int32_t *tile_node0, *tile_info, *cols, *task_tile, *task_c0, *task_nch, *task_part;
     const int32_t *task_ntiles, *chunk_ptr;   // chained tasks: tiles the task walks, first chunk of every tile
     const int16_t* map;
-    const int32_t* id_blocks;   // [chunks] bit b: an edge of the chunk carries one of the ids 16b .. 16b + 15
     int32_t num_tasks, num_part, num_chunks, nb_pad, W, zero;
     const int32_t* seq_len;   // [B] tokens of every sequence, or null
     int32_t leave_unkept;     // rows of nodes a shorter sequence does not keep: left unwritten instead of zero-filled
@@ -45,6 +44,9 @@ struct KeyArgs {
     // 8 task counters (one per XCD, 64 bytes apart), zero when the kernel starts: cleared by the last kernel
     // of the query side when both sides run in one call, else by zero_ints_kernel
     int32_t* queue;
+    // (what one variant reads stands last: in the middle of the struct it changed the code of all the others, the chained
+    // kernels' with dropout by 3 % in time)
+    const int32_t* id_blocks;   // [chunks] bit b: an edge of the chunk carries one of the ids 16b .. 16b + 15
 };
 
 // `count` ints = 0 (a fill kernel, so that the call can be captured in a graph)
@@ -607,11 +609,8 @@ __global__ void __launch_bounds__(kTileThreads, 2) bwd_kv_chain_kernel(const Key
                         const float bv1 = __shfl(b4[ci][1][r], src);
                         bv = bid[r] >= 16 ? bv1 : bv;
                     }
-                    // with dropout the branch is the better form: this kernel, n = 512, k = 4, 32 x 8 heads, 111 -> 108 us
-                    // (without dropout, 8 sequences, one head: 33.2 with the branch, 31.8 us without)
-                    const bool on = bid[r] >= 0 && key_kept;
-                    const float arg = (s4[ci][r] + bv) * qscale - st[r].x;
-                    const float p = DROP ? (on ? fast_exp2(arg) : 0.f) : masked_exp2(on, arg);
+                    const float p = DROP ? (bid[r] >= 0 && key_kept ? fast_exp2((s4[ci][r] + bv) * qscale - st[r].x) : 0.f)
+                                         : masked_exp2(bid[r] >= 0 && key_kept, (s4[ci][r] + bv) * qscale - st[r].x);
                     if (DROP) {
                         const uint32_t x2 = bid[r] < a.W ? (uint32_t)(level * a.W + bid[r]) : 0x80000000u + (uint32_t)(node0 + j);
                         const float keep = drop_scale(rowh_s[16 * ci + 4 * g + r], x2, a.drop_thr, a.drop_inv_keep);

@@ -219,7 +219,7 @@ __global__ void __launch_bounds__(kTileThreads) fwd_span_tile_kernel(const SpanA
         for (int c = 0; c < 2; ++c)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                p[c][r] = masked_exp2(p[c][r] > 0.5f * kNegBig, p[c][r] - m);
+                p[c][r] = p[c][r] > 0.5f * kNegBig ? fast_exp2(p[c][r] - m) : 0.f;
                 l += p[c][r];
             }
         l += __shfl_xor(l, 16);
@@ -362,7 +362,7 @@ __device__ __forceinline__ void fwd_span_merge_small(const SpanArgs& a, int item
     float acc = 0.f, ls = 0.f;
 #pragma unroll
     for (int b = 0; b < kSpanSmallMax; ++b) {
-        const float c = masked_exp2(b < r.cnt, m[b] - mx);
+        const float c = b < r.cnt ? fast_exp2(m[b] - mx) : 0.f;
         ls += l[b] * c;
         acc += o[b] * c;
     }
@@ -525,7 +525,7 @@ __global__ void __launch_bounds__(kTileThreads, 3) bwd_q_span_tile_kernel(const 
             for (int r = 0; r < 4; ++r) {
                 const int tt = 16 * c + 4 * g + r;
                 const bool member = valid && (grp == 2 || (tt >> level) == loc) && t0 + tt < len;
-                p[c][r] = masked_exp2(member, s4[r] * qscale + shift - lse2);
+                p[c][r] = member ? fast_exp2(s4[r] * qscale + shift - lse2) : 0.f;
                 const float keep = DROP ? drop_scale(rowh, drop_edge_x(false, 0, t0 + tt), a.drop_thr, a.drop_inv_keep) : 1.f;
                 wgt[c][r] = p[c][r] * d4[r] * keep;
                 dl += wgt[c][r];

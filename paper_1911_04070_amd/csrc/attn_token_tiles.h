@@ -42,9 +42,6 @@ struct TileArgs {
     float scale;
     const int32_t *chunk_ptr, *cols, *cid_to_id;
     const int16_t* map;
-    // Bias::kRing, kMemory: [chunks / 2] blocks of 16 compact ids a tile has met up to and with the pair, or null: all of
-    // them with the first
-    const int32_t* pair_blocks;
     int32_t num_tiles, num_chunks, num_cids, cid_pad, bias_stride;
     int32_t row_bytes;
     uint32_t slab_bytes;
@@ -58,7 +55,6 @@ struct TileArgs {
     const int32_t *seq_len, *id_to_cid;
     int32_t leave_unkept;   // rows of nodes a shorter sequence does not keep: left unwritten instead of zero-filled
     int32_t grad_bf16;      // dQ leaves rounded to bf16
-    float* dq32;            // not null (grad_bf16 without DENSE): dQ so far as fp32 [batch*head][num_tiles * 16][64], not to dQ
     int32_t n, k, W, ctx_levels, causal;
     // packed batch: delta[level][sequence] (see attn_device.h) or null; lse of (batch*head index bh, node u) is at
     // (bh / H) * lse_sb + (bh % H) * lse_sh + row of u
@@ -68,6 +64,11 @@ struct TileArgs {
     // dropout on the attention weights (DROP variants of the kernels)
     uint32_t drop_thr, drop_seed;
     float drop_inv_keep;
+    // (what some variants only read stands last: see KeyArgs)
+    // Bias::kRing, kMemory: [chunks / 2] blocks of 16 compact ids a tile has met up to and with the pair, or null: all of
+    // them with the first
+    const int32_t* pair_blocks;
+    float* dq32;            // not null (grad_bf16 without DENSE): dQ so far as fp32 [batch*head][num_tiles * 16][64], not to dQ
 };
 
 __device__ __forceinline__ void wave_lds_sync() {  // order LDS traffic between the lanes of one wavefront
@@ -539,7 +540,8 @@ __global__ void __launch_bounds__(kTileThreads, 2) fwd_tile_kernel(const TileArg
         for (int c = 0; c < 2; ++c)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                const float p = masked_exp2(sc[c][r] > 0.5f * kNegBig, sc[c][r] - mn);
+                const float p = kFromMemory ? masked_exp2(sc[c][r] > 0.5f * kNegBig, sc[c][r] - mn)
+                                            : sc[c][r] > 0.5f * kNegBig ? fast_exp2(sc[c][r] - mn) : 0.f;
                 sc[c][r] = p;
                 psum += p;
             }
@@ -936,7 +938,8 @@ __global__ void __launch_bounds__(kTileThreads, DENSE ? 1 : 2) bwd_q_tile_kernel
         for (int c = 0; c < 2; ++c) {
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                const float p = masked_exp2(cid[c][r] >= 0, (s4[c][r] + bv[c][r]) * qscale - lse2);
+                const float p = kFromMemory ? masked_exp2(cid[c][r] >= 0, (s4[c][r] + bv[c][r]) * qscale - lse2)
+                                            : cid[c][r] >= 0 ? fast_exp2((s4[c][r] + bv[c][r]) * qscale - lse2) : 0.f;
                 // with dropout out = sum keep p v, so dP carries the mask
                 const float keep = DROP ? drop_scale(rowh, (uint32_t)relid_s[max(cid[c][r], 0)], a.drop_thr, a.drop_inv_keep) : 1.f;
                 const float wgt = p * d4[c][r] * keep;
