@@ -698,13 +698,22 @@ int run_bwd_q(const bpt_graph* g, const BwdPlan& p, AttnArgs& a, hipStream_t st)
     return BPT_OK;
 }
 
+// Workgroups of a key-side kernel: as many as the device holds at once, a multiple of 8 (one share of the tasks per XCD),
+// but no more wavefronts than a share has tasks.  The wavefronts take the tasks in the order in which they arrive at the
+// share's counter; with more of them than tasks the tasks fall to whoever comes first, two to a SIMD in one place and none
+// in another, and a launch takes as long as the unlucky ones (causal, 10 x 5 heads, the kernel: n = 512, k = 2 39.7 -> 32.7
+// us, k = 4 42.3 -> 35.4 us; 4 x 8 heads, n = 1024, k = 4 45.7 -> 36.2 us; n = 1024, k = 16, 8 heads 30.2 -> 27.8 us).
+int kv_grid(const KeyArgs& t, int resident) {
+    const int64_t share = ((int64_t)t.BH * t.num_tasks + 7) / 8;
+    return (int)std::max<int64_t>(8, 8 * std::min<int64_t>(resident / 8, (share + kTileWaves - 1) / kTileWaves));
+}
+
 template <int NBC, bool DROP, bool PACKED = false>
 int launch_kv_tiles_as(const KeyArgs& t, const BwdPlan& p, const DeviceLimits& lim, hipStream_t st) {
     if (p.kv_lds > 65536)
         BPT_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(bwd_kv_tile_kernel<NBC, DROP, PACKED>),
                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)p.kv_lds));
-    const int grid =
-        std::max(8, lim.cus * resident_blocks(bwd_kv_tile_kernel<NBC, DROP, PACKED>, kTileThreads, p.kv_lds, lim) / 8 * 8);
+    const int grid = kv_grid(t, lim.cus * resident_blocks(bwd_kv_tile_kernel<NBC, DROP, PACKED>, kTileThreads, p.kv_lds, lim));
     BPT_LAUNCH("bwd_kv_tile_kernel", (bwd_kv_tile_kernel<NBC, DROP, PACKED>), dim3(grid), dim3(kTileThreads), p.kv_lds, st, t);
     BPT_HIP(hipGetLastError());
     return BPT_OK;
@@ -719,8 +728,7 @@ int launch_kv_chain_as(const KeyArgs& t, const BwdPlan& p, const DeviceLimits& l
     if (p.kv_lds > 65536)
         BPT_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(bwd_kv_chain_kernel<NBC, DROP, G16, PACKED>),
                                     hipFuncAttributeMaxDynamicSharedMemorySize, (int)p.kv_lds));
-    const int grid =
-        std::max(8, lim.cus * resident_blocks(bwd_kv_chain_kernel<NBC, DROP, G16, PACKED>, kTileThreads, p.kv_lds, lim) / 8 * 8);
+    const int grid = kv_grid(t, lim.cus * resident_blocks(bwd_kv_chain_kernel<NBC, DROP, G16, PACKED>, kTileThreads, p.kv_lds, lim));
     BPT_LAUNCH("bwd_kv_chain_kernel", (bwd_kv_chain_kernel<NBC, DROP, G16, PACKED>), dim3(grid), dim3(kTileThreads), p.kv_lds, st, t);
     BPT_HIP(hipGetLastError());
     return BPT_OK;
