@@ -561,15 +561,14 @@ int plan_bwd(const bpt_graph* g, const bpt_shape_t* s, BwdPlan* p) {
     off += align_up(bh * std::max<size_t>(std::max(g->fwd.num_part, g->fwd_span.num_part), span_partials(g)) *
                     kQPartStride * sizeof(float));
     p->off_kvpart = off;
-    off += align_up(bh * std::max<size_t>(g->tr.num_part, p->kv_tiles ? (size_t)g->ktiles.num_part * 16 : 0) * 2 * kD *
-                    sizeof(float));
+    // gradients rounded to bf16: dQ of the token rows stays fp32 until rel_grad_tile_kernel has added to it, where the key
+    // side, which runs behind it, keeps its partial sums (sized for either type of gradients: one workspace serves both)
+    p->off_dq32 = off;
+    off += align_up(std::max(bh * std::max<size_t>(g->tr.num_part, p->kv_tiles ? (size_t)g->ktiles.num_part * 16 : 0) * 2 * kD,
+                             p->drel_tile && !p->dense_ds ? bh * g->tiles.num_tiles * 16 * kD : 0) * sizeof(float));
     p->off_drel = off;
     if (!p->drel_tile) p->drel_part_rows = p->drel_rows;
     off += align_up((size_t)p->drel_grid_x * p->drel_part_rows * kD * sizeof(float));
-    // gradients rounded to bf16: dQ of the token rows stays fp32 until rel_grad_tile_kernel has added to it (sized for
-    // either type of gradients, so that one workspace serves both)
-    p->off_dq32 = off;
-    off += align_up(p->drel_tile && !p->dense_ds ? bh * g->tiles.num_tiles * 16 * kD * sizeof(float) : 0);
     p->off_queue = off;
     off += align_up(kQueueInts * sizeof(int32_t));   // task counters of the key-tile kernel
     p->total = off;

@@ -695,6 +695,15 @@ def test_gradients_rounded_to_bf16(n, k, causal, B, H, lengths, leave, node_majo
     g.destroy()
 
 
+def test_backward_workspace_at_the_character_level_density():
+    # the fp32 rows of dQ that bf16 gradients need for a while (64 MiB here) lie where the key side keeps its partial sums:
+    # 4 x 8 heads on n = 8192, k = 64 take what they took when dQ was rounded twice
+    g = bpt.bpt_build_graph(8192, 64, True)
+    Q = torch.empty((4, 8, g.num_nodes, 64), dtype=torch.bfloat16, device="cuda")
+    assert bpt.workspace_bytes(g, Q)[1] <= 975700224
+    g.destroy()
+
+
 def test_bf16_gradients_are_for_bf16_tensors():
     g = bpt.bpt_build_graph(64, 2, False)
     Q = torch.zeros(1, 1, g.num_nodes, 64, device="cuda")
