@@ -518,7 +518,7 @@ int build_tile_metadata(bpt_graph* g, const int32_t* cnt_l, const int32_t* min_l
     BPT_HIP(tile_hi.alloc(sizeof(int32_t) * (size_t)tiles * nb));
     BPT_HIP(tile_first.alloc(sizeof(int32_t) * (size_t)tiles * nb));
     BPT_HIP(tile_nch.alloc(sizeof(int32_t) * (size_t)tiles));
-    int32_t* d_tot = totals.as<int32_t>();   // 0: ids in use, 1: token chunks, 2: key chunks, 3: tasks, 4: partials, 5: multi tiles
+    int32_t* d_tot = totals.as<int32_t>();   // 0: ids in use, 1: token chunks, 2: key chunks, 3: tasks, 4: partials, 5: multi tiles, 6: a pair of token chunks is too wide for the ring
     BPT_HIP(hipMemsetAsync(d_tot, 0, sizeof(int32_t) * 8, st));
     BPT_HIP(hipMemsetAsync(used.p, 0, sizeof(int32_t) * (size_t)num_ids, st));
 
@@ -582,9 +582,7 @@ int build_tile_metadata(bpt_graph* g, const int32_t* cnt_l, const int32_t* min_l
     hipLaunchKernelGGL(token_tile_map, dim3((n + kTB / 64 - 1) / (kTB / 64)), dim3(kTB), 0, st, n, nb, W, zero, g->row_ptr, g->col,
                        g->rel, tt.chunk_ptr, tile_lo.as<int32_t>(), tile_first.as<int32_t>(), tt.id_to_cid, tt.map);
     hipLaunchKernelGGL(token_tile_pair_blocks, dim3(tiles), dim3(64), 0, st, tiles, tt.chunk_ptr, tt.map, tt.pair_blocks, d_tot + 6);
-    int32_t too_wide = 0;
     BPT_HIP(hipGetLastError());
-    BPT_HIP(hipMemcpyAsync(&too_wide, d_tot + 6, sizeof too_wide, hipMemcpyDeviceToHost, st));   // (read behind the last synchronisation)
     tt.num_cids = num_cids;
     tt.num_chunks = (int32_t)chunks;
     tt.num_tiles = tiles;
@@ -639,7 +637,10 @@ int build_tile_metadata(bpt_graph* g, const int32_t* cnt_l, const int32_t* min_l
         kt.num_part = num_part;
         kt.num_tasks = num_tasks;
     }
-    // the temporaries are freed when this function returns: wait for the kernels that read them
+    // the temporaries are freed when this function returns: wait for the kernels that read them.  (The copy is requested
+    // here, where nothing can return before it has arrived.)
+    int32_t too_wide = 0;
+    BPT_HIP(hipMemcpyAsync(&too_wide, d_tot + 6, sizeof too_wide, hipMemcpyDeviceToHost, st));
     BPT_HIP(hipStreamSynchronize(st));
     tt.ring_ok = too_wide == 0;
     return BPT_OK;
