@@ -761,18 +761,22 @@ bpt_shape_t attn_shape(const bpt_graph* g, int B, int H, float scale, const int3
     return s;
 }
 
-// slices of the contraction over K for an M x N result: enough to give every compute unit two tiles, a power of two
-// (the library's kernels for other counts are often slower ones) and at least 900 rows each.
-// 15 000 rows, d = 512: the four products of a layer 249 -> 168 us and the sums of their slices 24 -> 36 us; 65 532 rows:
-// [dWq | dWk | dWv] 193 us in 11 slices, 114 us in 16.
+// slices of the contraction over K for an M x N result: a power of two (the library's kernels for other counts are often
+// slower ones; 65 532 rows, d = 512, [dWq | dWk | dWv]: 193 us in 11 slices, 121 us in 16), no more than give every compute
+// unit two tiles, and at least 1000 rows each (trees of powers of two have just fewer rows than a power of two, which a
+// bound of 1024 would halve the slices of).  Swept over the four products of a layer, d = 128, 256, 384, 512, 1024, 13 row
+// counts from 1021 to 131 056 and 1, 2, 4, 8, 16 slices, sums of the slices included: this takes on average 1.046 times the
+// best count's time (at least 512 rows 1.059, 900 or 1024 rows 1.048, 1400 rows 1.053, 1800 rows 1.084).
 int pick_slices(int M, int N, int64_t K) {
     const int64_t tiles = (int64_t)((M + 127) / 128) * ((N + 127) / 128);
     int slices = 1;
-    while (slices < 16 && slices * tiles < 512 && K / (2 * slices) >= 900) slices *= 2;
+    while (slices < 16 && slices * tiles < 512 && K / (2 * slices) >= 1000) slices *= 2;
     return slices;
 }
 
-// workgroups of the normalisations up to d = 512: what 256 compute units hold at once at the kernels' registers
+// workgroups of the normalisations: what 256 compute units hold at once at the kernels' registers up to d = 512; wider ones
+// walk the same grid (two calls each, before they held parameters and read ahead / now, us: d = 1024, 16 376 rows, forward
+// 69.7 / 55.4, backward 160 / 85; d = 2048, 8188 rows, 76.9 / 65.2 and 268 / 154)
 constexpr int kLnBlocks = 7 * 256, kLnBwdBlocks = 4 * 256;
 constexpr int kColumnSumBlocks = 2048;   // workgroups (= partial rows) of the kernels that sum over rows
 
