@@ -525,15 +525,11 @@ int plan_bwd(const bpt_graph* g, const bpt_shape_t* s, BwdPlan* p) {
             if (cids <= 16 * kDenseChunks && plan_tiles(g, lim, true).ok) p->dense_ds = true;
         }
         if (g->ktiles.num_tasks > 0 && g->ktiles.nb_pad <= 16 * kMaxBiasChunks) {
-            p->kv_lds = (size_t)kTileWaves * (16 * (g->ktiles.nb_pad + 1) * sizeof(float) + 64 * kRowStride * sizeof(bf16_t) +
-                                              32 * sizeof(float2) + 32 * sizeof(uint32_t));
+            p->kv_chain = g->ktiles.nb_pad <= 32;
+            // per wavefront the rows, statistics and hashes of 32 queries, and the bias of 16 or the sums of 16 keys
+            p->kv_lds = (size_t)kTileWaves * (16 * (p->kv_chain ? kKvOutStride : g->ktiles.nb_pad + 1) * sizeof(float) +
+                                              64 * kRowStride * sizeof(bf16_t) + 32 * sizeof(float2) + 32 * sizeof(uint32_t));
             p->kv_tiles = p->kv_lds <= lim.lds;
-            const size_t chain_lds = (size_t)kTileWaves * (64 * kRowStride * sizeof(bf16_t) + 16 * kKvOutStride * sizeof(float) +
-                                                            32 * sizeof(float2) + 32 * sizeof(uint32_t));
-            if (g->ktiles.nb_pad <= 32 && chain_lds <= lim.lds) {
-                p->kv_tiles = p->kv_chain = true;
-                p->kv_lds = chain_lds;
-            }
         }
         p->drel_grid_y = p->drel_tile ? 1 : (p->drel_rows + kRgIds - 1) / kRgIds;
         blocks = (int64_t)s->B * s->H * ((g->n_tokens + kRgRows - 1) / kRgRows);
@@ -799,8 +795,8 @@ int run_bwd_kv_tiles(const bpt_graph* g, const BwdPlan& p, const AttnArgs& a, co
     }
     int rc = BPT_ERR_UNSUPPORTED;
     switch (kt.nb_pad / 16) {
-        case 1: rc = p.kv_chain ? launch_kv_chain<1>(t, p, lim, st) : launch_kv_tiles<1>(t, p, lim, st); break;
-        case 2: rc = p.kv_chain ? launch_kv_chain<2>(t, p, lim, st) : launch_kv_tiles<2>(t, p, lim, st); break;
+        case 1: rc = launch_kv_chain<1>(t, p, lim, st); break;   // (p.kv_chain)
+        case 2: rc = launch_kv_chain<2>(t, p, lim, st); break;
         case 3: rc = launch_kv_tiles<3>(t, p, lim, st); break;
         case 4: rc = launch_kv_tiles<4>(t, p, lim, st); break;
         default: rc = launch_kv_tiles<0>(t, p, lim, st); break;   // (at most kMaxBiasChunks, plan_bwd)
