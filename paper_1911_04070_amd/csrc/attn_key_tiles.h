@@ -44,9 +44,7 @@ struct KeyArgs {
     // 8 task counters (one per XCD, 64 bytes apart), zero when the kernel starts: cleared by the last kernel
     // of the query side when both sides run in one call, else by zero_ints_kernel
     int32_t* queue;
-    // (what one variant reads stands last: in the middle of the struct it changed the code of all the others, the chained
-    // kernels' with dropout by 3 % in time)
-    const int32_t* id_blocks;   // [chunks] bit b: an edge of the chunk carries one of the ids 16b .. 16b + 15
+    const int32_t* id_blocks;   // [chunks] bit b: an edge of the chunk carries one of the ids 16b .. 16b + 15 (last: see TileArgs)
 };
 
 // `count` ints = 0 (a fill kernel, so that the call can be captured in a graph)

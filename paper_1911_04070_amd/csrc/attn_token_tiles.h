@@ -35,7 +35,13 @@ constexpr int kDqStride = 68;    // floats per row of a tile's fp32 dQ rows on t
 constexpr int kDenseChunks = 8;   // 16-id chunks the dense variant of bwd_q_tile_kernel keeps d_rel sums for
 struct TileArgs {
     const bf16_t *Q, *K, *V, *rel;
-    bf16_t* out;
+    // (What only some variants read shares a place with what only others do or stands last: in the middle of the struct it
+    // changed the code of all variants.  The struct ends within its fifth 64 bytes, and with it the launch's own
+    // arguments behind it: a small launch waits for every line of them.)
+    union {
+        bf16_t* out;     // forward
+        float* dq32;     // query side, not null (grad_bf16 without DENSE): dQ so far as fp32 [batch*head][num_tiles * 16][64], not to dQ
+    };
     float* lse;
     int64_t sb, sh, sn;
     int32_t BH, H, N;
@@ -64,11 +70,9 @@ struct TileArgs {
     // dropout on the attention weights (DROP variants of the kernels)
     uint32_t drop_thr, drop_seed;
     float drop_inv_keep;
-    // (what some variants only read stands last: see KeyArgs)
     // Bias::kRing, kMemory: [chunks / 2] blocks of 16 compact ids a tile has met up to and with the pair, or null: all of
     // them with the first
     const int32_t* pair_blocks;
-    float* dq32;            // not null (grad_bf16 without DENSE): dQ so far as fp32 [batch*head][num_tiles * 16][64], not to dQ
 };
 
 __device__ __forceinline__ void wave_lds_sync() {  // order LDS traffic between the lanes of one wavefront
@@ -232,7 +236,7 @@ __device__ __forceinline__ void cursor_uniform(TileCursor& c) {
 //     64: 8 instead of 31 KB), which lets a second workgroup onto every compute unit.  k = 64, n = 8192, causal, 32 (batch,
 //     head)s: this kernel 356 -> 220 us, the query side 437 -> 374 us (the 1.2 GB of (w, p) it writes bound it); k = 16, n =
 //     4096, 64 of them, dropout: 200 -> 183 and 277 -> 262 us.
-//   kMemory: the whole table, formed as in the ring, or all of it with a tile's first pair (pair_blocks null).
+//   kMemory: the whole table, formed as in the ring, or all of it with a tile's first pair (TileArgs.pair_blocks null).
 constexpr int kRingAhead = 3;               // blocks of a pair requested ahead (the first pair of a tile may need more)
 struct RelAhead {
     bf16x8_t r[kRingAhead][2];
@@ -540,8 +544,8 @@ __global__ void __launch_bounds__(kTileThreads, 2) fwd_tile_kernel(const TileArg
         for (int c = 0; c < 2; ++c)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                const float p = kFromMemory ? masked_exp2(sc[c][r] > 0.5f * kNegBig, sc[c][r] - mn)
-                                            : sc[c][r] > 0.5f * kNegBig ? fast_exp2(sc[c][r] - mn) : 0.f;
+                const float p = kFromMemory || !DROP ? masked_exp2(sc[c][r] > 0.5f * kNegBig, sc[c][r] - mn)
+                                                     : sc[c][r] > 0.5f * kNegBig ? fast_exp2(sc[c][r] - mn) : 0.f;
                 sc[c][r] = p;
                 psum += p;
             }

@@ -299,7 +299,10 @@ void fill_tile_args(TileArgs& t, const bpt_graph* g, const AttnArgs& a, const Ti
     t.K = static_cast<const bf16_t*>(a.K);
     t.V = static_cast<const bf16_t*>(a.V);
     t.rel = static_cast<const bf16_t*>(a.rel);
-    t.out = static_cast<bf16_t*>(a.out);
+    if (a.out)
+        t.out = static_cast<bf16_t*>(a.out);
+    else
+        t.dq32 = a.dq32;
     t.lse = a.lse_w;
     t.sb = a.sb;
     t.sh = a.sh;
@@ -323,7 +326,6 @@ void fill_tile_args(TileArgs& t, const bpt_graph* g, const AttnArgs& a, const Ti
     t.seq_len = a.seq_len;
     t.leave_unkept = a.leave_unkept;
     t.grad_bf16 = a.grad_bf16;
-    t.dq32 = a.dq32;
     t.delta = a.delta;
     t.levels = g->num_levels;
     t.lg = g->num_levels - 1;
@@ -769,9 +771,9 @@ int run_bwd_kv_tiles(const bpt_graph* g, const BwdPlan& p, const AttnArgs& a, co
     t.task_c0 = kt.task_c0;
     t.task_nch = kt.task_nch;
     t.task_part = kt.task_part;
-    t.task_ntiles = kt.task_ntiles;
     t.chunk_ptr = kt.chunk_ptr;
     t.map = kt.map;
+    t.task_ntiles = kt.task_ntiles;
     t.id_blocks = kt.id_blocks;
     t.num_tasks = kt.num_tasks;
     t.num_part = kt.num_part;
