@@ -1254,7 +1254,7 @@ __global__ void __launch_bounds__(kThreads, CPW == 2 ? 4 : 2) rel_grad_tile_kern
         float4 dq_old = make_float4(0.f, 0.f, 0.f, 0.f);
         if (dq_add)
             dq_old = a.dq32 ? *reinterpret_cast<const float4*>(a.dq32 + ((int64_t)bh * a.num_tiles * 16 + dq_row) * kD + 16 * fc + 4 * g)
-                            : load_grad4(a.dQ, dq_at, a.grad_bf16);
+                            : *reinterpret_cast<const float4*>(a.dQ + dq_at);   // (fp32: with grad_bf16 there is dq32)
         const int blk_next = next_block(blk + gridDim.x);
         if (blk_next < total) prefetch(blk_next);
         __syncthreads();
