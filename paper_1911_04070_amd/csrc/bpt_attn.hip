@@ -195,8 +195,9 @@ struct TilePlan {
 };
 // dense: the plan of bwd_q_tile_kernel<.., DENSE> -- ids padded to 32, two more [16][bias_stride] fp32
 // tables per wavefront, and the relative-position table must be in LDS
-// shorter: the call has sequences shorter than n (t.ok does not depend on it)
-TilePlan plan_tiles(const bpt_graph* g, const DeviceLimits& lim, bool dense = false, bool shorter = false) {
+// shorter: the call has sequences shorter than n; few: one workgroup per compute unit takes all its tiles (t.ok does not
+// depend on either)
+TilePlan plan_tiles(const bpt_graph* g, const DeviceLimits& lim, bool dense = false, bool shorter = false, bool few = false) {
     TilePlan t;
     if (g->tiles.num_tiles == 0) return t;
     t.cid_pad = dense ? (g->tiles.num_cids + 31) & ~31 : (g->tiles.num_cids + 15) & ~15;
@@ -223,9 +224,12 @@ TilePlan plan_tiles(const bpt_graph* g, const DeviceLimits& lim, bool dense = fa
     //   the same with sequences of 33 - 512  ring 409, out of memory at once 318
     // Packed, H = 8, bidirectional, staged against ring, forward and query-side kernels together: n = 4096, k = 7, 3
     // sequences 87 / 126 us, 16 sequences 371 / 463 us; k = 12, 3 sequences 108 / 190 us; causal, k = 16, 80 / 72 us.
+    // A forward with few tiles has no use for the second workgroup, and finds the table's rows sooner in LDS (staged / ring,
+    // kernel, us: n = 512, k = 24, 8 heads 15.1 / 15.5; n = 2048, k = 16, causal, 8 heads 12.3 / 12.8; with dropout, n = 512, k =
+    // 12, 10 heads 13.8 / 15.2); its query side takes either form in the same time.
     const bool mask_right = shorter && !g->causal;
     const bool staged = t.lds <= room, two = 2 * (t.lds + prefix) <= lim.lds_cu, memory = table + rows <= room;
-    if (!two && g->tiles.ring_ok && !(mask_right && memory)) {
+    if (!two && g->tiles.ring_ok && !(mask_right && memory) && !(few && staged)) {
         t.bias = Bias::kRing;
         t.bias_stride = kRingStride;
         t.lds = (size_t)kTileWaves * 16 * kRingStride * sizeof(float) + rows;
@@ -456,7 +460,8 @@ int run_fwd(const bpt_graph* g, AttnArgs& a, hipStream_t st) {
     int rc = device_limits(g, &lim);
     if (rc) return rc;
     if (sizeof(T) == 2) {
-        const TilePlan tp = plan_tiles(g, lim, false, a.seq_len != nullptr);
+        const bool few = (int64_t)a.BH * g->tiles.num_tiles <= (int64_t)lim.cus * kTileWaves;
+        const TilePlan tp = plan_tiles(g, lim, false, a.seq_len != nullptr, few);
         if (tp.ok) {
             if ((rc = run_fwd_tiles(g, a, lim, tp, st))) return rc;
             if (span_tiles_ok(g)) return run_span_tiles(g, a, true, st);

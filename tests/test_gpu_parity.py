@@ -193,7 +193,9 @@ def test_key_tiles_of_many_ids(n, k, causal):
     (512, 33, False, [512, 400, 17]), (1024, 20, True, [1000, 1024]), (2048, 45, False, None), (2048, 61, False, None), (64, 31, False, [40, 64, 1])])
 def test_bias_table_whole_and_as_a_ring(n, k, causal, lengths):
     # (a wrong row of the table, 16 times the usual size, shifts a score by about its own size)
-    run_token_tiles(n, k, causal, lengths, rel_times=16, query_side=(n, k) != (2048, 61))
+    # (more than 1024 tiles: with fewer the forward stages its table)
+    H = 16384 // (n * (len(lengths) if lengths else 1)) + 1
+    run_token_tiles(n, k, causal, lengths, rel_times=16, query_side=(n, k) != (2048, 61), H=H)
 
 
 # bidirectional sequences that end before n: the nodes past their end are masked as the blocks of ids enter the ring.  n =
@@ -206,13 +208,13 @@ def test_ring_masks_past_the_end_of_a_sequence(n, k, lengths):
     run_token_tiles(n, k, False, lengths, v_times=8)
 
 
-def run_token_tiles(n, k, causal, lengths, p=0.0, v_times=1, rel_times=1, query_side=True):
+def run_token_tiles(n, k, causal, lengths, p=0.0, v_times=1, rel_times=1, query_side=True, H=2):
     """Forward and backward against the oracle with values of span nodes and a table that are larger than usual (powers
     of two: exact in bf16), so that a lost edge or a wrong row of the table shows; the token rows must run on tiles
     (query_side: also in the backward)."""
     say("token tiles", n, k, causal, lengths, p)
     B = len(lengths) if lengths else 1
-    w = Workload("token_tiles", 13, n, k, causal, B, 2, 64, "bf16", True)
+    w = Workload("token_tiles", 13, n, k, causal, B, H, 64, "bf16", True)
     x = make_inputs(w)
     x["V"][:, :, n:] *= np.float32(v_times)
     x["Rel"] = x["Rel"] * np.float32(rel_times)
