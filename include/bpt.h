@@ -53,6 +53,9 @@
  * produce zeros in every output (out, lse, dQ, dK, dV) -- or are left unwritten, see
  * bpt_shape_t.leave_unkept -- and add nothing to d_rel; their input rows are never used but
  * must hold finite values.  Values of seq_len outside [0, n] are clamped.
+ *
+ * Rows are multiplied in tiles of 16, weights of pairs without an edge being zero: a row of Q, K, V or
+ * dout that holds an infinity or a NaN also shows in results of nodes near those it has edges with.
  */
 #ifndef BPT_H_
 #define BPT_H_

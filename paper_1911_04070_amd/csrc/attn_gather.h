@@ -1,5 +1,6 @@
 // Gather kernels (vector ALU): forward, query side and key side of the backward over CSR /
-// transposed adjacency, and the dense d_rel contractions that read the CSR.  fp32 tensors and fallback.
+// transposed adjacency, and the dense d_rel contractions that read the CSR.  Fallback of both families of tile kernels; the
+// span rows' code also runs beside the fp32 token tiles.
 //
 // Work decomposition.  A row of an adjacency (query node u with its key nodes, or
 // key node v with its query nodes) is cut into segments of at most kSeg edges; one
@@ -26,10 +27,11 @@ namespace bpt {
 namespace {
 
 // ---- forward --------------------------------------------------------------------
-// One segment [e0, e1) of row u (e1 > e0).  SPAN: the row is a span node.
+// One segment [e0, e1) of row u (e1 > e0).  SPAN: the row is a span node.  part: where a partial result goes, or null:
+// the segment is the whole row.
 template <typename T, bool REL_LDS, bool SPAN>
 __device__ __forceinline__ void fwd_segment(const AttnArgs& a, const T* rel_s, rsrc_t rK, rsrc_t rV, rsrc_t rIa,
-                                            rsrc_t rIb, int bh, int64_t base, int u, int e0, int e1, int part,
+                                            rsrc_t rIb, int bh, int64_t base, int u, int e0, int e1, float* part,
                                             int lane, int len) {
     const int slot = lane >> 3, sub = lane & 7;
     const int lane_off = first_feature<T>(sub) * (int)sizeof(T);
@@ -115,15 +117,14 @@ __device__ __forceinline__ void fwd_segment(const AttnArgs& a, const T* rel_s, r
     for (int i = 0; i < 8; ++i) acc[i] *= c;
     const float mine = reduce_slots8(acc, lane);
     const int col = feature_of<T>(sub, slot_elem(lane));
-    if (part < 0) {
+    if (!part) {
         store1(static_cast<T*>(a.out) + base + (int64_t)u * a.sn + col, l > 0.f ? mine / l : 0.f);
         if (lane == 0) a.lse_w[(int64_t)bh * a.N + u] = l > 0.f ? (mall + fast_log2(l)) * kLn2 : 0.f;
     } else {
-        float* dst = a.part + ((int64_t)bh * a.num_part + part) * kPartStride;
-        dst[col] = mine;
+        part[col] = mine;
         if (lane == 0) {
-            dst[64] = mall;
-            dst[65] = l;
+            part[64] = mall;
+            part[65] = l;
         }
     }
 }
@@ -208,9 +209,10 @@ __global__ void __launch_bounds__(kThreads) fwd_kernel(const AttnArgs a) {
             const int u = a.seg_row[s];
             const int e0 = a.seg_begin[s];
             const int e1 = min(e0 + kSeg, a.ptr[u + 1]);
-            const int part = a.seg_part[s];
+            const int slot = a.seg_part[s];
             if (e1 <= e0) continue;  // no row of this adjacency is empty
-            if (part == kPartSpan8)
+            float* part = slot < 0 ? nullptr : a.part + ((int64_t)bh * a.num_part + slot) * kPartStride;
+            if (slot == kPartSpan8)
                 fwd_span8<T>(a, rK, rV, bh, base, u, e0, a.ptr[u + 1] - e0, lane, len);
             else if (u >= a.n_tokens)
                 fwd_segment<T, REL_LDS, true>(a, rel_s, rK, rV, rIa, rIb, bh, base, u, e0, e1, part, lane, len);
@@ -250,10 +252,11 @@ __global__ void __launch_bounds__(256) fwd_merge_kernel(const AttnArgs a, const 
 //   A = sum_e w_e (k_e + r_e),  Bv = sum_e p_e (k_e + r_e),
 // so one pass over the row gives delta exactly (in fp32, not through the rounded
 // `out`) and dQ.  For a span row r_anc drops out of dQ because the dS of a row sum to 0.
+// aff (SPAN, or null): (p_e dP_e, p_e) of the row's edge to token t goes to aff[t * aff_row]
 template <typename T, bool REL_LDS, bool SPAN>
 __device__ __forceinline__ void bwd_q_segment(const AttnArgs& a, const T* rel_s, rsrc_t rK, rsrc_t rV, rsrc_t rIa,
-                                              rsrc_t rIb, int bh, int64_t base, int u, int e0, int e1, int part,
-                                              int lane, int len) {
+                                              rsrc_t rIb, int bh, int64_t base, int u, int e0, int e1, float* part,
+                                              int lane, int len, float2* aff = nullptr, int aff_row = 0) {
     const int slot = lane >> 3, sub = lane & 7;
     const int lane_off = first_feature<T>(sub) * (int)sizeof(T);
     const T* relg = static_cast<const T*>(a.rel) + first_feature<T>(sub);
@@ -300,6 +303,7 @@ __device__ __forceinline__ void bwd_q_segment(const AttnArgs& a, const T* rel_s,
         const bool inside = eb + slot < e1;
         const bool valid = inside && row_kept && node_kept(a, cnow, len);
         const float keep = a.drop_thr ? drop_scale(rowh, drop_edge_x(!SPAN, r0, cnow), a.drop_thr, a.drop_inv_keep) : 1.f;
+        const int token = cnow;   // SPAN: the keys are tokens
         cnow = c1;
         float kk[8];
         unpack(kc, kk);
@@ -328,6 +332,7 @@ __device__ __forceinline__ void bwd_q_segment(const AttnArgs& a, const T* rel_s,
         }
         // what d_rel needs of this edge (dS_e = w_e - delta_u p_e once delta_u is known)
         if (!SPAN && inside && sub == 0) a.wp[(int64_t)bh * a.e_tok + (eo >> 2)] = make_float2(wgt, p);
+        if (SPAN && aff && inside && sub == 0) aff[(int64_t)token * aff_row] = make_float2(wgt, p);
         eo += 32;
         c1 = c2;
         r0 = r1;
@@ -341,23 +346,22 @@ __device__ __forceinline__ void bwd_q_segment(const AttnArgs& a, const T* rel_s,
     }
     dl = slots_sum(dl);
     const int col = feature_of<T>(sub, slot_elem(lane));
-    if (part < 0) {
+    if (!part) {
 #pragma unroll
         for (int i = 0; i < 8; ++i) A[i] -= dl * Bv[i];
         store_grad(a.dQ, base + (int64_t)u * a.sn + col, a.scale * reduce_slots8(A, lane), a.grad_bf16);
         if (lane == 0) a.stat[(int64_t)bh * a.N + u] = make_float2(row_kept ? lse2 : kLseGone, dl);
     } else {
-        float* dst = a.part + ((int64_t)bh * a.num_part + part) * kQPartStride;
-        dst[col] = reduce_slots8(A, lane);
-        dst[kD + col] = reduce_slots8(Bv, lane);
-        if (lane == 0) dst[2 * kD] = dl;
+        part[col] = reduce_slots8(A, lane);
+        part[kD + col] = reduce_slots8(Bv, lane);
+        if (lane == 0) part[2 * kD] = dl;
     }
 }
 
 // Query side of eight consecutive short span rows, one row per 8-lane group (see fwd_span8).
 template <typename T>
 __device__ __forceinline__ void bwd_q_span8(const AttnArgs& a, rsrc_t rK, rsrc_t rV, int bh, int64_t base, int u0,
-                                            int e0, int deg, int lane, int len) {
+                                            int e0, int deg, int lane, int len, float2* aff = nullptr, int aff_row = 0) {
     const int slot = lane >> 3, sub = lane & 7;
     const int lane_off = first_feature<T>(sub) * (int)sizeof(T);
     const int u = u0 + slot;
@@ -394,6 +398,7 @@ __device__ __forceinline__ void bwd_q_span8(const AttnArgs& a, rsrc_t rK, rsrc_t
         const float keep = a.drop_thr ? drop_scale(rowh, drop_edge_x(false, 0, tok0 + i), a.drop_thr, a.drop_inv_keep) : 1.f;
         const float wgt = p * sum8(dot8(g, vc, 0.f)) * keep;
         dl += wgt;
+        if (aff && sub == 0) aff[(int64_t)(tok0 + i) * aff_row] = make_float2(wgt, p);
 #pragma unroll
         for (int x = 0; x < 8; ++x) {
             A[x] = fmaf(wgt, kk[x], A[x]);
@@ -438,9 +443,10 @@ __global__ void __launch_bounds__(kThreads) bwd_q_kernel(const AttnArgs a) {
             const int u = a.seg_row[s];
             const int e0 = a.seg_begin[s];
             const int e1 = min(e0 + kSeg, a.ptr[u + 1]);
-            const int part = a.seg_part[s];
+            const int slot = a.seg_part[s];
             if (e1 <= e0) continue;
-            if (part == kPartSpan8)
+            float* part = slot < 0 ? nullptr : a.part + ((int64_t)bh * a.num_part + slot) * kQPartStride;
+            if (slot == kPartSpan8)
                 bwd_q_span8<T>(a, rK, rV, bh, base, u, e0, a.ptr[u + 1] - e0, lane, len);
             else if (u >= a.n_tokens)
                 bwd_q_segment<T, REL_LDS, true>(a, rel_s, rK, rV, rIa, rIb, bh, base, u, e0, e1, part, lane, len);

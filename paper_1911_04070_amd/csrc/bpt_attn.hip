@@ -1,7 +1,7 @@
 // Graph self-attention with tree relative positions (paper Sec. 3.1 eq. (6),
 // Sec. 3.4 eq. (8)) forward and backward for gfx950: the host side.  Chooses per call
-// between the gather kernels (attn_gather.h: fp32 tensors, fallback) and the matrix-core
-// kernels over dense tiles (attn_token_tiles.h, attn_span_tiles.h, attn_key_tiles.h: bf16),
+// between the gather kernels (attn_gather.h: fallback) and the matrix-core kernels over dense
+// tiles (attn_token_tiles.h, attn_span_tiles.h, attn_key_tiles.h: bf16; attn_f32_tiles.h: fp32),
 // lays out the workspace, launches, and exports the C entry points of bpt.h.
 #include <algorithm>
 #include <cmath>
@@ -12,6 +12,7 @@
 #include "attn_token_tiles.h"
 #include "attn_span_tiles.h"
 #include "attn_key_tiles.h"
+#include "attn_f32_tiles.h"
 
 // Scratch of bpt_attn_fwd_static: device memory that belongs to the library's code object, so that the call
 // needs no allocation.  Every device the library is loaded on holds its own copy at its own address; the name
@@ -454,11 +455,117 @@ int run_fwd_tiles(const bpt_graph* g, AttnArgs& a, const DeviceLimits& lim, cons
     }
 }
 
+// rows of the gather schedule that were cut into several segments
 template <typename T>
-int run_fwd(const bpt_graph* g, AttnArgs& a, hipStream_t st) {
+int launch_fwd_merge(const Schedule& sc, const AttnArgs& a, hipStream_t st) {
+    if (sc.num_multi == 0) return BPT_OK;
+    const int items = a.BH * sc.num_multi;
+    BPT_LAUNCH("fwd_merge_kernel", fwd_merge_kernel<T>, dim3((items + 3) / 4), dim3(256), 0, st, a, sc.multi_row, sc.multi_ptr,
+                       sc.num_multi);
+    BPT_HIP(hipGetLastError());
+    return BPT_OK;
+}
+int launch_bwd_q_merge(const Schedule& sc, const AttnArgs& a, hipStream_t st) {
+    if (sc.num_multi == 0) return BPT_OK;
+    const int items = a.BH * sc.num_multi;
+    BPT_LAUNCH("bwd_q_merge_kernel", bwd_q_merge_kernel, dim3((items + 3) / 4), dim3(256), 0, st, a, sc.multi_row,
+                       sc.multi_ptr, sc.num_multi);
+    BPT_HIP(hipGetLastError());
+    return BPT_OK;
+}
+
+// fp32 tensors on the matrix cores (attn_f32_tiles.h): one tree, every sequence of n tokens, no dropout.  They are the faster
+// ones over all sizes (fp32, forward + backward, gather kernels / these, us: n = 64, k = 3, 2 x 2 heads 37.8 / 36.6; n = 256, k =
+// 1, 32 x 4 180 / 112; n = 1024, k = 12, 4 heads 95 / 54; n = 4096, k = 2, one head 121 / 58; n = 4096, k = 16, 8 heads 687 /
+// 301).  The gather kernels keep lengths, dropout and batch graphs, and the backward of graphs with more than kF32MaxIds ids.
+struct F32Plan {
+    bool fwd = false, bwd = false;
+    int cid_pad = 0, bias_stride = 0, wp_row = 0;
+    size_t fwd_lds = 0, bwd_lds = 0;
+    int64_t token_blocks = 0;   // backward: workgroups of token tiles, each of which leaves a copy of d_rel
+};
+constexpr int kF32MaxIds = 384;   // 16-id blocks of d_rel that a wavefront of the query side keeps: at most 24
+F32Plan plan_f32(const bpt_graph* g, const bpt_shape_t* s, const DeviceLimits& lim) {
+    F32Plan p;
+    if (s->dtype != BPT_F32 || g->batch > 0 || g->tiles.num_tiles == 0) return p;
+    p.cid_pad = (g->tiles.num_cids + 15) & ~15;
+    p.bias_stride = p.cid_pad;   // 12, 20, 44 or 52 mod 64: the 16 token rows, read 16 bytes each, and four rows of 16 ids hit different banks
+    while (p.bias_stride % 64 != 12 && p.bias_stride % 64 != 20 && p.bias_stride % 64 != 44 && p.bias_stride % 64 != 52) p.bias_stride += 4;
+    p.wp_row = g->tiles.num_cids + g->num_levels - 1;
+    const size_t table = (size_t)16 * p.bias_stride * sizeof(float), ids = (size_t)p.cid_pad * sizeof(int32_t);
+    const size_t sums = (size_t)kF32Waves * 16 * kF32Stride * sizeof(float);
+    p.fwd_lds = std::max(table + ids, sums + 2 * kF32Waves * 16 * sizeof(float));
+    p.bwd_lds = 2 * table + sums + kF32Waves * 16 * sizeof(float) + ids;
+    const int64_t tiles = (int64_t)s->B * s->H * g->tiles.num_tiles;
+    p.token_blocks = std::min<int64_t>((tiles + 7) / 8 * 8, std::max(8, 2 * lim.cus / 8 * 8));
+    const int64_t blocks = tiles + (int64_t)s->B * s->H * g->fwd_span.num_segs + 32;
+    p.fwd = p.fwd_lds <= lim.lds && blocks < INT32_MAX;
+    p.bwd = p.fwd && p.cid_pad <= kF32MaxIds && p.bwd_lds <= lim.lds && g->ktiles.num_tasks > 0 &&
+            (int64_t)g->n * p.wp_row * 8 < ((int64_t)1 << 31) && (int64_t)s->B * s->H * g->ktiles.num_tasks + 8 < INT32_MAX;
+    return p;
+}
+// whether the plan serves a call
+bool f32_tiles(const AttnArgs& a) { return !a.seq_len && !a.drop_thr; }
+
+F32TileArgs fill_f32_args(const bpt_graph* g, const AttnArgs& a, const F32Plan& p) {
+    F32TileArgs t = {};
+    t.chunk_ptr = g->tiles.chunk_ptr;
+    t.cols = g->tiles.cols;
+    t.cid_to_id = g->tiles.cid_to_id;
+    t.map = g->tiles.map;
+    t.num_tiles = g->tiles.num_tiles;
+    t.num_chunks = g->tiles.num_chunks;
+    t.num_cids = g->tiles.num_cids;
+    t.cid_pad = p.cid_pad;
+    t.bias_stride = p.bias_stride;
+    t.first_long = g->fwd_span.first_long;
+    t.wp = a.wp;
+    t.wp_row = p.wp_row;
+    const int64_t longs = (int64_t)a.BH * (g->fwd_span.num_segs - t.first_long);
+    t.long_blocks = (int32_t)((longs + 7) / 8 * 8);
+    return t;
+}
+// workgroups of the span rows
+unsigned f32_span_grid(const F32TileArgs& t, const AttnArgs& a) {
+    const int64_t shorts = ((int64_t)a.BH * t.first_long + kF32Waves - 1) / kF32Waves;
+    return (unsigned)(t.long_blocks + (shorts + 7) / 8 * 8);
+}
+int run_fwd_f32(const bpt_graph* g, AttnArgs& a, const F32Plan& p, hipStream_t st) {
+    use_schedule(a, g->fwd_span);
+    F32TileArgs t = fill_f32_args(g, a, p);
+    t.token_blocks = (int32_t)(((int64_t)a.BH * t.num_tiles + 7) / 8 * 8);
+    if (p.fwd_lds > 65536)
+        BPT_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(fwd_f32_tile_kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)p.fwd_lds));
+    BPT_LAUNCH("fwd_f32_tile_kernel", fwd_f32_tile_kernel, dim3(t.token_blocks + f32_span_grid(t, a)),
+               dim3(64 * kF32Waves), p.fwd_lds, st, a, t);
+    BPT_HIP(hipGetLastError());
+    return BPT_OK;
+}
+template <int NB>
+int launch_bwd_q_f32(const AttnArgs& a, const F32TileArgs& t, const F32Plan& p, hipStream_t st) {
+    if (p.bwd_lds > 65536)
+        BPT_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(bwd_q_f32_tile_kernel<NB>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)p.bwd_lds));
+    BPT_LAUNCH("bwd_q_f32_tile_kernel", bwd_q_f32_tile_kernel<NB>, dim3(t.token_blocks + f32_span_grid(t, a)),
+               dim3(64 * kF32Waves), p.bwd_lds, st, a, t);
+    BPT_HIP(hipGetLastError());
+    return BPT_OK;
+}
+int run_bwd_q_f32(const bpt_graph* g, AttnArgs& a, const F32Plan& p, hipStream_t st) {
+    F32TileArgs t = fill_f32_args(g, a, p);
+    t.token_blocks = (int32_t)p.token_blocks;
+    return p.cid_pad <= 96 ? launch_bwd_q_f32<6>(a, t, p, st) : p.cid_pad <= 192 ? launch_bwd_q_f32<12>(a, t, p, st) : launch_bwd_q_f32<24>(a, t, p, st);
+}
+
+template <typename T>
+int run_fwd(const bpt_graph* g, const bpt_shape_t* s, AttnArgs& a, hipStream_t st) {
     DeviceLimits lim;
     int rc = device_limits(g, &lim);
     if (rc) return rc;
+    const F32Plan f32 = plan_f32(g, s, lim);
+    if (sizeof(T) == 4 && f32.fwd && f32_tiles(a)) {
+        if ((rc = run_fwd_f32(g, a, f32, st))) return rc;
+        return launch_fwd_merge<T>(g->fwd_span, a, st);
+    }
     if (sizeof(T) == 2) {
         const bool few = (int64_t)a.BH * g->tiles.num_tiles <= (int64_t)lim.cus * kTileWaves;
         const TilePlan tp = plan_tiles(g, lim, false, a.seq_len != nullptr, few);
@@ -482,14 +589,7 @@ int run_fwd(const bpt_graph* g, AttnArgs& a, hipStream_t st) {
         rc = launch("fwd_kernel", fwd_kernel<T, false>, grid, kThreads, 0, st, a);
     }
     if (rc) return rc;
-    const Schedule& sc = a.seg_row == g->fwd_span.seg_row ? g->fwd_span : g->fwd;
-    if (sc.num_multi > 0) {
-        const int items = a.BH * sc.num_multi;
-        BPT_LAUNCH("fwd_merge_kernel", fwd_merge_kernel<T>, dim3((items + 3) / 4), dim3(256), 0, st, a, sc.multi_row, sc.multi_ptr,
-                           sc.num_multi);
-        BPT_HIP(hipGetLastError());
-    }
-    return BPT_OK;
+    return launch_fwd_merge<T>(a.seg_row == g->fwd_span.seg_row ? g->fwd_span : g->fwd, a, st);
 }
 
 // Workspace layout of the backward and the launch shape of rel_grad_kernel.
@@ -503,6 +603,8 @@ struct BwdPlan {
     bool dense_ds = false;    // ... which also forms d_rel (one copy per wavefront): no (w, p) pairs, no d_rel kernel
     bool kv_tiles = false;    // key side on dense tiles of key nodes (bwd_kv_tile_kernel)
     bool kv_chain = false;    // ... with at most 32 ids per tile: bwd_kv_chain_kernel (tasks that walk several tiles)
+    F32Plan f32_plan;
+    bool f32 = false;         // fp32 tensors: both sides on the matrix cores (attn_f32_tiles.h)
     size_t kv_lds = 0;
     int drel_ipw = 32;        // ids per wavefront: 8, 16 or 32
     int drel_block = 32;      // token rows per block
@@ -551,6 +653,16 @@ int plan_bwd(const bpt_graph* g, const bpt_shape_t* s, BwdPlan* p) {
     const int per_cu = (int)std::max<size_t>(1, std::min<size_t>(4, lim.lds_cu / p->drel_lds));
     p->drel_grid_x = (int)std::max<int64_t>(1, std::min<int64_t>(blocks, (int64_t)lim.cus * per_cu / p->drel_grid_y));
     if (p->dense_ds) p->drel_grid_x = dense_grid(lim);   // copies of d_rel: one per workgroup of bwd_q_tile_kernel
+    // (a workspace serves calls with and without lengths and dropout: sized for either path)
+    p->f32_plan = plan_f32(g, s, lim);
+    const F32Plan& f = p->f32_plan;
+    if (!p->drel_tile) p->drel_part_rows = p->drel_rows;
+    const size_t drel_rows = std::max((size_t)p->drel_grid_x * p->drel_part_rows, f.bwd ? (size_t)f.token_blocks * f.cid_pad : 0);
+    p->f32 = f.bwd && !s->seq_len && !(s->dropout_p > 0.f);
+    if (p->f32) {
+        p->drel_grid_x = (int)f.token_blocks;
+        p->drel_part_rows = f.cid_pad;
+    }
     const size_t bh = (size_t)s->B * s->H;
     size_t off = 0;
     p->off_stat = off;
@@ -559,7 +671,8 @@ int plan_bwd(const bpt_graph* g, const bpt_shape_t* s, BwdPlan* p) {
     // (w, p) pairs: per edge of a token row in CSR order, or per slot of the token tiles
     // (none with dense_ds)
     off += align_up(p->dense_ds ? 0
-                                : bh * (p->q_tiles ? (size_t)g->tiles.num_chunks * 256 : (size_t)g->num_token_edges) * sizeof(float2));
+                                : bh * (p->q_tiles ? (size_t)g->tiles.num_chunks * 256
+                                                   : std::max((size_t)g->num_token_edges, f.bwd ? (size_t)g->n * f.wp_row : 0)) * sizeof(float2));
     p->off_qpart = off;
     off += align_up(bh * std::max<size_t>(std::max(g->fwd.num_part, g->fwd_span.num_part), span_partials(g)) *
                     kQPartStride * sizeof(float));
@@ -567,11 +680,10 @@ int plan_bwd(const bpt_graph* g, const bpt_shape_t* s, BwdPlan* p) {
     // gradients rounded to bf16: dQ of the token rows stays fp32 until rel_grad_tile_kernel has added to it, where the key
     // side, which runs behind it, keeps its partial sums (sized for either type of gradients: one workspace serves both)
     p->off_dq32 = off;
-    off += align_up(std::max(bh * std::max<size_t>(g->tr.num_part, p->kv_tiles ? (size_t)g->ktiles.num_part * 16 : 0) * 2 * kD,
+    off += align_up(std::max(bh * std::max<size_t>(g->tr.num_part, p->kv_tiles || f.bwd ? (size_t)g->ktiles.num_part * 16 : 0) * 2 * kD,
                              p->drel_tile && !p->dense_ds ? bh * g->tiles.num_tiles * 16 * kD : 0) * sizeof(float));
     p->off_drel = off;
-    if (!p->drel_tile) p->drel_part_rows = p->drel_rows;
-    off += align_up((size_t)p->drel_grid_x * p->drel_part_rows * kD * sizeof(float));
+    off += align_up(drel_rows * kD * sizeof(float));
     p->off_queue = off;
     off += align_up(kQueueInts * sizeof(int32_t));   // task counters of the key-tile kernel
     p->total = off;
@@ -612,7 +724,11 @@ int run_bwd_q(const bpt_graph* g, const BwdPlan& p, AttnArgs& a, hipStream_t st)
         sc = &g->fwd_span;
     }
     int grid = 8;
-    if (p.q_tiles && span_tiles_ok(g)) {
+    if (p.f32) {
+        use_schedule(a, g->fwd_span);
+        sc = &g->fwd_span;
+        rc = run_bwd_q_f32(g, a, p.f32_plan, st);
+    } else if (p.q_tiles && span_tiles_ok(g)) {
         if ((rc = run_span_tiles(g, a, false, st))) return rc;
         sc = nullptr;
     } else if (rel_lds) {
@@ -623,13 +739,10 @@ int run_bwd_q(const bpt_graph* g, const BwdPlan& p, AttnArgs& a, hipStream_t st)
         rc = launch("bwd_q_kernel", bwd_q_kernel<T, false>, grid, kThreads, 0, st, a);
     }
     if (rc) return rc;
-    if (sc && sc->num_multi > 0) {
-        const int items = a.BH * sc->num_multi;
-        BPT_LAUNCH("bwd_q_merge_kernel", bwd_q_merge_kernel, dim3((items + 3) / 4), dim3(256), 0, st, a, sc->multi_row,
-                           sc->multi_ptr, sc->num_multi);
-        BPT_HIP(hipGetLastError());
-    }
-    if (p.drel_tile) {
+    if (sc && (rc = launch_bwd_q_merge(*sc, a, st))) return rc;
+    if (p.f32) {
+        // bwd_q_f32_tile_kernel has left the copies of d_rel
+    } else if (p.drel_tile) {
         RelGradArgs t = {};
         t.Q = static_cast<const bf16_t*>(a.Q);
         t.rel = static_cast<const bf16_t*>(a.rel);
@@ -695,7 +808,7 @@ int run_bwd_q(const bpt_graph* g, const BwdPlan& p, AttnArgs& a, hipStream_t st)
     }
     if (rc) return rc;
     BPT_LAUNCH("drel_reduce_kernel", drel_reduce_kernel, dim3(a.rel_rows), dim3(1024), 0, st, a.drel_part, p.drel_grid_x,
-               p.drel_part_rows, p.drel_tile ? g->tiles.id_to_cid : nullptr, a.d_rel, a.queue, kQueueInts);
+               p.drel_part_rows, p.drel_tile || p.f32 ? g->tiles.id_to_cid : nullptr, a.d_rel, a.queue, kQueueInts);
     BPT_HIP(hipGetLastError());
     return BPT_OK;
 }
@@ -744,10 +857,7 @@ int launch_kv_chain(const KeyArgs& t, const BwdPlan& p, const DeviceLimits& lim,
     return t.drop_thr ? launch_kv_chain_as<NBC, true, false>(t, p, lim, st) : launch_kv_chain_as<NBC, false, false>(t, p, lim, st);
 }
 
-// bf16 key side on dense tiles of key nodes
-// queue_cleared: the query side ran in the same call and its last kernel has put the task counters to zero
-int run_bwd_kv_tiles(const bpt_graph* g, const BwdPlan& p, const AttnArgs& a, const DeviceLimits& lim, bool queue_cleared,
-                     hipStream_t st) {
+KeyArgs fill_key_args(const bpt_graph* g, const AttnArgs& a) {
     const KeyTiles& kt = g->ktiles;
     KeyArgs t = {};
     t.Q = static_cast<const bf16_t*>(a.Q);
@@ -795,20 +905,10 @@ int run_bwd_kv_tiles(const bpt_graph* g, const BwdPlan& p, const AttnArgs& a, co
     t.drop_seed = a.drop_seed;
     t.drop_inv_keep = a.drop_inv_keep;
     t.queue = a.queue;
-    if ((int64_t)a.BH * kt.num_tasks > INT32_MAX) return BPT_ERR_UNSUPPORTED;
-    if (!queue_cleared) {
-        BPT_LAUNCH("zero_ints_kernel", zero_ints_kernel, dim3(1), dim3(kQueueInts), 0, st, t.queue, kQueueInts);
-        BPT_HIP(hipGetLastError());
-    }
-    int rc = BPT_ERR_UNSUPPORTED;
-    switch (kt.nb_pad / 16) {
-        case 1: rc = launch_kv_chain<1>(t, p, lim, st); break;   // (p.kv_chain)
-        case 2: rc = launch_kv_chain<2>(t, p, lim, st); break;
-        case 3: rc = launch_kv_tiles<3>(t, p, lim, st); break;
-        case 4: rc = launch_kv_tiles<4>(t, p, lim, st); break;
-        default: rc = launch_kv_tiles<0>(t, p, lim, st); break;   // (at most kMaxBiasChunks, plan_bwd)
-    }
-    if (rc) return rc;
+    return t;
+}
+int launch_kv_merge(const bpt_graph* g, const AttnArgs& a, const KeyArgs& t, hipStream_t st) {
+    const KeyTiles& kt = g->ktiles;
     // threads of the zero pass of kv_tile_merge_kernel: one per node it has to look at, in wavefronts of 64 nodes
     const int zero_row0 = a.seq_len && !a.leave_unkept ? 0 : (kt.first_uncovered & ~63);
     const int64_t zero_elems = (int64_t)a.BH * ((a.N - zero_row0 + 63) / 64) * 64;
@@ -825,11 +925,65 @@ int run_bwd_kv_tiles(const bpt_graph* g, const BwdPlan& p, const AttnArgs& a, co
     return BPT_OK;
 }
 
+// bf16 key side on dense tiles of key nodes
+// queue_cleared: the query side ran in the same call and its last kernel has put the task counters to zero
+int run_bwd_kv_tiles(const bpt_graph* g, const BwdPlan& p, const AttnArgs& a, const DeviceLimits& lim, bool queue_cleared,
+                     hipStream_t st) {
+    const KeyTiles& kt = g->ktiles;
+    const KeyArgs t = fill_key_args(g, a);
+    if ((int64_t)a.BH * kt.num_tasks > INT32_MAX) return BPT_ERR_UNSUPPORTED;
+    if (!queue_cleared) {
+        BPT_LAUNCH("zero_ints_kernel", zero_ints_kernel, dim3(1), dim3(kQueueInts), 0, st, t.queue, kQueueInts);
+        BPT_HIP(hipGetLastError());
+    }
+    int rc = BPT_ERR_UNSUPPORTED;
+    switch (kt.nb_pad / 16) {
+        case 1: rc = launch_kv_chain<1>(t, p, lim, st); break;   // (p.kv_chain)
+        case 2: rc = launch_kv_chain<2>(t, p, lim, st); break;
+        case 3: rc = launch_kv_tiles<3>(t, p, lim, st); break;
+        case 4: rc = launch_kv_tiles<4>(t, p, lim, st); break;
+        default: rc = launch_kv_tiles<0>(t, p, lim, st); break;   // (at most kMaxBiasChunks, plan_bwd)
+    }
+    if (rc) return rc;
+    return launch_kv_merge(g, a, t, st);
+}
+
+// fp32 key side: needs the (w, p) pairs that bwd_q_f32_tile_kernel has left in the workspace
+int run_bwd_kv_f32(const bpt_graph* g, const F32Plan& p, const AttnArgs& a, hipStream_t st) {
+    const KeyTiles& kt = g->ktiles;
+    F32KeyArgs t = {};
+    t.tile_node0 = kt.tile_node0;
+    t.tile_info = kt.tile_info;
+    t.chunk_ptr = kt.chunk_ptr;
+    t.cols = kt.cols;
+    t.task_tile = kt.task_tile;
+    t.task_c0 = kt.task_c0;
+    t.task_nch = kt.task_nch;
+    t.task_part = kt.task_part;
+    t.task_ntiles = kt.task_ntiles;
+    t.map = kt.map;
+    t.id_to_cid = g->tiles.id_to_cid;
+    t.num_tasks = kt.num_tasks;
+    t.num_part = kt.num_part;
+    t.num_chunks = kt.num_chunks;
+    t.W = g->rel_width;
+    t.ctx_levels = g->ctx_levels;
+    t.wp = a.wp;
+    t.wp_row = p.wp_row;
+    t.num_cids = g->tiles.num_cids;
+    const int64_t tasks = (int64_t)a.BH * kt.num_tasks;
+    BPT_LAUNCH("bwd_kv_f32_tile_kernel", bwd_kv_f32_tile_kernel, dim3((unsigned)((tasks + 7) / 8 * 8)), dim3(64 * kF32Waves),
+               (size_t)t.W * sizeof(int32_t), st, a, t);
+    BPT_HIP(hipGetLastError());
+    return launch_kv_merge(g, a, fill_key_args(g, a), st);
+}
+
 template <typename T>
 int run_bwd_kv(const bpt_graph* g, const BwdPlan& p, AttnArgs& a, bool queue_cleared, hipStream_t st) {
     DeviceLimits lim;
     int rc = device_limits(g, &lim);
     if (rc) return rc;
+    if (p.f32) return run_bwd_kv_f32(g, p.f32_plan, a, st);
     if (p.kv_tiles) return run_bwd_kv_tiles(g, p, a, lim, queue_cleared, st);
     a.ptr = g->t_ptr;
     a.ia = g->t_src;
@@ -1008,7 +1162,7 @@ int bpt_attn_fwd(const bpt_graph_t* g, const bpt_shape_t* s, const void* Q, cons
     a.ib = g->rel;
     bpt::use_schedule(a, g->fwd);
     hipStream_t st = static_cast<hipStream_t>(stream);
-    return s->dtype == BPT_BF16 ? bpt::run_fwd<bpt::bf16_t>(g, a, st) : bpt::run_fwd<float>(g, a, st);
+    return s->dtype == BPT_BF16 ? bpt::run_fwd<bpt::bf16_t>(g, s, a, st) : bpt::run_fwd<float>(g, s, a, st);
 }
 
 int bpt_attn_fwd_static(const bpt_graph_t* g, const bpt_shape_t* s, const void* Q, const void* K, const void* V,

@@ -639,10 +639,12 @@ int upload(const std::vector<T>& h, T** d) {
 // Cut rows into segments of at most kSeg edges and group consecutive segments
 // into tiles of about kTileWork work units.  Rows without edges still get one
 // (empty) segment so that their outputs are written.
-// Rows from `span_from` on are span rows: 8 consecutive ones of equal degree <= kSpan8MaxDeg, a power of two (a
+// Rows from `span_from` on are span rows: 8 consecutive ones of equal degree <= span8_deg, a power of two (a
 // span of a batch graph that a sequence's end cuts short has any degree), become one segment marked kPartSpan8
-// (pass the row count to disable).
-int make_schedule(const std::vector<int32_t>& ptr, int32_t first_row, int32_t span_from, Schedule& out) {
+// (pass the row count to disable).  Such a segment is a chain of `degree` dependent steps: the schedule of the span rows
+// alone, which run beside the fp32 token tiles, takes only the shortest that way (n = 512, k = 4, one head, fp32 forward: up
+// to 64 edges 13.8 us, up to 8 edges 7.6 us; n = 2048, 16 heads, query side 85 and 78 us).
+int make_schedule(const std::vector<int32_t>& ptr, int32_t first_row, int32_t span_from, int32_t span8_deg, Schedule& out) {
     const int32_t rows = (int32_t)ptr.size() - 1;
     std::vector<int32_t> seg_row, seg_begin, seg_part, tile_ptr, multi_row, multi_ptr;
     seg_row.reserve(rows + rows / 8);
@@ -654,7 +656,7 @@ int make_schedule(const std::vector<int32_t>& ptr, int32_t first_row, int32_t sp
     int32_t parts = 0;
     for (int32_t u = first_row; u < rows; ++u) {
         const int32_t b = ptr[u], deg = ptr[u + 1] - b;
-        if (u >= span_from && u + 8 <= rows && deg >= 2 && deg <= kSpan8MaxDeg && (deg & (deg - 1)) == 0 &&
+        if (u >= span_from && u + 8 <= rows && deg >= 2 && deg <= span8_deg && (deg & (deg - 1)) == 0 &&
             ptr[u + 8] - b == 8 * deg) {
             bool same = true;
             for (int32_t x = 1; x < 8; ++x) same = same && ptr[u + x + 1] - ptr[u + x] == deg;
@@ -662,6 +664,7 @@ int make_schedule(const std::vector<int32_t>& ptr, int32_t first_row, int32_t sp
                 seg_row.push_back(u);
                 seg_begin.push_back(b);
                 seg_part.push_back(kPartSpan8);
+                out.first_long = (int32_t)seg_row.size();
                 work += 8 * deg + kRowCost;
                 if (work >= kTileWork) {
                     tile_ptr.push_back((int32_t)seg_row.size());
@@ -672,6 +675,7 @@ int make_schedule(const std::vector<int32_t>& ptr, int32_t first_row, int32_t sp
             }
         }
         const int32_t nseg = deg <= kSeg ? 1 : (deg + kSeg - 1) / kSeg;
+        if (deg <= kSpan8MaxDeg) out.first_long = (int32_t)seg_row.size() + 1;
         for (int32_t s = 0; s < nseg; ++s) {
             const int32_t len = std::min<int32_t>(kSeg, deg - s * kSeg);
             seg_row.push_back(u);
@@ -818,12 +822,12 @@ int build(int32_t n, int32_t k, int32_t causal, hipStream_t st, bpt_graph* g) {
     BPT_HIP(hipMemcpyAsync(h_ptr.data(), g->row_ptr, sizeof(int32_t) * h_ptr.size(), hipMemcpyDeviceToHost, st));
     BPT_HIP(hipMemcpyAsync(h_tptr.data(), g->t_ptr, sizeof(int32_t) * h_tptr.size(), hipMemcpyDeviceToHost, st));
     BPT_HIP(hipStreamSynchronize(st));
-    if ((rc = make_schedule(h_ptr, 0, n, g->fwd))) return rc;
-    if ((rc = make_schedule(h_tptr, 0, num_nodes, g->tr))) return rc;
+    if ((rc = make_schedule(h_ptr, 0, n, kSpan8MaxDeg, g->fwd))) return rc;
+    if ((rc = make_schedule(h_tptr, 0, num_nodes, kSpan8MaxDeg, g->tr))) return rc;
     // 6. dense tiles for the matrix-core kernels (GPU, from the CSR on the device)
     if ((rc = build_tile_metadata(g, cnt_l.as<int32_t>(), min_l.as<int32_t>(), cnt_r.as<int32_t>(), min_r.as<int32_t>(), st)))
         return rc;
-    if (g->tiles.num_tiles > 0 && (rc = make_schedule(h_ptr, n, n, g->fwd_span))) return rc;
+    if (g->tiles.num_tiles > 0 && (rc = make_schedule(h_ptr, n, n, 8, g->fwd_span))) return rc;
     return BPT_OK;
 }
 
@@ -996,8 +1000,8 @@ int build_batch(int32_t n, int32_t k, int32_t causal, const int32_t* lengths, in
     BPT_HIP(hipMemcpyAsync(h_ptr.data(), g->row_ptr, sizeof(int32_t) * h_ptr.size(), hipMemcpyDeviceToHost, st));
     BPT_HIP(hipMemcpyAsync(h_tptr.data(), g->t_ptr, sizeof(int32_t) * h_tptr.size(), hipMemcpyDeviceToHost, st));
     BPT_HIP(hipStreamSynchronize(st));
-    if ((rc = make_schedule(h_ptr, 0, T, g->fwd))) return rc;
-    return make_schedule(h_tptr, 0, num_nodes, g->tr);
+    if ((rc = make_schedule(h_ptr, 0, T, kSpan8MaxDeg, g->fwd))) return rc;
+    return make_schedule(h_tptr, 0, num_nodes, kSpan8MaxDeg, g->tr);
 }
 
 }  // namespace

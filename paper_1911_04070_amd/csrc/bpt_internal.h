@@ -24,6 +24,7 @@ constexpr int kPartStride = 66;   // forward partial: 64 accumulators, running m
 // a merge kernel combines.  Segments are grouped into tiles of about equal work.
 struct Schedule {
     int32_t num_segs = 0, num_tiles = 0, num_multi = 0, num_part = 0;
+    int32_t first_long = 0;        // span rows only: segments from here on are (parts of) rows of more than kSpan8MaxDeg edges
     int32_t* seg_row = nullptr;    // [num_segs]   row (node id) of the segment
     int32_t* seg_begin = nullptr;  // [num_segs]   first edge of the segment
     int32_t* seg_part = nullptr;   // [num_segs]   partial slot, -1 if the row has one segment, kPartSpan8 for a row group
