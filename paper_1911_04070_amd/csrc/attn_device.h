@@ -173,15 +173,12 @@ __device__ __forceinline__ float sum8(float x) {
 }
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 // exp2(x), or 0 where the edge does not exist.  The mask goes into the argument: written as `on ? exp2(x) : 0` every
-// element becomes a branch of its own around the exponential, and the loads that feed the elements (the bias lookups
-// of a tile) are then waited for one after the other instead of once.  It is used where it wins (kernel times, branch /
-// mask, us): chained key tiles without dropout (n = 512, k = 4, 32 x 8 heads 94.3 / 93.0; n = 8192, k = 8 181.8 / 180.7;
-// n = 65536, k = 4 389 / 387), the other key tiles (k = 12 77.2 / 76.5; k = 16 301 / 300), token tiles forward without
-// dropout (n = 8192, k = 8 61.3 / 60.3; n = 512, k = 4, 32 x 8 29.4 / 28.9) or with their bias out of memory (k = 12 38.5 /
-// 37.9; k = 16 171.5 / 170.3; k = 64 210 / 209), the query side with its bias out of memory (k = 16 255.9 / 254.7).  With
-// dropout the branch is the better form of the staged token tiles and the chained key tiles (n = 512, k = 4, 32 x 8: 32.2 /
-// 32.7 and 106.7 / 111); on the staged query side and the span tiles the two forms are within 1 % of each other, and the
-// span tiles' branch is the faster one at n = 512, k = 4, 32 x 8 (22.7 / 23.3).
+// element becomes a branch of its own around the exponential, and the loads that feed the elements are then waited for
+// one after the other instead of once.  It is used where it wins (kernel times, branch / mask, us): chained key tiles without
+// dropout (n = 512, k = 4, 32 x 8 heads 94.3 / 93.0; n = 8192, k = 8 181.8 / 180.7; n = 65536, k = 4 389 / 387), the other key
+// tiles (k = 12 77.2 / 76.5; k = 16 301 / 300).  With dropout the branch is the better form of the chained key tiles (n = 512,
+// k = 4, 32 x 8: 106.7 / 111); on the span tiles the two forms are within 1 % of each other, and the branch is the faster one at
+// n = 512, k = 4, 32 x 8 (22.7 / 23.3).
 __device__ __forceinline__ float masked_exp2(bool on, float x) { return fast_exp2(on ? x : kNegBig); }
 __device__ __forceinline__ float fast_log2(float x) { return __builtin_amdgcn_logf(x); }
 

@@ -593,6 +593,19 @@ def test_large_table_on_every_kernel_variant(n, k, causal, B, H, q_times, rel_st
     g.destroy()
 
 
+@pytest.mark.parametrize("n,k,causal,step", [(512, 4, False, 1.0), (512, 4, False, 5.0), (2048, 16, True, 1.0), (1024, 24, False, 5.0),
+                                             (512, 8, False, -1.0), (512, 80, False, 1.0)])
+def test_scores_that_rise_along_a_row(n, k, causal, step):
+    # the forward moves the reference of its softmax only when a score passes it by more than 2^8: scores that rise (or
+    # fall) by step / ln 2 powers of two per level of the key, on tables in LDS, as a ring and in memory
+    w = Workload("rising", 15, n, k, causal, 1, 3, 64, "bf16", False)
+    x = make_inputs(w)
+    level = np.maximum(n.bit_length() - 1 - np.floor(np.log2(2 * n - 1 - np.arange(2 * n - 1))).astype(int), 0)
+    x["Q"][..., 0] = 8.0                              # score = (8 * step * level + the other features) / 8
+    x["K"][..., 0] = step * level
+    run_case(w, x, scaled=True)
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_zero_queries_and_zero_values(dtype):
     # degenerate rows: q = 0 makes every row uniform over its neighbours (lse = ln deg, dK = d_rel = 0);
