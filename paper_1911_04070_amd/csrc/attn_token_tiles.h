@@ -135,8 +135,6 @@ __device__ __forceinline__ s16x4_t lds_tr4(const bf16_t* base, int stride, int r
 // token j of the tile; the four lane groups share the ids.
 // c0, c1: the ids to look at (the others are not in the table yet, or no longer): in a ring at most as many as it holds.
 constexpr float kMaskBias = -1.0e30f;
-constexpr float kSoftmaxSlack = 8.f;        // forward: how far (in powers of 2) a score may pass the reference of its row
-constexpr float kSoftmaxFloor = -1.0e28f;   // ... and where the reference starts: below every score, above every mask
 enum class Bias { kStaged, kRing, kMemory };   // (see ring_form)
 constexpr int kRingIds = 16 * kRingBlocks;
 constexpr int kRingStride = kRingIds + 4;   // = 4 mod 32: the 16 token rows hit different banks
@@ -146,10 +144,9 @@ __device__ __forceinline__ int bias_slot(int cid) {   // where a token's row of 
 }
 // The column of a token's row of the table that a map word (16 bits: a compact id, or 0xFFFF where there is no edge) reads: the
 // words without an edge read the column behind the ids, which holds kMaskBias, so that nothing behind the lookup asks
-// whether there is an edge -- the weight of such a slot comes out as exactly 0 by itself.  Together with the softmax reference
-// that seldom moves, descriptors formed once per tile, ids requested without a branch and the table formed two blocks at
-// a time: 225 -> 160 vector instructions per pair in the forward (n = 8192, k = 8, causal, 32 (batch, head)s: 64.0 -> 58.4
-// us), and the query side 137 -> 128 us.
+// whether there is an edge -- the weight of such a slot comes out as exactly 0 by itself.  Together with descriptors
+// formed once per tile, ids requested without a branch and the table formed two blocks at a time (n = 8192, k = 8, causal, 32
+// (batch, head)s, us): forward 64.0 -> 61.1, query side 137 -> 128.
 template <Bias BIAS>
 __device__ __forceinline__ int mask_column(int cid_pad) { return BIAS == Bias::kRing ? kRingIds : cid_pad; }
 template <Bias BIAS>
@@ -488,8 +485,7 @@ __global__ void __launch_bounds__(kTileThreads, 2) fwd_tile_kernel(const TileArg
     advance(ci);
 
     bf16x8_t qb0, qb1;
-    float m_run = kSoftmaxFloor, l_part = 0.f;
-    const float slack = kSoftmaxSlack / qscale;
+    float m_run = kNegBig, l_part = 0.f;
     f32x4_t o[4];
     uint32_t rowh = 0;   // DROP: hash of (seed, batch*head, token j of the tile)
 
@@ -503,7 +499,7 @@ __global__ void __launch_bounds__(kTileThreads, 2) fwd_tile_kernel(const TileArg
             if (DROP) rowh = drop_row_hash(drop_bh_hash(a.drop_seed, cc.bh), cc.tile * 16 + j);
             qb0 = qn0;
             qb1 = qn1;
-            m_run = kSoftmaxFloor;
+            m_run = kNegBig;
             l_part = 0.f;
 #pragma unroll
             for (int f = 0; f < 4; ++f) o[f] = f32x4_t{0.f, 0.f, 0.f, 0.f};
@@ -558,39 +554,35 @@ __global__ void __launch_bounds__(kTileThreads, 2) fwd_tile_kernel(const TileArg
             s4[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(*reinterpret_cast<const bf16x8_t*>(krow), qb0, s4[c], 0, 0, 0);
             s4[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(*reinterpret_cast<const bf16x8_t*>(krow + 8), qb1, s4[c], 0, 0, 0);
         }
-        // Online softmax over the pair's 32 columns.  The reference that the exponentials are taken against moves only when
-        // a score passes it by more than kSoftmaxSlack: until then weights above 1 (up to 2^8) do no harm, and neither the
-        // maximum across the lane groups (two dependent cross-lane reads) nor the rescaling of the sums is needed.
+        // online softmax over the pair's 32 columns
         float sc[2][4], gm = kNegBig;
 #pragma unroll
         for (int c = 0; c < 2; ++c)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                sc[c][r] = s4[c][r] + bv[c][r];
+                sc[c][r] = (s4[c][r] + bv[c][r]) * qscale;
                 gm = fmaxf(gm, sc[c][r]);
             }
-        if (__any(gm > m_run + slack)) {
-            gm = fmaxf(gm, __shfl_xor(gm, 16));
-            gm = fmaxf(gm, __shfl_xor(gm, 32));
-            const float mn = fmaxf(m_run, gm), corr = fast_exp2((m_run - mn) * qscale);
-            m_run = mn;
-            l_part *= corr;
-            // the accumulators hold out^T, C[m = feature][n = token]: all four values of a lane belong to its token j
-#pragma unroll
-            for (int f = 0; f < 4; ++f)
-#pragma unroll
-                for (int r = 0; r < 4; ++r) o[f][r] *= corr;
-        }
-        const float mq = m_run * qscale;
+        gm = fmaxf(gm, __shfl_xor(gm, 16));
+        gm = fmaxf(gm, __shfl_xor(gm, 32));
+        const float mn = fmaxf(m_run, gm);
+        const float corr = fast_exp2(m_run - mn);
+        m_run = mn;
         float psum = 0.f;
 #pragma unroll
         for (int c = 0; c < 2; ++c)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                sc[c][r] = fast_exp2(fmaf(sc[c][r], qscale, -mq));
+                asm("" : "+v"(sc[c][r]));   // (the scaled score that the maximum was taken of, not a fused multiply-add of the unscaled one)
+                sc[c][r] = fast_exp2(sc[c][r] - mn);
                 psum += sc[c][r];
             }
-        l_part += psum;
+        l_part = l_part * corr + psum;
+        // the accumulators hold out^T, C[m = feature][n = token]: all four values of a lane belong to its token j
+#pragma unroll
+        for (int f = 0; f < 4; ++f)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) o[f][r] *= corr;
         if (DROP) {   // dropout acts on the weighted sum of values only: the row sum keeps every edge
 #pragma unroll
             for (int c = 0; c < 2; ++c)
@@ -621,7 +613,7 @@ __global__ void __launch_bounds__(kTileThreads, 2) fwd_tile_kernel(const TileArg
             const int row0 = PACKED ? t0 + level_delta(cc.dvec, 0) : t0;
             constexpr bool guard = PACKED;
             const int64_t lse_at = PACKED ? (int64_t)(cc.bh / a.H) * a.lse_sb + (int64_t)(cc.bh % a.H) * a.lse_sh : (int64_t)cc.bh * a.N;
-            if (g == 0 && !(guard && t0 + j >= len)) a.lse[lse_at + row0 + j] = t0 + j < len ? (m_run * qscale + fast_log2(l)) * kLn2 : 0.f;
+            if (g == 0 && !(guard && t0 + j >= len)) a.lse[lse_at + row0 + j] = t0 + j < len ? (m_run + fast_log2(l)) * kLn2 : 0.f;
             // out^T = V^T P^T (the operands of P V changed places: the same registers): lane (g, j) holds features
             // 16f + 4g .. + 3 of token j.  The rows go through k_s (this pair's products have read it; the next
             // pair's rows are written behind the barrier at the top of the loop) and leave as whole rows, 16 bytes

@@ -596,8 +596,8 @@ def test_large_table_on_every_kernel_variant(n, k, causal, B, H, q_times, rel_st
 @pytest.mark.parametrize("n,k,causal,step", [(512, 4, False, 1.0), (512, 4, False, 5.0), (2048, 16, True, 1.0), (1024, 24, False, 5.0),
                                              (512, 8, False, -1.0), (512, 80, False, 1.0)])
 def test_scores_that_rise_along_a_row(n, k, causal, step):
-    # the forward moves the reference of its softmax only when a score passes it by more than 2^8: scores that rise (or
-    # fall) by step / ln 2 powers of two per level of the key, on tables in LDS, as a ring and in memory
+    # the reference of a row's softmax moves with (or stays through) every pair of chunks: scores that rise (or fall) by
+    # step / ln 2 powers of two per level of the key, on tables in LDS, as a ring and in memory
     w = Workload("rising", 15, n, k, causal, 1, 3, 64, "bf16", False)
     x = make_inputs(w)
     level = np.maximum(n.bit_length() - 1 - np.floor(np.log2(2 * n - 1 - np.arange(2 * n - 1))).astype(int), 0)
