@@ -141,7 +141,9 @@ int bpt_build_batch_graph(int32_t n, int32_t k, int32_t causal, const int32_t* l
  * building its own (the caller keeps `tree` alive until the new graph is destroyed; both on the
  * current device), and, with with_edges == 0, without the batch's own CSR, transposed adjacency and
  * gather schedules: only the row layout and the small tables the matrix-core kernels need are made
- * (host arithmetic and four small copies).  Such a graph serves every call that runs on the
+ * (host arithmetic and one small copy, waiting for neither `stream` nor the device: the tables lie in
+ * a few blocks that `tree` keeps and that bpt_graph_destroy, which does not wait for the device
+ * either, gives back to it; a block is used again when the calls that read it are through).  Such a graph serves every call that runs on the
  * matrix-core kernels (see above; also the layer and stack calls); the graph accessors and calls
  * that would need the gather kernels return BPT_ERR_UNSUPPORTED (workspace queries SIZE_MAX), and
  * bpt_graph_info reports 0 edges. */

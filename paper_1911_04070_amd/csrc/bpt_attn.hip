@@ -1059,6 +1059,7 @@ int backward(const bpt_graph_t* g, const bpt_shape_t* s, const void* Q, const vo
     if (misaligned(Q) || misaligned(K) || misaligned(V) || misaligned(rel) || misaligned(dout) || misaligned(dQ) ||
         misaligned(dK) || misaligned(dV) || misaligned(d_rel) || misaligned(workspace))
         return BPT_ERR_INVALID_ARG;
+    const UseOnReturn use = {g, static_cast<hipStream_t>(stream)};
     // a batch graph on the matrix-core kernels: from here on g and s are the tree of one sequence and the view of
     // the packed tensors as one batch entry per sequence
     bpt_shape_t view;
@@ -1141,6 +1142,7 @@ int bpt_attn_fwd(const bpt_graph_t* g, const bpt_shape_t* s, const void* Q, cons
     const size_t need = bpt_attn_fwd_workspace(g, s);
     if (need == SIZE_MAX) return BPT_ERR_UNSUPPORTED;
     if (need > 0 && (!workspace || workspace_bytes < need)) return BPT_ERR_INVALID_ARG;
+    const bpt::UseOnReturn use = {g, static_cast<hipStream_t>(stream)};
     bpt::AttnArgs a;
     bpt_shape_t view;
     const bool packed = bpt::packed_tiles(g, s, &view);

@@ -4,6 +4,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <memory>
+#include <utility>
 #include <vector>
 
 #include "bpt.h"
@@ -84,6 +86,20 @@ struct KeyTiles {
     int32_t* multi_ptr = nullptr;   // [num_multi+1] their partial slots
 };
 
+// Device memory for the small tables of batch graphs on one tree (lengths, row deltas, roots), kept by the tree from one
+// graph to the next: a training loop makes and destroys a graph per step, and a hipFree or a copy on the caller's stream
+// would wait for the whole step before it.  A block is handed out again when the work that read it is through, which
+// events say that every call on a batch graph records behind its last kernel, on its stream.  At most kTableBlocks blocks a
+// tree; they go with it and the graphs on it.
+struct TableBlock {
+    int32_t* p = nullptr;
+    size_t capacity = 0;   // int32s
+    bool unknown = false;  // used where no event could say when (inside a stream capture): not handed out again
+    std::vector<std::pair<hipStream_t, hipEvent_t>> uses;   // the last use on every stream that used it
+};
+struct TablePool;
+constexpr int kTableBlocks = 8;
+
 }  // namespace bpt
 
 struct bpt_graph {
@@ -97,6 +113,8 @@ struct bpt_graph {
     // allocation, d_delta, holds these and the roots' tables)
     bpt_graph* tree = nullptr;
     bool owns_tree = false;       // built by this graph (else shared with the caller, who keeps it alive)
+    std::shared_ptr<bpt::TablePool> pool;   // blocks of the tables of the batch graphs on a tree: the tree's and theirs
+    bpt::TableBlock* tables = nullptr;   // batch graph: the block that holds d_delta, d_lengths and the roots
     int32_t *d_lengths = nullptr, *d_delta = nullptr;
     // batch graph, for the stack's readout: the row of every sequence's root (-1: the sequence is empty), and for
     // the rows from first_root on (the root level) the sequence they belong to
@@ -117,6 +135,13 @@ struct bpt_graph {
 };
 
 namespace bpt {
+// bpt_graph.hip: a call has put its kernels on `st`; a batch graph's tables are in use until these are through
+void note_use(const bpt_graph* g, hipStream_t st);
+struct UseOnReturn {   // the same when a scope ends, whichever way
+    const bpt_graph* g;
+    hipStream_t st;
+    ~UseOnReturn() { note_use(g, st); }
+};
 // bpt_attn.hip: address of the current device's copy of the library's static scratch, resolved on first use
 int static_scratch(int device, void** out);
 // bpt_tiles.hip: token tiles and key tiles of a graph whose CSR is on the device

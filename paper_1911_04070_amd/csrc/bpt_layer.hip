@@ -1098,6 +1098,7 @@ int bpt_stack_fwd(const bpt_graph_t* g, int32_t B, int32_t H, int32_t num_layers
     const int64_t rows = (int64_t)B * g->num_nodes;
     if (rows > INT32_MAX) return BPT_ERR_UNSUPPORTED;
     hipStream_t st = static_cast<hipStream_t>(stream);
+    const UseOnReturn use = {g, st};
     unsigned char* ws = static_cast<unsigned char*>(workspace);
     const int row_chunks = H * kD / 8;
     const int64_t chunks = rows * row_chunks;
@@ -1151,6 +1152,7 @@ int bpt_stack_bwd(const bpt_graph_t* g, int32_t B, int32_t H, int32_t num_layers
     const int64_t rows = (int64_t)B * g->num_nodes;
     if (rows > INT32_MAX) return BPT_ERR_UNSUPPORTED;
     hipStream_t st = static_cast<hipStream_t>(stream);
+    const UseOnReturn use = {g, st};
     const unsigned char* fw = static_cast<const unsigned char*>(fwd_workspace);
     unsigned char* ws = static_cast<unsigned char*>(workspace);
     unsigned char* dh[2] = {ws, ws + S.state_bytes};   // gradients with respect to the states, alternating

@@ -344,3 +344,48 @@ def test_a_batch_of_32_sentences():
     rng = np.random.default_rng(32)
     lengths = [int(v) for v in np.clip(rng.lognormal(5.2, 0.7, size=32), 5, 512)]
     run_attention_case("bf16", 512, 4, False, 2, lengths)
+
+
+@pytest.mark.parametrize("graphs,streams,captured", [(3, 1, False), (24, 1, False), (24, 3, False), (6, 1, True)])
+def test_graphs_destroyed_while_their_work_runs(graphs, streams, captured):
+    # the tables of a batch graph lie in a block of the tree's that the next graph takes over: graphs made and destroyed
+    # with their calls still queued (more of them than there are blocks, on several streams, or called inside a stream
+    # capture that is replayed later) have to give the bits of graphs that are alone on the device
+    tree = bpt.bpt_build_graph(512, 4, False)
+    side = [torch.cuda.Stream() for _ in range(streams)]
+    rng = np.random.default_rng(5)
+    cases = []
+    for i in range(graphs):
+        lengths = rng.integers(1, 513, size=8 if i % 5 else 200).astype(np.int32)
+        g = bpt.bpt_build_batch_graph_on(tree, lengths)
+        gen = torch.Generator(device="cuda").manual_seed(i)
+        q = torch.randn(1, 2, g.num_nodes, 64, device="cuda", generator=gen).to(torch.bfloat16)
+        rel = torch.randn(g.num_levels, g.rel_width, 64, device="cuda", generator=gen).to(torch.bfloat16)
+        ws = torch.empty(max(256, bpt.workspace_bytes(g, q)[0]), dtype=torch.uint8, device="cuda")
+        want, _ = bpt.bpt_attn_fwd(g, q, q, q, rel, workspace=ws)
+        torch.cuda.synchronize()
+        g.destroy()
+        cases.append((lengths, q, rel, ws, want, torch.zeros_like(q), torch.zeros(q.shape[:3], dtype=torch.float32, device="cuda")))
+    torch.cuda.synchronize()
+    captures, kept = [], []
+    for i, (lengths, q, rel, ws, _, out, lse) in enumerate(cases):
+        g = bpt.bpt_build_batch_graph_on(tree, lengths)
+        if captured:
+            cg = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(cg):
+                bpt.bpt_attn_fwd(g, q, q, q, rel, out=out, lse=lse, workspace=ws)
+            captures.append(cg)
+            kept.append(g)
+            continue
+        with torch.cuda.stream(side[i % streams]):
+            for _ in range(4):
+                bpt.bpt_attn_fwd(g, q, q, q, rel, out=out, lse=lse, workspace=ws)
+        g.destroy()
+    for cg in captures + captures:
+        cg.replay()
+    torch.cuda.synchronize()
+    for _, _, _, _, want, out, _ in cases:
+        assert torch.equal(out, want)
+    for g in kept:
+        g.destroy()
+    tree.destroy()
