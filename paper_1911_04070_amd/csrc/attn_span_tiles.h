@@ -16,13 +16,19 @@ namespace {
 //   S^T [32 tokens x 16 queries] = K_block (A, rows from memory) x Q^T (B),
 //   out [16 queries x 64]        = P (A: the C layout of S^T, two token chunks interleaved)
 //                                  x V_block (B, read transposed out of LDS).
-// A span inside the block is finished here; an ancestor covers 2^(l-5) blocks, so the
-// block contributes a partial (accumulators, running max, sum) that a merge kernel
-// combines in block order.  K and V of the tokens are read once for all levels instead
-// of once per level.  Every edge of a span row carries r_anc(l): the constant
+// A span inside the block is finished here; an ancestor covers 2^(l-5) blocks, so the block
+// contributes a partial (accumulators, running max, sum).  The four blocks of a workgroup are
+// neighbours (n is a power of two): ancestors of levels 6 and 7 lie inside them and are finished
+// through LDS; for the levels above, the four partials are added up to one, or leave as they
+// are (SpanArgs.unit_log), and a merge kernel combines what a row has in order.  The partials
+// were a quarter to a half of what these kernels write, and are read again: with one per workgroup
+// (8192 tokens, 32 heads) 28 + 11 -> 27 + 5 us forward and 46 + 12 -> 41 + 5 us backward.  K and V of
+// the tokens are read once for all levels instead of once per level.  Every edge of a span row carries r_anc(l): the constant
 // scale * q . r_anc(l) is added to the row's scores (it only moves lse).
 constexpr int kSpanTok = 32;       // tokens per block
 constexpr int kSpanInLevels = 5;   // levels whose spans lie inside one block
+constexpr int kSpanGroupLevels = 7;   // ... inside the four blocks of a workgroup
+static_assert(kTileWaves == 4, "a workgroup covers a span of level kSpanGroupLevels");
 struct SpanArgs {
     const bf16_t *Q, *K, *V, *rel, *dout;
     bf16_t* out;
@@ -33,6 +39,7 @@ struct SpanArgs {
     float* part;
     int64_t sb, sh, sn;
     int32_t BH, H, N, n, L, W, zero;
+    int32_t unit_log;         // a partial stands for 2^unit_log tokens: 5 (a block) or 7 (a workgroup's four blocks)
     float scale;
     const int32_t* seq_len;   // [B] tokens of every sequence, or null
     int32_t leave_unkept;     // rows of nodes a shorter sequence does not keep: left unwritten instead of zero-filled
@@ -124,6 +131,31 @@ __device__ __forceinline__ void span_block_gone(const SpanArgs& a, int bh, int t
     }
 }
 
+// What the four blocks of a workgroup are combined to: row q = 0, 1 are its two spans of level 6, row 2 the span of level 7,
+// the rows behind them the partials of levels 8, 9, ...; wavefronts first .. first + cnt - 1 hold what row q has (blocks
+// that a shorter sequence does not have are left out: they are the last ones).
+struct SpanGroupRow {
+    int bh, level, slot, t0, first, cnt;   // slot: the ancestor's; t0: first token of the row's blocks
+    bool ok;
+};
+__device__ __forceinline__ SpanGroupRow span_group_row(const SpanArgs& a, int q, int nblk) {
+    SpanGroupRow r;
+    r.slot = q < 2 ? 0 : q - 1;
+    r.level = kSpanInLevels + 1 + r.slot;
+    r.first = q == 1 ? 2 : 0;
+    const int span = q < 2 ? 2 : 4, item = blockIdx.x * kTileWaves + r.first;
+    r.ok = r.level <= a.L && item < a.BH * nblk && (r.level <= kSpanGroupLevels || a.unit_log == kSpanGroupLevels);
+    r.bh = min(item, a.BH * nblk - 1) / nblk;
+    r.t0 = (item - r.bh * nblk) * kSpanTok;
+    const int len = seq_length(a.seq_len, r.bh / a.H, a.n);
+    r.cnt = min(span, max(0, (len - r.t0 + kSpanTok - 1) / kSpanTok));
+    return r;
+}
+template <bool PACKED>
+__device__ __forceinline__ int span_group_node_row(const SpanArgs& a, const SpanGroupRow& r, int node) {
+    return PACKED ? node + a.delta[r.level * (a.BH / a.H) + r.bh / a.H] : node;
+}
+
 // PACKED: the rows of the caller's tensors are those of a packed batch (SpanArgs.delta; see attn_device.h)
 template <bool DROP, bool PACKED = false>
 __global__ void __launch_bounds__(kTileThreads) fwd_span_tile_kernel(const SpanArgs a) {
@@ -132,21 +164,20 @@ __global__ void __launch_bounds__(kTileThreads) fwd_span_tile_kernel(const SpanA
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int g = lane >> 4, j = lane & 15;
     bf16_t* v_s = reinterpret_cast<bf16_t*>(smem) + (size_t)wave * kSpanTok * kVStride;   // [32 tokens][kVStride]
+    float* part_s = reinterpret_cast<float*>(v_s);                                        // later: [16 ancestors][kDqStride]
+    static_assert(16 * kDqStride * sizeof(float) == kSpanTok * kVStride * sizeof(bf16_t), "a wavefront's partials fill its V rows");
+    __shared__ float2 ml_s[kTileWaves][16];                                               // (max, sum) of the partials
     const int nblk = a.n / kSpanTok;
     const int item = blockIdx.x * kTileWaves + wave;
-    if (item >= a.BH * nblk) return;   // wave-uniform; the kernel has no workgroup barrier
-    const int bh = item / nblk, blk = item - bh * nblk, t0 = blk * kSpanTok;
+    const int bh = min(item, a.BH * nblk - 1) / nblk, blk = item - bh * nblk, t0 = blk * kSpanTok;
     const int64_t base = (int64_t)(bh / a.H) * a.sb + (int64_t)(bh % a.H) * a.sh;
     const float qscale = a.scale * kLog2e;
     const int ngroups = a.L > kSpanInLevels ? 3 : 2;
     const int nanc = a.L - kSpanInLevels;
     const int len = seq_length(a.seq_len, bh / a.H, a.n);   // tokens from `len` on do not exist
 
+    auto block = [&]() {
     // the block's K rows as A operands (token j of chunk c, features 16g..16g+15); V rows into LDS
-    if (t0 >= len) {   // wave-uniform: a block past the end of a shorter sequence
-        span_block_gone(a, bh, t0, base, true, lane);
-        return;
-    }
     // packed batch: rows of the caller's tensors are the node ids moved by the sequence's delta of the node's level;
     // a node the sequence does not keep has no row, its loads go to the last kept node of its level instead (every
     // score of such a query, and of such a token, is masked) and nothing is stored for it
@@ -272,19 +303,78 @@ __global__ void __launch_bounds__(kTileThreads) fwd_span_tile_kernel(const SpanA
                 store_once(reinterpret_cast<uint4*>(a.out + base + (int64_t)orow_at * a.sn + piece * 8), make_uint4(x0.x, x0.y, x1.x, x1.y));
             }
         } else {
-            // partial of the ancestor at level 6 + slot: [bh][level][block][66]
-            if (g == 0 && valid) {
+            // partial of the ancestor at level 6 + slot, for the workgroup
+            if (g == 0) ml_s[wave][j] = make_float2(m, l);
+            wave_lds_sync();   // the previous group's rows have been read
+#pragma unroll
+            for (int f = 0; f < 4; ++f) *reinterpret_cast<f32x4_t*>(part_s + j * kDqStride + 16 * f + 4 * g) = o[f];
+            if (a.unit_log > kSpanInLevels) continue;   // uniform
+            // ... and as it is, above level 7: [bh][level][block][66]
+            if (g == 0 && valid && j >= 2) {
                 float* dst = a.part + (((int64_t)bh * nanc + j) * nblk + blk) * kPartStride;
                 dst[64] = m;
                 dst[65] = l;
             }
-            if (j < nanc) {   // (a partial is 264 bytes: 8-byte stores)
+            if (j >= 2 && j < nanc) {   // (a partial is 264 bytes: 8-byte stores)
                 float* dst = a.part + (((int64_t)bh * nanc + j) * nblk + blk) * kPartStride + 4 * g;
 #pragma unroll
                 for (int f = 0; f < 4; ++f) {
                     *reinterpret_cast<float2*>(dst + 16 * f) = make_float2(o[f][0], o[f][1]);
                     *reinterpret_cast<float2*>(dst + 16 * f + 2) = make_float2(o[f][2], o[f][3]);
                 }
+            }
+        }
+    }
+    };
+    if (item < a.BH * nblk) {   // wave-uniform
+        if (t0 >= len)
+            span_block_gone(a, bh, t0, base, true, lane);   // a block past the end of a shorter sequence
+        else
+            block();
+    }
+    if (nanc <= 0) return;
+    __syncthreads();
+    for (int q = threadIdx.x >> 4; q <= nanc; q += kTileThreads / 16) {   // thread -> (row, 4 features); see fwd_span_merge_small
+        const SpanGroupRow r = span_group_row(a, q, nblk);
+        if (!r.ok) continue;
+        const int f4 = 4 * j;
+        f32x4_t x[kTileWaves];
+        float m[kTileWaves], l[kTileWaves], mx = kNegBig;
+#pragma unroll
+        for (int b = 0; b < kTileWaves; ++b) {
+            const int w = r.first + min(b, max(r.cnt - 1, 0));
+            const float2 ml = ml_s[w][r.slot];
+            x[b] = *reinterpret_cast<const f32x4_t*>(reinterpret_cast<float*>(smem) + (w * 16 + r.slot) * kDqStride + f4);
+            m[b] = b < r.cnt ? ml.x : kNegBig;
+            l[b] = b < r.cnt ? ml.y : 0.f;
+            mx = fmaxf(mx, m[b]);
+        }
+        float ls = 0.f;
+        f32x4_t acc = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int b = 0; b < kTileWaves; ++b)
+            if (b < r.cnt) {
+                const float c = fast_exp2(m[b] - mx);
+                ls += l[b] * c;
+#pragma unroll
+                for (int i = 0; i < 4; ++i) acc[i] += x[b][i] * c;
+            }
+        if (r.level <= kSpanGroupLevels) {
+            if (r.cnt == 0 && a.leave_unkept) continue;   // the sequence does not keep the node
+            const int row = span_group_node_row<PACKED>(a, r, span_level_offset(a.n, r.level) + (r.t0 >> r.level));
+            const int64_t at = (int64_t)(r.bh / a.H) * a.sb + (int64_t)(r.bh % a.H) * a.sh + (int64_t)row * a.sn + f4;
+            float y[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) y[i] = ls > 0.f ? acc[i] / ls : 0.f;
+            *reinterpret_cast<uint2*>(a.out + at) = make_uint2(pack_bf16(y[0], y[1]), pack_bf16(y[2], y[3]));
+            if (j == 0) a.lse[span_lse_at<PACKED>(a, r.bh) + row] = ls > 0.f ? (mx + fast_log2(ls)) * kLn2 : 0.f;
+        } else if (r.cnt > 0) {   // the workgroup's partial: [bh][level][workgroup][66]
+            float* dst = a.part + (((int64_t)r.bh * nanc + r.slot) * (a.n >> kSpanGroupLevels) + (r.t0 >> kSpanGroupLevels)) * kPartStride;
+            *reinterpret_cast<float2*>(dst + f4) = make_float2(acc[0], acc[1]);
+            *reinterpret_cast<float2*>(dst + f4 + 2) = make_float2(acc[2], acc[3]);
+            if (j == 0) {
+                dst[64] = mx;
+                dst[65] = ls;
             }
         }
     }
@@ -297,16 +387,16 @@ __device__ __forceinline__ void span_node_level(int n, int L, int v, int& level,
     m = v - span_level_offset(n, level);
 }
 
-// Ancestors (levels 6..L): combine the per-block partials of a row in block order.  A row of
-// level l has 2^(l-5) partials.  Rows with at most 16 (levels 6..9) take one wavefront each,
+// Ancestors above level 7: combine the partials of a row in order.  A row of level l has
+// 2^(l-unit_log) partials.  Rows with at most 16 take one wavefront each,
 // lane = feature, all loads issued at once; longer rows take a workgroup of 1024 threads
 // (thread = 4 features x one of 64 interleaved block lists) and a fixed-order sum of the 64
 // lists, so the result does not depend on timing.
-constexpr int kSpanSmallLevels = 4;                                  // levels 6..9
+constexpr int kSpanSmallLevels = 4;
 constexpr int kSpanSmallMax = 1 << kSpanSmallLevels;                 // 16 partials
 constexpr int kSpanBigThreads = 1024;
 struct SpanRow {
-    int bh, v, cnt;   // cnt: partials of the row that exist -- its blocks that begin before the end of the sequence
+    int bh, v, cnt;   // cnt: partials of the row that exist -- those whose tokens begin before the end of the sequence
     const float* src;
 };
 // rows [first, first + rows) of every (batch, head); stride = floats per partial
@@ -316,9 +406,9 @@ __device__ __forceinline__ bool span_merge_row(const SpanArgs& a, int item, int 
     r.v = first + (item - r.bh * rows);
     int level, mi;
     span_node_level(a.n, a.L, r.v, level, mi);
-    const int nblk = a.n / kSpanTok, nanc = a.L - kSpanInLevels;
-    const int all = 1 << (level - kSpanInLevels);
-    const int live_blocks = (seq_length(a.seq_len, r.bh / a.H, a.n) + kSpanTok - 1) / kSpanTok;
+    const int nblk = a.n >> a.unit_log, nanc = a.L - kSpanInLevels;
+    const int all = 1 << (level - a.unit_log);
+    const int live_blocks = (seq_length(a.seq_len, r.bh / a.H, a.n) + (1 << a.unit_log) - 1) >> a.unit_log;
     r.cnt = min(all, max(live_blocks - mi * all, 0));
     r.src = a.part + (((int64_t)r.bh * nanc + (level - kSpanInLevels - 1)) * nblk + (int64_t)mi * all) * stride;
     return true;
@@ -434,27 +524,28 @@ __global__ void __launch_bounds__(kSpanBigThreads) fwd_span_merge_kernel(const S
 // and dS = w - delta p are final and dQ = scale * dS K_block (r_anc drops out: the dS of a row
 // sum to zero).  An ancestor stores the partial sums A = W K, Bv = P K, delta, which the merge
 // kernel turns into dQ = scale * (sum A - delta * sum Bv).
+__host__ __device__ inline int span_bwd_floats(int nanc) {   // LDS of a wavefront
+    return max(kSpanTok * kVStride / 2, nanc * kQPartStride);
+}
 template <bool DROP, bool G16, bool PACKED = false>   // G16: dQ leaves rounded to bf16
 __global__ void __launch_bounds__(kTileThreads, 3) bwd_q_span_tile_kernel(const SpanArgs a) {
     extern __shared__ __align__(16) unsigned char smem[];
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int g = lane >> 4, j = lane & 15;
-    bf16_t* k_s = reinterpret_cast<bf16_t*>(smem) + (size_t)wave * kSpanTok * kVStride;
+    const int nanc = a.L - kSpanInLevels;
+    const int stride = span_bwd_floats(nanc);   // of a wavefront: the block's K rows, later [ancestor][kQPartStride]
+    float* part_s = reinterpret_cast<float*>(smem) + wave * stride;
+    bf16_t* k_s = reinterpret_cast<bf16_t*>(part_s);
     const int nblk = a.n / kSpanTok;
     const int item = blockIdx.x * kTileWaves + wave;
-    if (item >= a.BH * nblk) return;
-    const int bh = item / nblk, blk = item - bh * nblk, t0 = blk * kSpanTok;
+    const int bh = min(item, a.BH * nblk - 1) / nblk, blk = item - bh * nblk, t0 = blk * kSpanTok;
     const int64_t base = (int64_t)(bh / a.H) * a.sb + (int64_t)(bh % a.H) * a.sh;
     const float qscale = a.scale * kLog2e;
     const int ngroups = a.L > kSpanInLevels ? 3 : 2;
-    const int nanc = a.L - kSpanInLevels;
     const int len = seq_length(a.seq_len, bh / a.H, a.n);
 
-    if (t0 >= len) {   // wave-uniform: a block past the end of a shorter sequence
-        span_block_gone(a, bh, t0, base, false, lane);
-        return;
-    }
+    auto block = [&]() {
     // packed batch: see fwd_span_tile_kernel
     const int dvec = PACKED ? load_delta(a.delta, a.BH / a.H, bh / a.H, lane, a.L + 1) : 0;
     // the Q and dO rows and the lse of all three groups are asked for together with the block's K and V:
@@ -612,15 +703,54 @@ __global__ void __launch_bounds__(kTileThreads, 3) bwd_q_span_tile_kernel(const 
                 op[f] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kB[f], pH, op[f], 0, 0, 0);
                 op[f] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kB[f], pL, op[f], 0, 0, 0);
             }
-            if (g == 0 && valid) a.part[(((int64_t)bh * nanc + j) * nblk + blk) * kQPartStride + 2 * kD] = dl;
-            if (j < nanc) {   // features 16f + 4g .. + 3 of ancestor j: 16 bytes at a time
-                float* dst = a.part + (((int64_t)bh * nanc + j) * nblk + blk) * kQPartStride + 4 * g;
+            wave_lds_sync();   // the previous group's rows have been read
+            if (j < nanc) {   // features 16f + 4g .. + 3 of ancestor j
+                if (g == 0) part_s[j * kQPartStride + 2 * kD] = dl;
+                float* dst = part_s + j * kQPartStride + 4 * g;
 #pragma unroll
                 for (int f = 0; f < 4; ++f) {
                     *reinterpret_cast<f32x4_t*>(dst + 16 * f) = ow[f];
                     *reinterpret_cast<f32x4_t*>(dst + kD + 16 * f) = op[f];
                 }
             }
+        }
+    }
+    };
+    if (item < a.BH * nblk) {   // wave-uniform
+        if (t0 >= len)
+            span_block_gone(a, bh, t0, base, false, lane);   // a block past the end of a shorter sequence
+        else
+            block();
+    }
+    if (nanc <= 0) return;
+    __syncthreads();
+    for (int q = threadIdx.x >> 4; q <= nanc; q += kTileThreads / 16) {   // thread -> (row, 4 features)
+        const SpanGroupRow r = span_group_row(a, q, nblk);
+        if (!r.ok) continue;
+        const int f4 = 4 * j;
+        f32x4_t sa = {0.f, 0.f, 0.f, 0.f}, sb = sa;
+        float dl = 0.f;
+        for (int b = 0; b < r.cnt; ++b) {
+            const float* pb = reinterpret_cast<const float*>(smem) + (r.first + b) * stride + r.slot * kQPartStride;
+            sa += *reinterpret_cast<const f32x4_t*>(pb + f4);
+            sb += *reinterpret_cast<const f32x4_t*>(pb + kD + f4);
+            dl += pb[2 * kD];
+        }
+        if (r.level <= kSpanGroupLevels) {   // the row is complete
+            const int node = span_level_offset(a.n, r.level) + (r.t0 >> r.level);
+            const int row = span_group_node_row<PACKED>(a, r, node);
+            if (r.cnt > 0 || !a.leave_unkept)
+                store_grad4(a.dQ, (int64_t)(r.bh / a.H) * a.sb + (int64_t)(r.bh % a.H) * a.sh + (int64_t)row * a.sn + f4,
+                            make_float4(a.scale * (sa[0] - dl * sb[0]), a.scale * (sa[1] - dl * sb[1]), a.scale * (sa[2] - dl * sb[2]),
+                                        a.scale * (sa[3] - dl * sb[3])), G16);
+            if (j == 0)
+                a.stat[(int64_t)r.bh * a.N + node] =
+                    r.cnt > 0 ? make_float2(a.lse_r[span_lse_at<PACKED>(a, r.bh) + row] * kLog2e, dl) : make_float2(kLseGone, 0.f);
+        } else if (r.cnt > 0) {   // the workgroup's partial: [bh][level][workgroup][132]
+            float* dst = a.part + (((int64_t)r.bh * nanc + r.slot) * (a.n >> kSpanGroupLevels) + (r.t0 >> kSpanGroupLevels)) * kQPartStride;
+            *reinterpret_cast<f32x4_t*>(dst + f4) = sa;
+            *reinterpret_cast<f32x4_t*>(dst + kD + f4) = sb;
+            if (j == 0) dst[2 * kD] = dl;
         }
     }
 }

@@ -398,7 +398,13 @@ int run_span_tiles(const bpt_graph* g, const AttnArgs& a, bool forward, hipStrea
     fill_span_args(t, g, a);
     const int64_t items = (int64_t)a.BH * (g->n / kSpanTok);
     const unsigned grid = (unsigned)((items + kTileWaves - 1) / kTileWaves);
-    const size_t lds = (size_t)kTileWaves * kSpanTok * kVStride * sizeof(bf16_t);
+    // Partials of whole workgroups, at any size in the backward.  The forward's rows above level 7 would be rounded
+    // differently with them (sums of sums), which a deep stack's ReLU gates amplify in its gradients: below 2048 tokens,
+    // where little is gained, they stay one sum over the blocks (forward in blocks -> workgroups: 512 tokens, 256 heads
+    // 43.3 -> 42.5 us, 1024 tokens 45.1 -> 44.7 and 76.4 -> 73.8; from 2048 on 77.0 -> 73.8 us, 8192 tokens 97 -> 88).
+    t.unit_log = g->n >= (forward ? 2048 : 128) ? kSpanGroupLevels : kSpanInLevels;
+    const size_t lds = forward ? (size_t)kTileWaves * kSpanTok * kVStride * sizeof(bf16_t)
+                               : (size_t)kTileWaves * span_bwd_floats(t.L - kSpanInLevels) * sizeof(float);
     if (t.delta && forward)
         BPT_LAUNCH("fwd_span_tile_kernel", (fwd_span_tile_kernel<false, true>), dim3(grid), dim3(kTileThreads), lds, st, t);
     else if (t.delta && t.grad_bf16)
@@ -418,10 +424,10 @@ int run_span_tiles(const bpt_graph* g, const AttnArgs& a, bool forward, hipStrea
     else
         BPT_LAUNCH("bwd_q_span_tile_kernel", (bwd_q_span_tile_kernel<false, false>), dim3(grid), dim3(kTileThreads), lds, st, t);
     BPT_HIP(hipGetLastError());
-    if (t.L > kSpanInLevels) {
-        // rows of levels 6..9 (at most 16 partials each), then the longer rows
-        const int first = 2 * g->n - ((2 * g->n) >> (kSpanInLevels + 1));
-        const int big_level = kSpanInLevels + 1 + kSpanSmallLevels;
+    if (t.L > kSpanGroupLevels) {
+        // rows above level 7 with at most 16 partials each, then the longer rows
+        const int first = 2 * g->n - ((2 * g->n) >> (kSpanGroupLevels + 1));
+        const int big_level = t.unit_log + 1 + kSpanSmallLevels;
         const int first_big = t.L >= big_level ? 2 * g->n - ((2 * g->n) >> big_level) : g->num_nodes;
         const int rows_small = first_big - first, rows_big = g->num_nodes - first_big;
         const int per_block = kSpanBigThreads / 64;   // short rows per workgroup
