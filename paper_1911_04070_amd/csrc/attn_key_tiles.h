@@ -44,6 +44,7 @@ struct KeyArgs {
     // 8 task counters (one per XCD, 64 bytes apart), zero when the kernel starts: cleared by the last kernel
     // of the query side when both sides run in one call, else by zero_ints_kernel
     int32_t* queue;
+    int32_t one_chunk_level;    // from this level on every id in use is below 16 (bwd_kv_chain_kernel)
     const int32_t* id_blocks;   // [chunks] bit b: an edge of the chunk carries one of the ids 16b .. 16b + 15 (last: see TileArgs)
 };
 
@@ -395,6 +396,9 @@ __global__ void __launch_bounds__(kTileThreads, 2) bwd_kv_tile_kernel(const KeyA
 // bias of (query, id) is not staged through LDS: the product Q_chunk x Rel_sel^T leaves bias[query 4g + r][id j]
 // in lane (g, j), register r, and the lane that needs it reads it from there (ds_bpermute), which makes room
 // for the staging area.
+// With two chunks of ids (NBC == 2) only tasks of the token level look into the second: above it the ids are orders, nearly
+// always below 16 (KeyArgs.one_chunk_level), and the LDS unit, which serves the exchange, is the busiest one here (8192
+// tokens, k = 8, 32 heads: 188 -> 183 us; packed, lengths up to 8192: 189 -> 178).
 // G16: dK and dV leave rounded to bf16 (a compile-time switch: the stores sit inside the pipelined loop)
 template <int NBC, bool DROP, bool G16, bool PACKED = false>
 __global__ void __launch_bounds__(kTileThreads, 2) bwd_kv_chain_kernel(const KeyArgs a) {
@@ -428,6 +432,7 @@ __global__ void __launch_bounds__(kTileThreads, 2) bwd_kv_chain_kernel(const Key
         const int kt0 = uniform_i32(a.task_tile, task), c0 = uniform_i32(a.task_c0, task), part = uniform_i32(a.task_part, task);
         const int nch = uniform_i32(a.task_nch, task), ntiles = uniform_i32(a.task_ntiles, task);
         const int level = uniform_i32(a.tile_info, kt0) & 255;   // the same for all tiles of the task
+        const bool wide = NBC == 2 && level < a.one_chunk_level;
         const int len = seq_length_u(a.seq_len, bh / a.H, a.n);
         const int level_node0 = 2 * a.n - ((2 * a.n) >> level), level_kept = (len + (1 << level) - 1) >> level;
         const int64_t base = (int64_t)(bh / a.H) * a.sb + (int64_t)(bh % a.H) * a.sh;
@@ -571,7 +576,7 @@ __global__ void __launch_bounds__(kTileThreads, 2) bwd_kv_chain_kernel(const Key
             const bool key_kept = j < kept_keys;
             const bf16x8_t kb0 = __builtin_bit_cast(bf16x8_t, kk[0].w), kb1 = __builtin_bit_cast(bf16x8_t, kk[1].w);
             const bf16x8_t vb0 = __builtin_bit_cast(bf16x8_t, vv[0].w), vb1 = __builtin_bit_cast(bf16x8_t, vv[1].w);
-            f32x4_t s4[2], d4[2], b4[2][NBC];
+            f32x4_t s4[2], d4[2], b4[2];
 #pragma unroll
             for (int ci = 0; ci < 2; ++ci) {
                 const bf16_t* qr = q_s + (16 * ci + j) * kRowStride + 16 * g;
@@ -583,12 +588,33 @@ __global__ void __launch_bounds__(kTileThreads, 2) bwd_kv_chain_kernel(const Key
                 s4[ci] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(q1, kb1, s4[ci], 0, 0, 0);
                 d4[ci] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(g0, vb0, d4[ci], 0, 0, 0);
                 d4[ci] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(g1, vb1, d4[ci], 0, 0, 0);
+                b4[ci] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+                b4[ci] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(q0, rb[0][0], b4[ci], 0, 0, 0);
+                b4[ci] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(q1, rb[0][1], b4[ci], 0, 0, 0);
+            }
+            // bias[query 4g + r][id] sits in lane (g, id % 16), register r of the id's chunk
+            float bias[2][4];
+            const auto id_of = [&](int ci, int r) { return (int)(short)((r < 2 ? mpc[ci].x : mpc[ci].y) >> (16 * (r & 1))); };
 #pragma unroll
-                for (int bc = 0; bc < NBC; ++bc) {
-                    b4[ci][bc] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-                    b4[ci][bc] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(q0, rb[bc][0], b4[ci][bc], 0, 0, 0);
-                    b4[ci][bc] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(q1, rb[bc][1], b4[ci][bc], 0, 0, 0);
+            for (int ci = 0; ci < 2; ++ci)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) bias[ci][r] = __shfl(b4[ci][r], (lane & 48) | (max(id_of(ci, r), 0) & 15));
+            if (NBC == 2 && wide) {   // uniform for the task
+                asm volatile("");     // (a branch)
+#pragma unroll
+                for (int ci = 0; ci < 2; ++ci) {
+                    const bf16_t* qr = q_s + (16 * ci + j) * kRowStride + 16 * g;
+                    b4[ci] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+                    b4[ci] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(*reinterpret_cast<const bf16x8_t*>(qr), rb[NBC - 1][0], b4[ci], 0, 0, 0);
+                    b4[ci] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(*reinterpret_cast<const bf16x8_t*>(qr + 8), rb[NBC - 1][1], b4[ci], 0, 0, 0);
                 }
+#pragma unroll
+                for (int ci = 0; ci < 2; ++ci)
+#pragma unroll
+                    for (int r = 0; r < 4; ++r) {
+                        const float x = __shfl(b4[ci][r], (lane & 48) | (max(id_of(ci, r), 0) & 15));
+                        bias[ci][r] = id_of(ci, r) >= 16 ? x : bias[ci][r];
+                    }
             }
             float ds[2][4], pp[2][4];
 #pragma unroll
@@ -596,21 +622,13 @@ __global__ void __launch_bounds__(kTileThreads, 2) bwd_kv_chain_kernel(const Key
                 const float4 x = *reinterpret_cast<const float4*>(stat_s + 16 * ci + 4 * g);
                 const float4 y = *reinterpret_cast<const float4*>(stat_s + 16 * ci + 4 * g + 2);
                 const float2 st[4] = {make_float2(x.x, x.y), make_float2(x.z, x.w), make_float2(y.x, y.y), make_float2(y.z, y.w)};
-                const int bid[4] = {(int)(short)(mpc[ci].x & 0xFFFFu), (int)(short)(mpc[ci].x >> 16),
-                                    (int)(short)(mpc[ci].y & 0xFFFFu), (int)(short)(mpc[ci].y >> 16)};
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    // bias[query 4g + r][id] sits in lane (g, id % 16), register r of the id's chunk
-                    const int src = (lane & 48) | (max(bid[r], 0) & 15);
-                    float bv = __shfl(b4[ci][0][r], src);
-                    if (NBC == 2) {
-                        const float bv1 = __shfl(b4[ci][1][r], src);
-                        bv = bid[r] >= 16 ? bv1 : bv;
-                    }
-                    const float p = DROP ? (bid[r] >= 0 && key_kept ? fast_exp2((s4[ci][r] + bv) * qscale - st[r].x) : 0.f)
-                                         : masked_exp2(bid[r] >= 0 && key_kept, (s4[ci][r] + bv) * qscale - st[r].x);
+                    const int bid = id_of(ci, r);
+                    const float x = (s4[ci][r] + bias[ci][r]) * qscale - st[r].x;
+                    const float p = DROP ? (bid >= 0 && key_kept ? fast_exp2(x) : 0.f) : masked_exp2(bid >= 0 && key_kept, x);
                     if (DROP) {
-                        const uint32_t x2 = bid[r] < a.W ? (uint32_t)(level * a.W + bid[r]) : 0x80000000u + (uint32_t)(node0 + j);
+                        const uint32_t x2 = bid < a.W ? (uint32_t)(level * a.W + bid) : 0x80000000u + (uint32_t)(node0 + j);
                         const float keep = drop_scale(rowh_s[16 * ci + 4 * g + r], x2, a.drop_thr, a.drop_inv_keep);
                         pp[ci][r] = p * keep;
                         ds[ci][r] = p * (d4[ci][r] * keep - st[r].y);

@@ -901,6 +901,8 @@ KeyArgs fill_key_args(const bpt_graph* g, const AttnArgs& a) {
     t.nb_pad = kt.nb_pad;
     t.W = g->rel_width;
     t.zero = g->k + 1;
+    // Above the tokens an edge's id is its order: 0..k on the left, k + 2..2k + 2 on the right (r_anc ends in a token only)
+    t.one_chunk_level = (g->causal ? g->k : 2 * g->k + 2) < 16 ? 1 : g->num_levels;
     t.num_chunks = kt.num_chunks;
     t.seq_len = a.seq_len;
     t.leave_unkept = a.leave_unkept;
