@@ -13,7 +13,7 @@
 // spend about 70 vector instructions per 8 edges and side on dot products across lanes, online softmax per edge and index
 // arithmetic, at half of the vector unit's time, the rest waiting.
 // n = 2048, k = 8, causal, 16 (batch, head)s, gather kernels -> these (us): forward 71 -> 38, query side with d_rel 112 -> 73, key
-// side 101 -> 39, step 315 -> 178; n = 512, k = 4, one head, forward 15.2 -> 7.6.  The matrix cores are busy for a fifth of
+// side 101 -> 39, step 315 -> 166; n = 512, k = 4, one head, forward 15.2 -> 7.6.  The matrix cores are busy for a fifth of
 // that (7, 16 and 11 us); the rest is the chain ids -> rows -> products -> sums of a tile at two to four wavefronts per SIMD,
 // and the span rows' vector code (15 and 19 us by themselves; in a launch of their own the step was no shorter).
 #pragma once

@@ -1150,7 +1150,7 @@ struct RelGradArgs {
     const float* dq32;        // the key part of dQ (see TileArgs), or null: it is in dQ
     const int32_t* delta;     // packed batch: delta[level][sequence] (only the token level is used here), or null
 };
-// tile slots per thread fetched one block ahead: 8 (512 threads: 16 chunks) with up to 256 ids, 24 with more --
+// tile slots per thread fetched one block ahead: 8 (512 threads: 16 chunks) with up to 256 ids, up to 32 with more --
 // those graphs have 25..30 slots per thread and block, and one workgroup per compute unit to hide their latency
 template <int CPW>
 struct RgPrefetch {
