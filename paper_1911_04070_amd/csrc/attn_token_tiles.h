@@ -134,7 +134,8 @@ __device__ __forceinline__ s16x4_t lds_tr4(const bf16_t* base, int stride, int r
 // not end on a parent boundary), and level l keeps ceil(len / 2^l) nodes.  Lane (g, j) works on
 // token j of the tile; the four lane groups share the ids.
 // c0, c1: the ids to look at (the others are not in the table yet, or no longer): in a ring at most as many as it holds.
-constexpr float kMaskBias = -1.0e30f;
+// (An infinity: any finite number would be brought back into range by a small enough scale.)
+constexpr float kMaskBias = -INFINITY;
 enum class Bias { kStaged, kRing, kMemory };   // (see ring_form)
 constexpr int kRingIds = 16 * kRingBlocks;
 constexpr int kRingStride = kRingIds + 4;   // = 4 mod 32: the 16 token rows hit different banks
@@ -142,17 +143,18 @@ template <Bias BIAS>
 __device__ __forceinline__ int bias_slot(int cid) {   // where a token's row of the table holds an id
     return BIAS == Bias::kRing ? cid & (kRingIds - 1) : cid;
 }
-// The column of a token's row of the table that a map word (16 bits: a compact id, or 0xFFFF where there is no edge) reads: the
-// words without an edge read the column behind the ids, which holds kMaskBias, so that nothing behind the lookup asks
-// whether there is an edge -- the weight of such a slot comes out as exactly 0 by itself.  Together with descriptors
-// formed once per tile, ids requested without a branch and the table formed two blocks at a time (n = 8192, k = 8, causal, 32
-// (batch, head)s, us): forward 64.0 -> 61.1, query side 137 -> 128.
-template <Bias BIAS>
-__device__ __forceinline__ int mask_column(int cid_pad) { return BIAS == Bias::kRing ? kRingIds : cid_pad; }
+// The column of a token's row of the table that a map word (16 bits: a compact id, or 0xFFFF where there is no edge) reads.
+// Words without an edge read some column of the row (staged and whole tables: the one behind the ids), and has_edge masks
+// what comes of it: by the word and not by a large negative bias, which a large score, an infinity or a NaN in the K row
+// of a column without an edge, or a small scale would pass (the two selects per element cost, at n = 8192, k = 8, causal, 32
+// (batch, head)s: forward 58.7 -> 61.0 us, query side 120.9 -> 123.8).  The masked score is kNegBig; the running maximum starts
+// above it (kMaxStart), so that its weight is 0 also where a token has no edge in its first pairs.
 template <Bias BIAS>
 __device__ __forceinline__ int bias_column(uint32_t word, int cid_pad) {
-    return BIAS == Bias::kRing ? (int)((word & (kRingIds - 1)) + (word >> 15)) : (int)min(word, (uint32_t)cid_pad);
+    return BIAS == Bias::kRing ? (int)(word & (kRingIds - 1)) : (int)min(word, (uint32_t)cid_pad);
 }
+__device__ __forceinline__ bool has_edge(uint32_t word) { return word < 0x8000u; }
+constexpr float kMaxStart = 0.5f * kNegBig;
 template <Bias BIAS>
 __device__ __forceinline__ void mask_bias(const TileArgs& a, float* bias_s, int t0, int len, int g, int j, int c0, int c1) {
     const int t = t0 + j;
@@ -485,7 +487,7 @@ __global__ void __launch_bounds__(kTileThreads, 2) fwd_tile_kernel(const TileArg
     advance(ci);
 
     bf16x8_t qb0, qb1;
-    float m_run = kNegBig, l_part = 0.f;
+    float m_run = kMaxStart, l_part = 0.f;
     f32x4_t o[4];
     uint32_t rowh = 0;   // DROP: hash of (seed, batch*head, token j of the tile)
 
@@ -499,11 +501,10 @@ __global__ void __launch_bounds__(kTileThreads, 2) fwd_tile_kernel(const TileArg
             if (DROP) rowh = drop_row_hash(drop_bh_hash(a.drop_seed, cc.bh), cc.tile * 16 + j);
             qb0 = qn0;
             qb1 = qn1;
-            m_run = kNegBig;
+            m_run = kMaxStart;
             l_part = 0.f;
 #pragma unroll
             for (int f = 0; f < 4; ++f) o[f] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-            bias_s[j * bias_stride + mask_column<BIAS>(a.cid_pad)] = kMaskBias;
             // bias^T = Rel x Q^T, kept in LDS as [token][compact id]
             if (!kFromMemory) staged_bias(a, rel_s, bias_s, qb0, qb1, g, j);
             if (!kFromMemory && a.seq_len) {   // uniform
@@ -560,7 +561,7 @@ __global__ void __launch_bounds__(kTileThreads, 2) fwd_tile_kernel(const TileArg
         for (int c = 0; c < 2; ++c)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                sc[c][r] = (s4[c][r] + bv[c][r]) * qscale;
+                sc[c][r] = has_edge(word[c][r]) ? (s4[c][r] + bv[c][r]) * qscale : kNegBig;
                 gm = fmaxf(gm, sc[c][r]);
             }
         gm = fmaxf(gm, __shfl_xor(gm, 16));
@@ -905,7 +906,6 @@ __global__ void __launch_bounds__(kTileThreads, DENSE ? 1 : 2) bwd_q_tile_kernel
             dl_part = 0.f;
 #pragma unroll
             for (int f = 0; f < 4; ++f) ow[f] = op[f] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-            bias_s[j * bias_stride + mask_column<BIAS>(a.cid_pad)] = kMaskBias;
             // bias^T = Rel x Q^T, kept in LDS as [token][compact id]
             if (!kFromMemory) staged_bias(a, rel_s, bias_s, qb0, qb1, g, j);
             if (!kFromMemory && a.seq_len) {   // uniform
@@ -969,7 +969,7 @@ __global__ void __launch_bounds__(kTileThreads, DENSE ? 1 : 2) bwd_q_tile_kernel
         for (int c = 0; c < 2; ++c) {
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                const float p = fast_exp2((s4[c][r] + bv[c][r]) * qscale - lse2);   // (0 without an edge)
+                const float p = masked_exp2(has_edge(word[c][r]), (s4[c][r] + bv[c][r]) * qscale - lse2);
                 // with dropout out = sum keep p v, so dP carries the mask
                 const float keep = DROP ? drop_scale(rowh, (uint32_t)relid_s[min(word[c][r], (uint32_t)a.cid_pad - 1)], a.drop_thr, a.drop_inv_keep) : 1.f;
                 const float wgt = p * d4[c][r] * keep;
