@@ -54,8 +54,11 @@
  * bpt_shape_t.leave_unkept -- and add nothing to d_rel; their input rows are never used but
  * must hold finite values.  Values of seq_len outside [0, n] are clamped.
  *
- * Rows are multiplied in tiles of 16, weights of pairs without an edge being zero: a row of Q, K, V or
- * dout that holds an infinity or a NaN also shows in results of nodes near those it has edges with.
+ * Infinities and NaNs.  fp32: a row of Q, K, V or dout that holds one shows at most in the results of the nodes
+ * it has edges with (K, V: the rows that read the node; Q, dout: the node itself; backward also the keys of every
+ * such row) and in d_rel.  bf16, forward: the same for Q, K and rel; rows of V, and all rows in the backward, are
+ * multiplied in tiles of 16 with weight 0 where there is no edge, so that what is not finite in one of them also
+ * shows in results of its neighbours in the tile.  Finite values show nowhere else.
  */
 #ifndef BPT_H_
 #define BPT_H_

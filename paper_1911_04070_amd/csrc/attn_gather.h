@@ -40,16 +40,17 @@ __device__ __forceinline__ void fwd_segment(const AttnArgs& a, const T* rel_s, r
     const uint32_t rowh = drop_row_hash(drop_bh_hash(a.drop_seed, bh), u);
 
     // indices two iterations ahead, rows one iteration ahead.  Lanes past the end of
-    // the segment read the next rows' indices (or 0 past the array): valid nodes,
-    // and their contribution is masked.
+    // the segment repeat its last edge with weight 0 (another row's key would bring
+    // that key's infinities and NaNs into this row: 0 times those is not 0).
     int eo = (e0 + slot) * 4;
-    const int c0 = buf_i32(rIa, eo);
+    const int eo_last = (e1 - 1) * 4;
+    const int c0 = buf_i32(rIa, min(eo, eo_last));
     int cnow = c0;   // key node of the rows in work
-    int c1 = buf_i32(rIa, eo + 32);
+    int c1 = buf_i32(rIa, min(eo + 32, eo_last));
     int r0 = 0, r1 = 0;
     if (!SPAN) {
-        r0 = buf_i32(rIb, eo);
-        r1 = buf_i32(rIb, eo + 32);
+        r0 = buf_i32(rIb, min(eo, eo_last));
+        r1 = buf_i32(rIb, min(eo + 32, eo_last));
     }
     Row<T> k0 = gather_row<T>(rK, c0, a.row_bytes, lane_off), v0 = gather_row<T>(rV, c0, a.row_bytes, lane_off);
 
@@ -66,9 +67,9 @@ __device__ __forceinline__ void fwd_segment(const AttnArgs& a, const T* rel_s, r
     // then work on the rows kc/vc fetched one iteration ago.  Called alternately with
     // the two row buffers swapped, so nothing has to be copied between iterations.
     auto step = [&](int eb, const Row<T>& kc, const Row<T>& vc, Row<T>& kn, Row<T>& vn) {
-        const int c2 = buf_i32(rIa, eo + 64);
+        const int ahead = min(eo + 64, eo_last), c2 = buf_i32(rIa, ahead);
         int r2 = 0;
-        if (!SPAN) r2 = buf_i32(rIb, eo + 64);
+        if (!SPAN) r2 = buf_i32(rIb, ahead);
         kn = gather_row<T>(rK, c1, a.row_bytes, lane_off);
         vn = gather_row<T>(rV, c1, a.row_bytes, lane_off);
         eo += 32;
@@ -78,8 +79,7 @@ __device__ __forceinline__ void fwd_segment(const AttnArgs& a, const T* rel_s, r
         cnow = c1;
         float vv[8], d = 0.f;
         if (!SPAN) {
-            const int rid = valid ? r0 : 0;  // a masked lane may hold an id of some other row
-            d = dot8(q, REL_LDS ? load_row(rel_s + rid * kD + first_feature<T>(sub)) : load_row(relg + (int64_t)rid * kD), 0.f);
+            d = dot8(q, REL_LDS ? load_row(rel_s + r0 * kD + first_feature<T>(sub)) : load_row(relg + (int64_t)r0 * kD), 0.f);
         }
         d = dot8(q, kc, d);
         float sc = sum8(d) * qscale + shift;
@@ -264,13 +264,14 @@ __device__ __forceinline__ void bwd_q_segment(const AttnArgs& a, const T* rel_s,
     const uint32_t rowh = drop_row_hash(drop_bh_hash(a.drop_seed, bh), u);
 
     int eo = (e0 + slot) * 4;
-    const int c0 = buf_i32(rIa, eo);
+    const int eo_last = (e1 - 1) * 4;   // (lanes past the end: see fwd_segment)
+    const int c0 = buf_i32(rIa, min(eo, eo_last));
     int cnow = c0;   // key node of the rows in work
-    int c1 = buf_i32(rIa, eo + 32);
+    int c1 = buf_i32(rIa, min(eo + 32, eo_last));
     int r0 = 0, r1 = 0;
     if (!SPAN) {
-        r0 = buf_i32(rIb, eo);
-        r1 = buf_i32(rIb, eo + 32);
+        r0 = buf_i32(rIb, min(eo, eo_last));
+        r1 = buf_i32(rIb, min(eo + 32, eo_last));
     }
     Row<T> k0 = gather_row<T>(rK, c0, a.row_bytes, lane_off), v0 = gather_row<T>(rV, c0, a.row_bytes, lane_off);
 
@@ -294,9 +295,9 @@ __device__ __forceinline__ void bwd_q_segment(const AttnArgs& a, const T* rel_s,
     for (int i = 0; i < 8; ++i) A[i] = Bv[i] = 0.f;
 
     auto step = [&](int eb, const Row<T>& kc, const Row<T>& vc, Row<T>& kn, Row<T>& vn) {
-        const int c2 = buf_i32(rIa, eo + 64);
+        const int ahead = min(eo + 64, eo_last), c2 = buf_i32(rIa, ahead);
         int r2 = 0;
-        if (!SPAN) r2 = buf_i32(rIb, eo + 64);
+        if (!SPAN) r2 = buf_i32(rIb, ahead);
         kn = gather_row<T>(rK, c1, a.row_bytes, lane_off);
         vn = gather_row<T>(rV, c1, a.row_bytes, lane_off);
 
@@ -309,11 +310,10 @@ __device__ __forceinline__ void bwd_q_segment(const AttnArgs& a, const T* rel_s,
         unpack(kc, kk);
         if (!SPAN) {
             float r[8];
-            const int rid = inside ? r0 : 0;  // a lane past the end may hold an id of some other row
             if (REL_LDS)
-                load8(rel_s + rid * kD + first_feature<T>(sub), r);
+                load8(rel_s + r0 * kD + first_feature<T>(sub), r);
             else
-                load8(relg + (int64_t)rid * kD, r);
+                load8(relg + (int64_t)r0 * kD, r);
 #pragma unroll
             for (int i = 0; i < 8; ++i) kk[i] += r[i];
         }
@@ -497,11 +497,12 @@ __device__ __forceinline__ void bwd_kv_segment(const AttnArgs& a, const T* rel_s
     // queries that are not kept carry kLseGone in `stat`; a key that is not kept has no edge at all
     if (e1 > e0 && node_kept(a, v, len)) {
         int eo = (e0 + slot) * 4;
-        const int u0 = buf_i32(rIa, eo);
+        const int eo_last = (e1 - 1) * 4;   // (lanes past the end: see fwd_segment)
+        const int u0 = buf_i32(rIa, min(eo, eo_last));
         int unow = u0;   // query node of the rows in work
         const uint32_t bhh = drop_bh_hash(a.drop_seed, bh);
-        int u1 = buf_i32(rIa, eo + 32);
-        int r0 = buf_i32(rIb, eo), r1 = buf_i32(rIb, eo + 32);
+        int u1 = buf_i32(rIa, min(eo + 32, eo_last));
+        int r0 = buf_i32(rIb, min(eo, eo_last)), r1 = buf_i32(rIb, min(eo + 32, eo_last));
         Row<T> q0 = gather_row<T>(rQ, u0, a.row_bytes, lane_off), g0 = gather_row<T>(rG, u0, a.row_bytes, lane_off);
         float2 st0 = buf_f2(rS, u0 * 8);
         const Row<T> kk = load_row(static_cast<const T*>(a.K) + base + (int64_t)v * a.sn + first_feature<T>(sub));
@@ -509,8 +510,9 @@ __device__ __forceinline__ void bwd_kv_segment(const AttnArgs& a, const T* rel_s
 
         auto step = [&](int eb, const Row<T>& qc, const Row<T>& gc, const float2& stc, Row<T>& qn, Row<T>& gn,
                         float2& stn) {
-            const int u2 = buf_i32(rIa, eo + 64);
-            const int r2 = buf_i32(rIb, eo + 64);
+            const int ahead = min(eo + 64, eo_last);
+            const int u2 = buf_i32(rIa, ahead);
+            const int r2 = buf_i32(rIb, ahead);
             qn = gather_row<T>(rQ, u1, a.row_bytes, lane_off);
             gn = gather_row<T>(rG, u1, a.row_bytes, lane_off);
             stn = buf_f2(rS, u1 * 8);

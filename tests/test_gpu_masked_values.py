@@ -45,6 +45,15 @@ def reads_of(g, nodes):
     return hit
 
 
+def keys_of(g, rows):
+    """nodes that one of the rows (a mask) has an edge to"""
+    row_ptr, col, _ = g.csr_to_host()
+    row = np.repeat(np.arange(len(row_ptr) - 1), np.diff(row_ptr))
+    hit = np.zeros(len(row_ptr) - 1, bool)
+    hit[col[rows[row]]] = True
+    return hit
+
+
 def bad_nodes(n):
     """tokens at both ends and in the middle of a tile, spans of a low and a high level"""
     return np.array([0, n // 2 + 5, n - 1, n + n // 4 + 3, 2 * n - 3])
@@ -82,4 +91,55 @@ def test_bf16_keys_of_other_rows(n, k, causal, kind, value):
     assert int(other.sum()) > 0
     assert torch.equal(out[:, :, other], out0[:, :, other])
     assert torch.equal(lse[:, :, other], lse0[:, :, other])
+    graph.destroy()
+
+
+# sizes of the fp32 tiles: fewer chunks than wavefronts, rows of all kinds of span segments, ids on either side of the
+# query side's variants (up to 96, 192, 384 and gather), key tiles cut into several tasks
+F32 = [(32, 3, True), (256, 8, False), (512, 7, True), (1024, 25, False), (512, 59, False), (4096, 2, False)]
+
+
+F32_KINDS = [("full", c, v) for c in F32 for v in (NAN, -INF)] + [(kind, c, -INF) for kind in ("lengths", "dropout", "packed") for c in F32[:3]]
+
+
+@pytest.mark.parametrize("what", ["K", "V", "Q", "dO"])
+@pytest.mark.parametrize("kind,graph,value", F32_KINDS)
+def test_f32_reaches_only_neighbours(kind, graph, value, what):
+    # the tiles (full) and the gather kernels (the rest)
+    n, k, causal = graph
+    say("f32", n, k, causal, kind, value, what)
+    B, H = 1, 2
+    w = Workload("masked", 15, n, k, causal, B, H, 64, "f32", True)
+    x = make_inputs(w)
+    g = bpt.bpt_build_graph(n, k, causal)
+    bad = bad_nodes(n)
+    kw, okw = {}, {}
+    if kind == "lengths":
+        kw["seq_len"] = torch.tensor([n - n // 4], dtype=torch.int32, device="cuda")
+        bad = bad[:2]      # (nodes that a sequence does not keep have to hold finite values)
+    if kind == "dropout":
+        kw["dropout"], okw = (0.2, 3), dict(dropout=0.2, seed=3)
+    lengths = [n - n // 4 if kind == "lengths" else n] * B
+    o, l, _ = oracle.attn_fwd_lengths(n, k, causal, lengths, x["Q"], x["K"], x["V"], x["Rel"], w.scale, **okw)
+    refs = oracle.attn_bwd_lengths(n, k, causal, lengths, x["Q"], x["K"], x["V"], x["Rel"], x["dO"], w.scale, **okw)
+    d = {key: to_dev(x[key], "f32") for key in ("Q", "K", "V", "dO", "Rel")}
+    d[what][:, :, torch.from_numpy(bad).cuda()] = value
+    graph = bpt.bpt_build_batch_graph(n, k, causal, [n]) if kind == "packed" else g
+    out, lse = bpt.bpt_attn_fwd(graph, d["Q"], d["K"], d["V"], d["Rel"], scale=w.scale, **kw)
+    grads = bpt.bpt_attn_bwd(graph, d["Q"], d["K"], d["V"], d["Rel"], lse, d["dO"], scale=w.scale, **kw)
+    torch.cuda.synchronize()
+    own = np.zeros(g.num_nodes, bool)
+    own[bad] = True
+    rows = reads_of(g, bad) if what in ("K", "V") else own          # rows with a score or a value that is not finite
+    forward = rows if what != "dO" else np.zeros_like(rows)
+    touched = dict(out=forward, lse=forward if what in ("K", "Q") else np.zeros_like(rows), dQ=rows, dK=keys_of(g, rows) | own,
+                   dV=keys_of(g, rows) | own)
+    for name, got, ref in zip(("out", "lse", "dQ", "dK", "dV"), (out, lse) + tuple(grads), (o, l) + tuple(refs)):
+        a, keep = host(got), ~touched[name]
+        assert keep.any() or n <= 32, name
+        assert np.isfinite(a[:, :, keep]).all(), name
+        if keep.any():
+            assert np.abs(a[:, :, keep] - ref[:, :, keep]).max() <= tol_for("f32", ref[:, :, keep], scaled=True), name
+    if what == "V" and kind == "full":   # and it does reach the rows it belongs to
+        assert not np.isfinite(host(out)[:, :, rows]).all(-1).any()
     graph.destroy()
