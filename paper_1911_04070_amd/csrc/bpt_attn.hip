@@ -491,6 +491,10 @@ struct F32Plan {
     int64_t token_blocks = 0;   // backward: workgroups of token tiles, each of which leaves a copy of d_rel
 };
 constexpr int kF32MaxIds = 384;   // 16-id blocks of d_rel that a wavefront of the query side keeps: at most 24
+// The key side keeps the compact ids of a level's 2k + 3 orders in LDS, beside its partial sums.  Short trees use few ids at
+// any k, so this is a limit of its own (k <= 3966): what fits without more LDS than a kernel gets unasked.
+constexpr size_t kF32KeyLds = 65536;
+size_t f32_key_lds(const bpt_graph* g) { return kF32Waves * 16 * (2 * kD + 4) * sizeof(float) + (size_t)g->rel_width * sizeof(int32_t); }
 F32Plan plan_f32(const bpt_graph* g, const bpt_shape_t* s, const DeviceLimits& lim) {
     F32Plan p;
     if (s->dtype != BPT_F32 || g->batch > 0 || g->tiles.num_tiles == 0) return p;
@@ -506,7 +510,7 @@ F32Plan plan_f32(const bpt_graph* g, const bpt_shape_t* s, const DeviceLimits& l
     p.token_blocks = std::min<int64_t>((tiles + 7) / 8 * 8, std::max(8, 2 * lim.cus / 8 * 8));
     const int64_t blocks = tiles + (int64_t)s->B * s->H * g->fwd_span.num_segs + 32;
     p.fwd = p.fwd_lds <= lim.lds && blocks < INT32_MAX;
-    p.bwd = p.fwd && p.cid_pad <= kF32MaxIds && p.bwd_lds <= lim.lds && g->ktiles.num_tasks > 0 &&
+    p.bwd = p.fwd && p.cid_pad <= kF32MaxIds && p.bwd_lds <= lim.lds && g->ktiles.num_tasks > 0 && f32_key_lds(g) <= kF32KeyLds &&
             (int64_t)g->n * p.wp_row * 8 < ((int64_t)1 << 31) && (int64_t)s->B * s->H * g->ktiles.num_tasks + 8 < INT32_MAX;
     return p;
 }

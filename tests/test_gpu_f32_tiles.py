@@ -35,3 +35,14 @@ def test_fp32_tiles(n, k, causal, B, H, ids, layout):
     tiles = {"bwd_q_f32_tile_kernel", "bwd_kv_f32_tile_kernel"}
     assert "fwd_f32_tile_kernel" in ran and "fwd_kernel" not in ran, ran
     assert tiles <= ran if ids is None or ids <= 384 else not tiles & ran, ran
+
+
+@pytest.mark.parametrize("n,k,causal,key_tiles", [(16, 3966, False, True), (16, 3967, False, False), (64, 17000, True, False)])
+def test_more_orders_than_the_key_side_holds(n, k, causal, key_tiles):
+    # few ids in use, but 2 k + 3 orders per level: up to 7936 in the key side's LDS, the gather kernels beyond
+    w = Workload("f32_tiles", 14, n, k, causal, 1, 2, 64, "f32", True)
+    bpt.bpt_profile_enable(True)
+    run_case(w, make_inputs(w), scaled=True)
+    ran = set(bpt.bpt_profile_report())
+    bpt.bpt_profile_enable(False)
+    assert ("bwd_kv_f32_tile_kernel" in ran) == key_tiles and ("bwd_kv_kernel" in ran) != key_tiles, ran
