@@ -12,7 +12,6 @@
 #include <algorithm>
 #include <cstdio>
 #include <cstring>
-#include <mutex>
 #include <new>
 #include <string>
 #include <utility>
@@ -835,124 +834,8 @@ int build(int32_t n, int32_t k, int32_t causal, hipStream_t st, bpt_graph* g) {
 
 }  // namespace
 
-struct TablePool {
-    std::mutex m;
-    hipStream_t copies = nullptr;
-    std::vector<TableBlock*> free;   // destroyed graphs' blocks, oldest first
-    int blocks = 0;                  // these and the ones in use
-    void drop(TableBlock* b) {
-        for (auto& u : b->uses) (void)hipEventDestroy(u.second);
-        (void)hipFree(b->p);   // (waits for the device)
-        delete b;
-        --blocks;
-    }
-    ~TablePool() {
-        for (TableBlock* b : free) drop(b);
-        if (copies) (void)hipStreamDestroy(copies);
-    }
-};
-
-namespace {
-
-// whether the work that read the block is through (wait: until it is)
-bool block_idle(const TableBlock& b, bool wait) {
-    for (const auto& u : b.uses) {
-        const hipError_t e = wait ? hipEventSynchronize(u.second) : hipEventQuery(u.second);
-        if (e != hipSuccess) {
-            (void)hipGetLastError();   // (not ready)
-            return false;
-        }
-    }
-    return true;
-}
-// A block of the tree's with the values h in it, in place when this returns.
-int acquire_tables(TablePool& pool, const std::vector<int32_t>& h, TableBlock** out) {
-    TableBlock* b = nullptr;
-    {
-        std::lock_guard<std::mutex> lock(pool.m);
-        if (!pool.copies) BPT_HIP(hipStreamCreateWithFlags(&pool.copies, hipStreamNonBlocking));
-        // the first that is large enough and idle; with all blocks there are in use, the oldest, when it is
-        for (int pass = 0; pass < 2 && !b; ++pass) {
-            if (pass == 1 && pool.blocks < kTableBlocks) break;
-            for (size_t i = 0; i < pool.free.size() && !b; ++i)
-                if (pool.free[i]->capacity >= h.size() && block_idle(*pool.free[i], pass == 1)) {
-                    b = pool.free[i];
-                    pool.free.erase(pool.free.begin() + i);
-                }
-        }
-        if (b && b->uses.size() > 4) {   // streams come and go: no event for each that ever was
-            for (auto& u : b->uses) (void)hipEventDestroy(u.second);
-            b->uses.clear();
-        }
-        if (!b && pool.blocks >= kTableBlocks && !pool.free.empty()) {   // none is large enough: one makes way
-            pool.drop(pool.free.front());
-            pool.free.erase(pool.free.begin());
-        }
-    }
-    if (!b) {
-        b = new TableBlock();
-        b->capacity = 1024;
-        while (b->capacity < h.size()) b->capacity *= 2;
-        const hipError_t e = hipMalloc((void**)&b->p, b->capacity * sizeof(int32_t));
-        if (e != hipSuccess) {
-            delete b;
-            BPT_HIP(e);
-        }
-        std::lock_guard<std::mutex> lock(pool.m);
-        ++pool.blocks;
-    }
-    *out = b;   // (an error below: the graph's destruction gives it back)
-    BPT_HIP(hipMemcpyAsync(b->p, h.data(), h.size() * sizeof(int32_t), hipMemcpyHostToDevice, pool.copies));
-    BPT_HIP(hipStreamSynchronize(pool.copies));
-    return BPT_OK;
-}
-void release_tables(TablePool& pool, TableBlock* b) {
-    std::lock_guard<std::mutex> lock(pool.m);
-    if (b->unknown || pool.blocks > kTableBlocks) {
-        pool.drop(b);
-        return;
-    }
-    try {
-        pool.free.push_back(b);
-    } catch (const std::bad_alloc&) {
-        pool.drop(b);
-    }
-}
-
-}  // namespace
-
 void note_use(const bpt_graph* g, hipStream_t st) {
-    if (!g || !g->tables) return;
-    TableBlock& b = *g->tables;
-    std::lock_guard<std::mutex> lock(g->pool->m);
-    if (b.unknown) return;
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(st, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) {
-        (void)hipGetLastError();
-        b.unknown = true;   // a captured graph can be replayed at any time
-        return;
-    }
-    hipEvent_t ev = nullptr;
-    for (auto& u : b.uses)
-        if (u.first == st) ev = u.second;
-    if (!ev) {
-        if (hipEventCreateWithFlags(&ev, hipEventDisableTiming) != hipSuccess) {
-            (void)hipGetLastError();
-            b.unknown = true;
-            return;
-        }
-        try {
-            b.uses.emplace_back(st, ev);
-        } catch (const std::bad_alloc&) {
-            (void)hipEventDestroy(ev);
-            b.unknown = true;
-            return;
-        }
-    }
-    if (hipEventRecord(ev, st) != hipSuccess) {
-        (void)hipGetLastError();
-        b.unknown = true;
-    }
+    if (g && g->tables) g->pool->note(*g->tables, st);
 }
 
 namespace {
@@ -998,7 +881,7 @@ int batch_tables(int32_t n, int32_t k, int32_t causal, const int32_t* lengths, i
         if (g->row_count[top + b] > 0) h[seq_at + roots++] = b;
     }
     g->pool = g->tree->pool;
-    if ((rc = acquire_tables(*g->pool, h, &g->tables))) return rc;
+    BPT_HIP(g->pool->acquire(h, &g->tables));   // (an error: the graph's destruction gives back what there is)
     g->d_delta = g->tables->p;
     g->d_lengths = g->d_delta + len_at;
     g->d_root_row = g->d_delta + row_at;
@@ -1278,7 +1161,7 @@ void bpt_graph_destroy(bpt_graph_t* g) {
     bpt::free_schedule(g->fwd_span);
     bpt::free_tiles(g->tiles);
     bpt::free_key_tiles(g->ktiles);
-    if (g->tables) bpt::release_tables(*g->pool, g->tables);   // d_delta, with the lengths and the roots' tables behind it
+    if (g->tables) g->pool->release(g->tables);   // d_delta, with the lengths and the roots' tables behind it
     if (g->owns_tree) bpt_graph_destroy(g->tree);
     delete g;
 }

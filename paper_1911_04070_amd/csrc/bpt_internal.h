@@ -5,10 +5,10 @@
 #include <stdint.h>
 
 #include <memory>
-#include <utility>
 #include <vector>
 
 #include "bpt.h"
+#include "table_pool.h"
 
 namespace bpt {
 
@@ -85,20 +85,6 @@ struct KeyTiles {
     int32_t* multi_tile = nullptr;  // [num_multi] tiles with several tasks
     int32_t* multi_ptr = nullptr;   // [num_multi+1] their partial slots
 };
-
-// Device memory for the small tables of batch graphs on one tree (lengths, row deltas, roots), kept by the tree from one
-// graph to the next: a training loop makes and destroys a graph per step, and a hipFree or a copy on the caller's stream
-// would wait for the whole step before it.  A block is handed out again when the work that read it is through, which
-// events say that every call on a batch graph records behind its last kernel, on its stream.  At most kTableBlocks blocks a
-// tree; they go with it and the graphs on it.
-struct TableBlock {
-    int32_t* p = nullptr;
-    size_t capacity = 0;   // int32s
-    bool unknown = false;  // used where no event could say when (inside a stream capture): not handed out again
-    std::vector<std::pair<hipStream_t, hipEvent_t>> uses;   // the last use on every stream that used it
-};
-struct TablePool;
-constexpr int kTableBlocks = 8;
 
 }  // namespace bpt
 
