@@ -144,9 +144,14 @@ int bpt_build_batch_graph(int32_t n, int32_t k, int32_t causal, const int32_t* l
  * building its own (the caller keeps `tree` alive until the new graph is destroyed; both on the
  * current device), and, with with_edges == 0, without the batch's own CSR, transposed adjacency and
  * gather schedules: only the row layout and the small tables the matrix-core kernels need are made
- * (host arithmetic and one small copy, waiting for neither `stream` nor the device: the tables lie in
- * a few blocks that `tree` keeps and that bpt_graph_destroy, which does not wait for the device
- * either, gives back to it; a block is used again when the calls that read it are through).  Such a graph serves every call that runs on the
+ * (host arithmetic and one small copy).  The tables lie in blocks that `tree` keeps, at most eight of
+ * them; bpt_graph_destroy gives the block back, and it is used again when the calls that read it are
+ * through.  So neither making nor destroying such a graph waits for `stream` or the device, as long as
+ * fewer than eight graphs are alive or have calls queued: with eight, the next graph waits for the
+ * oldest destroyed one's calls.  A hipFree, which waits for the device, takes the place of giving back
+ * where a call on the graph was captured into a HIP graph, where it saw more than 256 calls, where more
+ * than eight graphs are alive, and for a block that is too small when all eight are taken.
+ * Such a graph serves every call that runs on the
  * matrix-core kernels (see above; also the layer and stack calls); the graph accessors and calls
  * that would need the gather kernels return BPT_ERR_UNSUPPORTED (workspace queries SIZE_MAX), and
  * bpt_graph_info reports 0 edges. */
@@ -245,9 +250,10 @@ int bpt_attn_bwd(const bpt_graph_t* g, const bpt_shape_t* s, const void* Q, cons
 
 /* The two stages of bpt_attn_bwd, callable on their own (same workspace, same
  * stream order): the query side walks the CSR rows and produces dQ, d_rel and,
- * in the workspace, delta; the key side walks the transposed adjacency, reads that
- * delta and produces dK and dV.  bpt_attn_bwd is exactly the first followed by the
- * second. */
+ * in the workspace, delta and (fp32) p and p dP of every edge; the key side walks the transposed
+ * adjacency, reads those and produces dK and dV.  It needs the workspace as the query side of
+ * the same shape (strides, seq_len, dropout and gradient type included) left it.  bpt_attn_bwd is
+ * exactly the first followed by the second. */
 int bpt_attn_bwd_query_side(const bpt_graph_t* g, const bpt_shape_t* s, const void* Q,
                             const void* K, const void* V, const void* rel, const float* lse,
                             const void* dout, void* dQ, float* d_rel, void* workspace,

@@ -33,7 +33,7 @@ struct TableBlock {
 };
 
 struct TablePool {
-    std::mutex m;
+    std::mutex m;   // (never held while something is waited for: calls of other threads note their uses under it)
     hipStream_t copies = nullptr;
     std::vector<TableBlock*> free;   // destroyed graphs' blocks, oldest first
     int blocks = 0;                  // these and the ones in use
@@ -42,14 +42,15 @@ struct TablePool {
     TablePool(const TablePool&) = delete;
     TablePool& operator=(const TablePool&) = delete;
     ~TablePool() {
-        for (TableBlock* b : free) drop(b);
+        for (TableBlock* b : free) destroy(b);
         if (copies) (void)hipStreamDestroy(copies);
     }
 
     // A block of the tree's with the values h in it, in place when this returns.  *out may be set on an error as well: the
     // graph's destruction gives it back.
     hipError_t acquire(const std::vector<int32_t>& h, TableBlock** out) {
-        TableBlock* b = nullptr;
+        TableBlock *b = nullptr, *small = nullptr;
+        bool wait = false;
         {
             std::lock_guard<std::mutex> lock(m);
             if (!copies) {
@@ -60,15 +61,22 @@ struct TablePool {
             for (int pass = 0; pass < 2 && !b; ++pass) {
                 if (pass == 1 && blocks < kTableBlocks) break;
                 for (size_t i = 0; i < free.size() && !b; ++i)
-                    if (free[i]->capacity >= h.size() && idle(*free[i], pass == 1)) {
-                        b = free[i];
-                        free.erase(free.begin() + i);
-                    }
+                    if (free[i]->capacity >= h.size() && (pass == 1 || idle(*free[i], false))) b = take(i);
+                wait = b && pass == 1;
             }
             if (!b && blocks >= kTableBlocks && !free.empty()) {   // none is large enough: one makes way
-                drop(free.front());
-                free.erase(free.begin());
+                small = take(0);
+                --blocks;
             }
+        }
+        if (small) destroy(small);
+        if (wait && !idle(*b, true)) {   // (an event that cannot be waited for: the block is not used again)
+            {
+                std::lock_guard<std::mutex> lock(m);
+                --blocks;
+            }
+            destroy(b);
+            b = nullptr;
         }
         if (b) {
             b->uses = 0;
@@ -91,11 +99,15 @@ struct TablePool {
 
     // the graph that held the block is gone
     void release(TableBlock* b) {
-        std::lock_guard<std::mutex> lock(m);
-        if (b->unknown || blocks > kTableBlocks)
-            drop(b);
-        else
-            free.push_back(b);
+        {
+            std::lock_guard<std::mutex> lock(m);
+            if (!b->unknown && blocks <= kTableBlocks) {
+                free.push_back(b);
+                return;
+            }
+            --blocks;
+        }
+        destroy(b);
     }
 
     // a call has put its kernels, which read the block, on `st`
@@ -136,11 +148,15 @@ private:
         }
         return true;
     }
-    void drop(TableBlock* b) {
+    TableBlock* take(size_t i) {
+        TableBlock* b = free[i];
+        free.erase(free.begin() + i);
+        return b;
+    }
+    static void destroy(TableBlock* b) {
         for (hipEvent_t ev : b->events) (void)hipEventDestroy(ev);
         (void)hipFree(b->p);   // (waits for the device)
         delete b;
-        --blocks;
     }
 };
 

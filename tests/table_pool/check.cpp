@@ -3,6 +3,8 @@
 
 #include <stdio.h>
 
+#include <thread>
+
 using namespace bpt;
 
 static int failed = 0;
@@ -97,9 +99,22 @@ static void many_calls() {
     CHECK(pool.blocks == 0);
 }
 
-// more graphs queued than there are blocks: the next one waits for the oldest that is large enough
+// more graphs queued than there are blocks: the next one waits for the oldest that is large enough; another thread's
+// call does not wait with it
+static TablePool* g_pool = nullptr;
+static bool g_locked = false;
+static void other_thread() {
+    std::thread([] {
+        if (g_pool->m.try_lock())
+            g_pool->m.unlock();
+        else
+            g_locked = true;
+    }).join();
+}
 static void all_in_use(bool large) {
     TablePool pool;
+    g_pool = &pool;
+    g_on_wait = other_thread;
     int32_t* first = nullptr;
     for (int i = 0; i < kTableBlocks; ++i) {
         TableBlock* b = take(pool, kSmall);
@@ -124,6 +139,8 @@ static void all_in_use(bool large) {
     CHECK(pool.blocks > kTableBlocks);
     for (TableBlock* x : held) pool.release(x);
     CHECK(pool.blocks == kTableBlocks && (int)pool.free.size() == kTableBlocks);
+    CHECK(!g_locked);
+    g_on_wait = nullptr;
 }
 
 int main(int argc, char** argv) {

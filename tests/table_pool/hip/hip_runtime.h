@@ -28,12 +28,17 @@ typedef Event* hipEvent_t;
 inline std::map<hipStream_t, std::shared_ptr<Queue>> g_queue;
 inline std::set<void*> g_memory;
 inline int g_waits = 0;                   // calls that waited for work
+inline void (*g_on_wait)() = nullptr;     // ... tell the test
 inline bool g_no_events = false;
 
 inline Queue& queue_of(hipStream_t s) {
     auto& q = g_queue[s];
     if (!q) q = std::make_shared<Queue>();
     return *q;
+}
+inline void waited() {
+    ++g_waits;
+    if (g_on_wait) g_on_wait();
 }
 inline hipError_t hipGetLastError() { return hipSuccess; }
 inline hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned) {
@@ -52,7 +57,7 @@ inline hipError_t hipMalloc(void** p, size_t bytes) {
     return hipSuccess;
 }
 inline hipError_t hipFree(void* p) {
-    ++g_waits;
+    waited();
     g_memory.erase(p);
     free(p);
     return hipSuccess;
@@ -78,7 +83,7 @@ inline hipError_t hipEventRecord(hipEvent_t e, hipStream_t s) {
 }
 inline hipError_t hipEventQuery(hipEvent_t e) { return e->queue->done >= e->at ? hipSuccess : hipErrorNotReady; }
 inline hipError_t hipEventSynchronize(hipEvent_t e) {
-    ++g_waits;
+    waited();
     if (e->queue->done < e->at) e->queue->done = e->at;
     return hipSuccess;
 }

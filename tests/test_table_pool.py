@@ -11,7 +11,7 @@ ROOT = os.path.dirname(HERE)
 @pytest.fixture(scope="module")
 def check(tmp_path_factory):
     out = str(tmp_path_factory.mktemp("table_pool") / "check")
-    subprocess.check_call(["g++", "-std=c++17", "-O1", "-g", "-D_GLIBCXX_ASSERTIONS", "-Wall", "-I", os.path.join(HERE, "table_pool"),
+    subprocess.check_call(["g++", "-std=c++17", "-O1", "-g", "-D_GLIBCXX_ASSERTIONS", "-Wall", "-pthread", "-I", os.path.join(HERE, "table_pool"),
                            "-I", os.path.join(ROOT, "paper_1911_04070_amd", "csrc"), os.path.join(HERE, "table_pool", "check.cpp"), "-o", out])
     return out
 
