@@ -1071,7 +1071,6 @@ int backward(const bpt_graph_t* g, const bpt_shape_t* s, const void* Q, const vo
     if (misaligned(Q) || misaligned(K) || misaligned(V) || misaligned(rel) || misaligned(dout) || misaligned(dQ) ||
         misaligned(dK) || misaligned(dV) || misaligned(d_rel) || misaligned(workspace))
         return BPT_ERR_INVALID_ARG;
-    const UseOnReturn use = {g, static_cast<hipStream_t>(stream)};
     // a batch graph on the matrix-core kernels: from here on g and s are the tree of one sequence and the view of
     // the packed tensors as one batch entry per sequence
     bpt_shape_t view;
@@ -1119,6 +1118,47 @@ int backward(const bpt_graph_t* g, const bpt_shape_t* s, const void* Q, const vo
 }
 
 }  // namespace
+
+int attn_fwd(const bpt_graph_t* g, const bpt_shape_t* s, const void* Q, const void* K, const void* V,
+             const void* rel, void* out, float* lse, void* workspace, size_t workspace_bytes, void* stream) {
+    int rc = check_shape(g, s);
+    if (rc) return rc;
+    if (!Q || !K || !V || !rel || !out || !lse) return BPT_ERR_INVALID_ARG;
+    if (misaligned(Q) || misaligned(K) || misaligned(V) || misaligned(rel) ||
+        misaligned(out) || misaligned(workspace))
+        return BPT_ERR_INVALID_ARG;
+    const size_t need = bpt_attn_fwd_workspace(g, s);
+    if (need == SIZE_MAX) return BPT_ERR_UNSUPPORTED;
+    if (need > 0 && (!workspace || workspace_bytes < need)) return BPT_ERR_INVALID_ARG;
+    AttnArgs a;
+    bpt_shape_t view;
+    const bool packed = packed_tiles(g, s, &view);
+    if (packed) {
+        fill_packed(a, g, s, &view);
+        g = g->tree;
+    } else {
+        fill_common(a, g, s);
+    }
+    a.Q = Q;
+    a.K = K;
+    a.V = V;
+    a.rel = rel;
+    a.out = out;
+    a.lse_w = lse;
+    a.part = static_cast<float*>(workspace);
+    a.ptr = g->row_ptr;
+    a.ia = g->col;
+    a.ib = g->rel;
+    use_schedule(a, g->fwd);
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    return s->dtype == BPT_BF16 ? run_fwd<bf16_t>(g, s, a, st) : run_fwd<float>(g, s, a, st);
+}
+
+int attn_bwd(const bpt_graph_t* g, const bpt_shape_t* s, const void* Q, const void* K, const void* V, const void* rel, const float* lse,
+             const void* dout, void* dQ, void* dK, void* dV, float* d_rel, void* workspace, size_t workspace_bytes, void* stream) {
+    return backward(g, s, Q, K, V, rel, lse, dout, dQ, dK, dV, d_rel, workspace, workspace_bytes, stream, kStageQ | kStageKV);
+}
+
 }  // namespace bpt
 
 extern "C" {
@@ -1145,38 +1185,8 @@ size_t bpt_attn_bwd_workspace(const bpt_graph_t* g, const bpt_shape_t* s) {
 
 int bpt_attn_fwd(const bpt_graph_t* g, const bpt_shape_t* s, const void* Q, const void* K, const void* V,
                  const void* rel, void* out, float* lse, void* workspace, size_t workspace_bytes, void* stream) {
-    int rc = bpt::check_shape(g, s);
-    if (rc) return rc;
-    if (!Q || !K || !V || !rel || !out || !lse) return BPT_ERR_INVALID_ARG;
-    if (bpt::misaligned(Q) || bpt::misaligned(K) || bpt::misaligned(V) || bpt::misaligned(rel) ||
-        bpt::misaligned(out) || bpt::misaligned(workspace))
-        return BPT_ERR_INVALID_ARG;
-    const size_t need = bpt_attn_fwd_workspace(g, s);
-    if (need == SIZE_MAX) return BPT_ERR_UNSUPPORTED;
-    if (need > 0 && (!workspace || workspace_bytes < need)) return BPT_ERR_INVALID_ARG;
     const bpt::UseOnReturn use = {g, static_cast<hipStream_t>(stream)};
-    bpt::AttnArgs a;
-    bpt_shape_t view;
-    const bool packed = bpt::packed_tiles(g, s, &view);
-    if (packed) {
-        bpt::fill_packed(a, g, s, &view);
-        g = g->tree;
-    } else {
-        bpt::fill_common(a, g, s);
-    }
-    a.Q = Q;
-    a.K = K;
-    a.V = V;
-    a.rel = rel;
-    a.out = out;
-    a.lse_w = lse;
-    a.part = static_cast<float*>(workspace);
-    a.ptr = g->row_ptr;
-    a.ia = g->col;
-    a.ib = g->rel;
-    bpt::use_schedule(a, g->fwd);
-    hipStream_t st = static_cast<hipStream_t>(stream);
-    return s->dtype == BPT_BF16 ? bpt::run_fwd<bpt::bf16_t>(g, s, a, st) : bpt::run_fwd<float>(g, s, a, st);
+    return bpt::attn_fwd(g, s, Q, K, V, rel, out, lse, workspace, workspace_bytes, stream);
 }
 
 int bpt_attn_fwd_static(const bpt_graph_t* g, const bpt_shape_t* s, const void* Q, const void* K, const void* V,
@@ -1198,13 +1208,14 @@ int bpt_attn_fwd_static(const bpt_graph_t* g, const bpt_shape_t* s, const void* 
 int bpt_attn_bwd(const bpt_graph_t* g, const bpt_shape_t* s, const void* Q, const void* K, const void* V,
                  const void* rel, const float* lse, const void* dout, void* dQ, void* dK, void* dV, float* d_rel,
                  void* workspace, size_t workspace_bytes, void* stream) {
-    return bpt::backward(g, s, Q, K, V, rel, lse, dout, dQ, dK, dV, d_rel, workspace, workspace_bytes, stream,
-                         bpt::kStageQ | bpt::kStageKV);
+    const bpt::UseOnReturn use = {g, static_cast<hipStream_t>(stream)};
+    return bpt::attn_bwd(g, s, Q, K, V, rel, lse, dout, dQ, dK, dV, d_rel, workspace, workspace_bytes, stream);
 }
 
 int bpt_attn_bwd_query_side(const bpt_graph_t* g, const bpt_shape_t* s, const void* Q, const void* K, const void* V,
                             const void* rel, const float* lse, const void* dout, void* dQ, float* d_rel,
                             void* workspace, size_t workspace_bytes, void* stream) {
+    const bpt::UseOnReturn use = {g, static_cast<hipStream_t>(stream)};
     return bpt::backward(g, s, Q, K, V, rel, lse, dout, dQ, nullptr, nullptr, d_rel, workspace, workspace_bytes,
                          stream, bpt::kStageQ);
 }
@@ -1212,6 +1223,7 @@ int bpt_attn_bwd_query_side(const bpt_graph_t* g, const bpt_shape_t* s, const vo
 int bpt_attn_bwd_key_side(const bpt_graph_t* g, const bpt_shape_t* s, const void* Q, const void* K, const void* V,
                           const void* rel, const float* lse, const void* dout, void* dK, void* dV, void* workspace,
                           size_t workspace_bytes, void* stream) {
+    const bpt::UseOnReturn use = {g, static_cast<hipStream_t>(stream)};
     return bpt::backward(g, s, Q, K, V, rel, lse, dout, nullptr, dK, dV, nullptr, workspace, workspace_bytes, stream,
                          bpt::kStageKV);
 }

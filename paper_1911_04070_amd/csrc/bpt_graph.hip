@@ -859,9 +859,11 @@ int batch_tables(int32_t n, int32_t k, int32_t causal, const int32_t* lengths, i
         if ((rc = build(n, k, causal, st, g->tree))) return rc;
     }
     g->ctx_levels = g->tree->ctx_levels;
-    // the four small tables as one block of the tree's, copied on a stream of the tree's own: neither waits for what the
-    // caller has queued (two layers on 32 packed sentences, graph built in the step: 1793 -> 1627 us;
-    // one layer on 30 sentences of up to 256 tokens, 2 heads: 467 -> 379 us)
+    // The four small tables as one block of the shared tree's, copied on a stream of the tree's own: neither waits for what
+    // the caller has queued (two layers on 32 packed sentences, graph built in the step: 1817 -> 1661 us;
+    // one layer on 30 sentences of up to 256 tokens, 2 heads: 467 -> 379 us).  A graph with a tree of its own frees the
+    // tree with it, which waits for the device in any case: an allocation of its own, and its calls leave no events
+    // (which cost 4 us each: 10 sequences of up to 512 tokens, 8 heads, forward and backward 107 -> 116 us).
     const size_t top = (size_t)(num_levels - 1) * B;
     std::vector<int32_t> h((size_t)num_levels * B);
     for (int l = 0; l < num_levels; ++l)
@@ -880,9 +882,13 @@ int batch_tables(int32_t n, int32_t k, int32_t causal, const int32_t* lengths, i
         h[row_at + b] = g->row_count[top + b] > 0 ? g->first_row[top + b] : -1;
         if (g->row_count[top + b] > 0) h[seq_at + roots++] = b;
     }
-    g->pool = g->tree->pool;
-    BPT_HIP(g->pool->acquire(h, &g->tables));   // (an error: the graph's destruction gives back what there is)
-    g->d_delta = g->tables->p;
+    if (g->owns_tree) {
+        if ((rc = upload(h, &g->d_delta))) return rc;
+    } else {
+        g->pool = g->tree->pool;
+        BPT_HIP(g->pool->acquire(h, &g->tables));   // (an error: the graph's destruction gives back what there is)
+        g->d_delta = g->tables->p;
+    }
     g->d_lengths = g->d_delta + len_at;
     g->d_root_row = g->d_delta + row_at;
     g->d_root_seq = g->d_delta + seq_at;
@@ -1161,7 +1167,10 @@ void bpt_graph_destroy(bpt_graph_t* g) {
     bpt::free_schedule(g->fwd_span);
     bpt::free_tiles(g->tiles);
     bpt::free_key_tiles(g->ktiles);
-    if (g->tables) g->pool->release(g->tables);   // d_delta, with the lengths and the roots' tables behind it
+    if (g->tables)   // d_delta, with the lengths and the roots' tables behind it
+        g->pool->release(g->tables);
+    else
+        (void)hipFree(g->d_delta);
     if (g->owns_tree) bpt_graph_destroy(g->tree);
     delete g;
 }

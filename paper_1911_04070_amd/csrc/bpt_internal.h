@@ -121,13 +121,19 @@ struct bpt_graph {
 };
 
 namespace bpt {
-// bpt_graph.hip: a call has put its kernels on `st`; a batch graph's tables are in use until these are through
+// bpt_graph.hip: a call has put its kernels on `st`; a batch graph's tables are in use until these are through.  Once per call
+// of a user's: the calls below are what the entry points of bpt.h and the calls built on them share.
 void note_use(const bpt_graph* g, hipStream_t st);
 struct UseOnReturn {   // the same when a scope ends, whichever way
     const bpt_graph* g;
     hipStream_t st;
     ~UseOnReturn() { note_use(g, st); }
 };
+// bpt_attn.hip: bpt_attn_fwd and bpt_attn_bwd without that
+int attn_fwd(const bpt_graph_t* g, const bpt_shape_t* s, const void* Q, const void* K, const void* V, const void* rel, void* out,
+             float* lse, void* workspace, size_t workspace_bytes, void* stream);
+int attn_bwd(const bpt_graph_t* g, const bpt_shape_t* s, const void* Q, const void* K, const void* V, const void* rel, const float* lse,
+             const void* dout, void* dQ, void* dK, void* dV, float* d_rel, void* workspace, size_t workspace_bytes, void* stream);
 // bpt_attn.hip: address of the current device's copy of the library's static scratch, resolved on first use
 int static_scratch(int device, void** out);
 // bpt_tiles.hip: token tiles and key tiles of a graph whose CSR is on the device

@@ -897,20 +897,12 @@ constexpr int kMaxStackLayers = 256;
 }  // namespace
 }  // namespace bpt
 
-using namespace bpt;
+namespace bpt {
+namespace {
 
-extern "C" {
-
-size_t bpt_layer_fwd_workspace(const bpt_graph_t* g, int32_t B, int32_t H, int32_t d_ff) {
-    if (!g || B < 1 || H < 1 || d_ff < 8) return 0;
-    const bpt_shape_t s = attn_shape(g, B, H, 0.f, nullptr);
-    const size_t attn_ws = bpt_attn_fwd_workspace(g, &s);
-    if (attn_ws == SIZE_MAX) return SIZE_MAX;   // the attention calls refuse this graph and shape
-    return layer_buffers(g, B, H, d_ff, attn_ws).total;
-}
-
-int bpt_layer_fwd(const bpt_graph_t* g, int32_t B, int32_t H, float scale, const int32_t* seq_len, const void* rel,
-                  const void* X, const bpt_layer_params_t* p, void* Y, void* workspace, size_t workspace_bytes, void* stream) {
+// One layer, forward and backward, for the entry points below: a stack of layers is one call of the user's (UseOnReturn).
+int layer_fwd(const bpt_graph_t* g, int32_t B, int32_t H, float scale, const int32_t* seq_len, const void* rel,
+              const void* X, const bpt_layer_params_t* p, void* Y, void* workspace, size_t workspace_bytes, void* stream) {
     if (!g || !rel || !X || !p || !Y || B < 1 || H < 1) return BPT_ERR_INVALID_ARG;
     if (!p->Wq || !p->Wk || !p->Wv || !p->Wo || !p->W1 || !p->W2 || !p->b1 || !p->b2 || !p->g1 || !p->beta1 || !p->g2 || !p->beta2)
         return BPT_ERR_INVALID_ARG;
@@ -949,7 +941,7 @@ int bpt_layer_fwd(const bpt_graph_t* g, int32_t B, int32_t H, float scale, const
                wchunks, d);
     BPT_HIP(hipGetLastError());
     if ((rc = gemm(bl, rows, 3 * d, d, X, false, wqkv, false, qkvo, false, 0, 4 * d))) return rc;
-    if ((rc = bpt_attn_fwd(g, &s, q, k, v, rel, o, lse, ws + L.attn, attn_ws, stream))) return rc;
+    if ((rc = attn_fwd(g, &s, q, k, v, rel, o, lse, ws + L.attn, attn_ws, stream))) return rc;
     // Z = norm(X + O Wo)
     if ((rc = gemm(bl, rows, d, d, o, false, p->Wo, false, acc1, true, 4 * d))) return rc;
     if ((rc = launch_ln(d, st, static_cast<const bf16_t*>(X), acc1, nullptr, p->g1, p->beta1, static_cast<bf16_t*>(z), st1, rows, eps))) return rc;
@@ -966,18 +958,10 @@ int bpt_layer_fwd(const bpt_graph_t* g, int32_t B, int32_t H, float scale, const
     return launch_ln(d, st, static_cast<const bf16_t*>(z), acc2, p->b2, p->g2, p->beta2, static_cast<bf16_t*>(Y), st2, rows, eps);
 }
 
-size_t bpt_layer_bwd_workspace(const bpt_graph_t* g, int32_t B, int32_t H, int32_t d_ff) {
-    if (!g || B < 1 || H < 1 || d_ff < 8) return 0;
-    const bpt_shape_t s = attn_shape(g, B, H, 0.f, nullptr);
-    const size_t attn_ws = bpt_attn_bwd_workspace(g, &s);
-    if (attn_ws == SIZE_MAX) return SIZE_MAX;
-    return layer_bwd_buffers(g, B, H, d_ff, attn_ws).total;
-}
-
-int bpt_layer_bwd(const bpt_graph_t* g, int32_t B, int32_t H, float scale, const int32_t* seq_len, const void* rel,
-                  const void* X, const bpt_layer_params_t* p, const void* fwd_workspace, size_t fwd_workspace_bytes,
-                  const void* dY, void* dX, float* d_rel, const bpt_layer_grads_t* gr, void* workspace,
-                  size_t workspace_bytes, void* stream) {
+int layer_bwd(const bpt_graph_t* g, int32_t B, int32_t H, float scale, const int32_t* seq_len, const void* rel,
+              const void* X, const bpt_layer_params_t* p, const void* fwd_workspace, size_t fwd_workspace_bytes,
+              const void* dY, void* dX, float* d_rel, const bpt_layer_grads_t* gr, void* workspace,
+              size_t workspace_bytes, void* stream) {
     if (!g || !rel || !X || !p || !fwd_workspace || !dY || !dX || !d_rel || !gr || B < 1 || H < 1) return BPT_ERR_INVALID_ARG;
     if (!p->Wq || !p->Wk || !p->Wv || !p->Wo || !p->W1 || !p->W2 || !p->b1 || !p->b2 || !p->g1 || !p->beta1 || !p->g2 || !p->beta2)
         return BPT_ERR_INVALID_ARG;
@@ -1057,7 +1041,7 @@ int bpt_layer_bwd(const bpt_graph_t* g, int32_t B, int32_t H, float scale, const
         return rc;
     if ((rc = gemm(bl, rows, d, d, ds1, false, p->Wo, true, da, false, 0, 4 * d))) return rc;
     // dQ, dK, dV leave the attention's backward rounded to bf16, side by side next to dO: no cast pass
-    if ((rc = bpt_attn_bwd(g, &s, q, k, v, rel, lse, da, dqkvo, dqkvo + d, dqkvo + 2 * d, d_rel, ws + L.attn, attn_ws, stream)))
+    if ((rc = attn_bwd(g, &s, q, k, v, rel, lse, da, dqkvo, dqkvo + d, dqkvo + 2 * d, d_rel, ws + L.attn, attn_ws, stream)))
         return rc;
     const int64_t chunks = rows * d / 8;
     // projections, one product each: [dWq | dWk | dWv] = X^T [dQ | dK | dV], dX = dS1 + [dQ | dK | dV] [Wq | Wk | Wv]^T
@@ -1071,6 +1055,44 @@ int bpt_layer_bwd(const bpt_graph_t* g, int32_t B, int32_t H, float scale, const
                static_cast<const bf16_t*>(ds1), static_cast<const float*>(t), static_cast<bf16_t*>(dX), chunks);
     BPT_HIP(hipGetLastError());
     return BPT_OK;
+}
+
+}  // namespace
+}  // namespace bpt
+
+using namespace bpt;
+
+extern "C" {
+
+size_t bpt_layer_fwd_workspace(const bpt_graph_t* g, int32_t B, int32_t H, int32_t d_ff) {
+    if (!g || B < 1 || H < 1 || d_ff < 8) return 0;
+    const bpt_shape_t s = attn_shape(g, B, H, 0.f, nullptr);
+    const size_t attn_ws = bpt_attn_fwd_workspace(g, &s);
+    if (attn_ws == SIZE_MAX) return SIZE_MAX;   // the attention calls refuse this graph and shape
+    return layer_buffers(g, B, H, d_ff, attn_ws).total;
+}
+
+int bpt_layer_fwd(const bpt_graph_t* g, int32_t B, int32_t H, float scale, const int32_t* seq_len, const void* rel,
+                  const void* X, const bpt_layer_params_t* p, void* Y, void* workspace, size_t workspace_bytes, void* stream) {
+    const UseOnReturn use = {g, static_cast<hipStream_t>(stream)};
+    return layer_fwd(g, B, H, scale, seq_len, rel, X, p, Y, workspace, workspace_bytes, stream);
+}
+
+size_t bpt_layer_bwd_workspace(const bpt_graph_t* g, int32_t B, int32_t H, int32_t d_ff) {
+    if (!g || B < 1 || H < 1 || d_ff < 8) return 0;
+    const bpt_shape_t s = attn_shape(g, B, H, 0.f, nullptr);
+    const size_t attn_ws = bpt_attn_bwd_workspace(g, &s);
+    if (attn_ws == SIZE_MAX) return SIZE_MAX;
+    return layer_bwd_buffers(g, B, H, d_ff, attn_ws).total;
+}
+
+int bpt_layer_bwd(const bpt_graph_t* g, int32_t B, int32_t H, float scale, const int32_t* seq_len, const void* rel,
+                  const void* X, const bpt_layer_params_t* p, const void* fwd_workspace, size_t fwd_workspace_bytes,
+                  const void* dY, void* dX, float* d_rel, const bpt_layer_grads_t* gr, void* workspace,
+                  size_t workspace_bytes, void* stream) {
+    const UseOnReturn use = {g, static_cast<hipStream_t>(stream)};
+    return layer_bwd(g, B, H, scale, seq_len, rel, X, p, fwd_workspace, fwd_workspace_bytes, dY, dX, d_rel, gr, workspace, workspace_bytes,
+                     stream);
 }
 
 size_t bpt_stack_fwd_workspace(const bpt_graph_t* g, int32_t B, int32_t H, int32_t d_ff, int32_t num_layers) {
@@ -1106,8 +1128,8 @@ int bpt_stack_fwd(const bpt_graph_t* g, int32_t B, int32_t H, int32_t num_layers
                static_cast<const bf16_t*>(E), reinterpret_cast<bf16_t*>(ws), chunks, g->n_tokens, g->num_nodes, row_chunks);
     BPT_HIP(hipGetLastError());
     for (int l = 0; l < num_layers; ++l) {
-        const int rc = bpt_layer_fwd(g, B, H, scale, seq_len, rel[l], ws + S.state_bytes * l, &p[l], ws + S.state_bytes * (l + 1),
-                                     ws + S.layers_at + S.layer_bytes * l, S.layer_bytes, stream);
+        const int rc = layer_fwd(g, B, H, scale, seq_len, rel[l], ws + S.state_bytes * l, &p[l], ws + S.state_bytes * (l + 1),
+                                 ws + S.layers_at + S.layer_bytes * l, S.layer_bytes, stream);
         if (rc) return rc;
     }
     // a tree has one root, its last row; the graph of a packed batch one per sequence
@@ -1166,9 +1188,9 @@ int bpt_stack_bwd(const bpt_graph_t* g, int32_t B, int32_t H, int32_t num_layers
     BPT_HIP(hipGetLastError());
     int cur = 0;
     for (int l = num_layers - 1; l >= 0; --l, cur ^= 1) {
-        const int rc = bpt_layer_bwd(g, B, H, scale, seq_len, rel[l], fw + S.state_bytes * l, &p[l],
-                                     fw + S.layers_at + S.layer_bytes * l, S.layer_bytes, dh[cur], dh[cur ^ 1], d_rel[l], &grads[l],
-                                     layer_ws, workspace_bytes - 2 * S.state_bytes, stream);
+        const int rc = layer_bwd(g, B, H, scale, seq_len, rel[l], fw + S.state_bytes * l, &p[l],
+                                 fw + S.layers_at + S.layer_bytes * l, S.layer_bytes, dh[cur], dh[cur ^ 1], d_rel[l], &grads[l],
+                                 layer_ws, workspace_bytes - 2 * S.state_bytes, stream);
         if (rc) return rc;
     }
     // the embeddings are the token rows of the first states; the zero rows of the spans have no parameter behind them
