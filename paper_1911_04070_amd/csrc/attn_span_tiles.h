@@ -18,10 +18,10 @@ namespace {
 //                                  x V_block (B, read transposed out of LDS).
 // A span inside the block is finished here; an ancestor covers 2^(l-5) blocks, so the block
 // contributes a partial (accumulators, running max, sum).  The four blocks of a workgroup are
-// neighbours (n is a power of two): ancestors of levels 6 and 7 lie inside them and are finished
-// through LDS; for the levels above, the four partials are added up to one, or leave as they
-// are (SpanArgs.unit_log), and a merge kernel combines what a row has in order.  The partials
-// were a quarter to a half of what these kernels write, and are read again: with one per workgroup
+// neighbours (n is a power of two): ancestors of levels 6 and 7 lie inside them and can be finished
+// through LDS (SpanArgs.finish); for the levels above, the four partials are added up to one, or leave
+// as they are (SpanArgs.unit_log), and a merge kernel combines what a row has in order.  The partials
+// are a quarter to a half of what these kernels write, and are read again: with one per workgroup
 // (8192 tokens, 32 heads) 28 + 11 -> 27 + 5 us forward and 46 + 12 -> 41 + 5 us backward.  K and V of
 // the tokens are read once for all levels instead of once per level.  Every edge of a span row carries r_anc(l): the constant
 // scale * q . r_anc(l) is added to the row's scores (it only moves lse).
@@ -40,6 +40,7 @@ struct SpanArgs {
     int64_t sb, sh, sn;
     int32_t BH, H, N, n, L, W, zero;
     int32_t unit_log;         // a partial stands for 2^unit_log tokens: 5 (a block) or 7 (a workgroup's four blocks)
+    int32_t finish;           // the rows of levels 6 and 7 are finished by their workgroup (always with unit_log 7)
     float scale;
     const int32_t* seq_len;   // [B] tokens of every sequence, or null
     int32_t leave_unkept;     // rows of nodes a shorter sequence does not keep: left unwritten instead of zero-filled
@@ -304,18 +305,21 @@ __global__ void __launch_bounds__(kTileThreads) fwd_span_tile_kernel(const SpanA
             }
         } else {
             // partial of the ancestor at level 6 + slot, for the workgroup
-            if (g == 0) ml_s[wave][j] = make_float2(m, l);
-            wave_lds_sync();   // the previous group's rows have been read
+            if (a.finish) {   // uniform
+                if (g == 0) ml_s[wave][j] = make_float2(m, l);
+                wave_lds_sync();   // the previous group's rows have been read
 #pragma unroll
-            for (int f = 0; f < 4; ++f) *reinterpret_cast<f32x4_t*>(part_s + j * kDqStride + 16 * f + 4 * g) = o[f];
-            if (a.unit_log > kSpanInLevels) continue;   // uniform
-            // ... and as it is, above level 7: [bh][level][block][66]
-            if (g == 0 && valid && j >= 2) {
+                for (int f = 0; f < 4; ++f) *reinterpret_cast<f32x4_t*>(part_s + j * kDqStride + 16 * f + 4 * g) = o[f];
+                if (a.unit_log > kSpanInLevels) continue;   // uniform
+            }
+            // ... and as it is, above what the workgroup finishes: [bh][level][block][66]
+            const int j0 = a.finish ? kSpanGroupLevels - kSpanInLevels : 0;
+            if (g == 0 && valid && j >= j0) {
                 float* dst = a.part + (((int64_t)bh * nanc + j) * nblk + blk) * kPartStride;
                 dst[64] = m;
                 dst[65] = l;
             }
-            if (j >= 2 && j < nanc) {   // (a partial is 264 bytes: 8-byte stores)
+            if (j >= j0 && j < nanc) {   // (a partial is 264 bytes: 8-byte stores)
                 float* dst = a.part + (((int64_t)bh * nanc + j) * nblk + blk) * kPartStride + 4 * g;
 #pragma unroll
                 for (int f = 0; f < 4; ++f) {
@@ -332,7 +336,7 @@ __global__ void __launch_bounds__(kTileThreads) fwd_span_tile_kernel(const SpanA
         else
             block();
     }
-    if (nanc <= 0) return;
+    if (nanc <= 0 || !a.finish) return;
     __syncthreads();
     for (int q = threadIdx.x >> 4; q <= nanc; q += kTileThreads / 16) {   // thread -> (row, 4 features); see fwd_span_merge_small
         const SpanGroupRow r = span_group_row(a, q, nblk);
@@ -387,7 +391,7 @@ __device__ __forceinline__ void span_node_level(int n, int L, int v, int& level,
     m = v - span_level_offset(n, level);
 }
 
-// Ancestors above level 7: combine the partials of a row in order.  A row of level l has
+// Ancestors that no workgroup finishes: combine the partials of a row in order.  A row of level l has
 // 2^(l-unit_log) partials.  Rows with at most 16 take one wavefront each,
 // lane = feature, all loads issued at once; longer rows take a workgroup of 1024 threads
 // (thread = 4 features x one of 64 interleaved block lists) and a fixed-order sum of the 64

@@ -398,11 +398,17 @@ int run_span_tiles(const bpt_graph* g, const AttnArgs& a, bool forward, hipStrea
     fill_span_args(t, g, a);
     const int64_t items = (int64_t)a.BH * (g->n / kSpanTok);
     const unsigned grid = (unsigned)((items + kTileWaves - 1) / kTileWaves);
-    // Partials of whole workgroups, at any size in the backward.  The forward's rows above level 7 would be rounded
-    // differently with them (sums of sums), which a deep stack's ReLU gates amplify in its gradients: below 2048 tokens,
-    // where little is gained, they stay one sum over the blocks (forward in blocks -> workgroups: 512 tokens, 256 heads
-    // 43.3 -> 42.5 us, 1024 tokens 45.1 -> 44.7 and 76.4 -> 73.8; from 2048 on 77.0 -> 73.8 us, 8192 tokens 97 -> 88).
-    t.unit_log = g->n >= (forward ? 2048 : 128) ? kSpanGroupLevels : kSpanInLevels;
+    // Partials of whole workgroups from 2048 tokens on, and in the backward at any size.  Forward, partials of blocks with
+    // levels 6 and 7 finished / of workgroups (call, us): 512 tokens, 256 heads 43.3 / 42.5; 1024 tokens, 256 heads 74.0 / 73.0;
+    // 2048 tokens, 128 heads 77.0 / 73.8; 8192 tokens, 32 heads 97 / 88.  Below 2048 tokens 2 % at most is gained, and the rows stay
+    // one sum over the blocks: another order of the sums moves single roundings to bf16, and in a stack the ReLU gates behind them.
+    t.unit_log = !forward || g->n >= 2048 ? kSpanGroupLevels : kSpanInLevels;
+    // With partials of blocks, finishing levels 6 and 7 in their workgroup gives the same bits.  It pays where it spares the
+    // merge launch (n <= 128) and where the partials no longer fit the caches, from about 20000 of 264 bytes on (all partials to
+    // the merge kernel / finished, call, us): 256 tokens, 512 heads (12288) 38.6 / 39.2, 1024 heads (24576) 65.7 / 63.9; 512
+    // tokens, 256 heads (16384) 42.3 / 42.9, 512 heads (32768) 71.2 / 68.8; 1024 tokens, 64 heads (10240) 30.7 / 30.9, 128 heads
+    // (20480) 45.9 / 44.9; one head's tile kernel 7.7 / 8.6.
+    t.finish = t.unit_log == kSpanGroupLevels || g->n <= 128 || items * (t.L - kSpanInLevels) >= 20000 ? 1 : 0;
     const size_t lds = forward ? (size_t)kTileWaves * kSpanTok * kVStride * sizeof(bf16_t)
                                : (size_t)kTileWaves * span_bwd_floats(t.L - kSpanInLevels) * sizeof(float);
     if (t.delta && forward)
@@ -424,9 +430,10 @@ int run_span_tiles(const bpt_graph* g, const AttnArgs& a, bool forward, hipStrea
     else
         BPT_LAUNCH("bwd_q_span_tile_kernel", (bwd_q_span_tile_kernel<false, false>), dim3(grid), dim3(kTileThreads), lds, st, t);
     BPT_HIP(hipGetLastError());
-    if (t.L > kSpanGroupLevels) {
-        // rows above level 7 with at most 16 partials each, then the longer rows
-        const int first = 2 * g->n - ((2 * g->n) >> (kSpanGroupLevels + 1));
+    const int merged = t.finish ? kSpanGroupLevels : kSpanInLevels;   // the last level that the tile kernel finishes
+    if (t.L > merged) {
+        // rows above it with at most 16 partials each, then the longer rows
+        const int first = 2 * g->n - ((2 * g->n) >> (merged + 1));
         const int big_level = t.unit_log + 1 + kSpanSmallLevels;
         const int first_big = t.L >= big_level ? 2 * g->n - ((2 * g->n) >> big_level) : g->num_nodes;
         const int rows_small = first_big - first, rows_big = g->num_nodes - first_big;

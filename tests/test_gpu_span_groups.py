@@ -43,3 +43,25 @@ def test_span_rows_of_workgroups(n, lengths, H, p):
         assert np.isfinite(a).all(), name
         assert np.abs(a - ref).max() <= tol_for("bf16", ref, scaled=True) / ((1.0 - p) if name == "out" else 1.0), name
     g.destroy()
+
+
+@pytest.mark.parametrize("n,B,H", [(256, 112, 8), (512, 40, 8), (1024, 16, 8)])
+@pytest.mark.parametrize("mixed", [False, True])
+def test_rows_do_not_depend_on_the_batch(n, B, H, mixed):
+    # forward below 2048 tokens: a large batch (20000 partial results and more) finishes levels 6 and 7 in the tile kernel, its
+    # quarters leave all of them to the merge kernel; the rows have the same bits
+    say("span rows, batch", n, B, H, mixed)
+    levels, blocks = n.bit_length() - 1 - 5, n // 32
+    assert B * H * blocks * levels >= 20000 > B // 4 * H * blocks * levels
+    g = bpt.bpt_build_graph(n, 2, False)
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    Q, K, V = (torch.randn(B, H, g.num_nodes, 64, device="cuda", generator=gen).to(torch.bfloat16) for _ in range(3))
+    R = torch.randn(g.num_levels, g.rel_width, 64, device="cuda", generator=gen).to(torch.bfloat16)
+    lens = torch.randint(1, n + 1, (B,), dtype=torch.int32, device="cuda", generator=gen) if mixed else None
+    out, lse = bpt.bpt_attn_fwd(g, Q, K, V, R, seq_len=lens)
+    for b in range(0, B, B // 4):
+        part = slice(b, b + B // 4)
+        o, l = bpt.bpt_attn_fwd(g, Q[part].contiguous(), K[part].contiguous(), V[part].contiguous(), R,
+                                seq_len=lens[part].contiguous() if mixed else None)
+        assert torch.equal(out[part], o) and torch.equal(lse[part], l), b
+    g.destroy()
