@@ -143,18 +143,23 @@ template <Bias BIAS>
 __device__ __forceinline__ int bias_slot(int cid) {   // where a token's row of the table holds an id
     return BIAS == Bias::kRing ? cid & (kRingIds - 1) : cid;
 }
-// The column of a token's row of the table that a map word (16 bits: a compact id, or 0xFFFF where there is no edge) reads.
-// Words without an edge read some column of the row (staged and whole tables: the one behind the ids), and has_edge masks
-// what comes of it: by the word and not by a large negative bias, which a large score, an infinity or a NaN in the K row
-// of a column without an edge, or a small scale would pass (the two selects per element cost, at n = 8192, k = 8, causal, 32
-// (batch, head)s: forward 58.7 -> 61.0 us, query side 120.9 -> 123.8).  The masked score is kNegBig; the running maximum starts
-// above it (kMaxStart), so that its weight is 0 also where a token has no edge in its first pairs.
+// The column of a token's row of the table that a map word (16 bits: a compact id, or 0xFFFF where there is no edge) reads: words
+// without an edge read the column behind the ids.
+// Query side: a slot without an edge is masked by its word (has_edge).
+// Forward: that column holds kMaskBias, so that the weight of such a slot comes out as exactly 0 by itself, at any finite score
+// and scale.  A score that is not finite leaves a NaN instead; then, and only then, the weights of the pair are selected
+// by the words.  The running maximum starts above no score but the masked ones (kMaxStart), so that they weigh 0 also in
+// front of a token's first edge.
+// n = 8192, k = 8, causal, 32 (batch, head)s (us), every slot selected / a branch to the selects / no mask but a large negative
+// bias, which large scores, infinities and NaNs pass: forward 59.2 / 57.0 / 56.0, query side 122.8 / 128.1 / 120.5.
+template <Bias BIAS>
+__device__ __forceinline__ int mask_column(int cid_pad) { return BIAS == Bias::kRing ? kRingIds : cid_pad; }
 template <Bias BIAS>
 __device__ __forceinline__ int bias_column(uint32_t word, int cid_pad) {
-    return BIAS == Bias::kRing ? (int)(word & (kRingIds - 1)) : (int)min(word, (uint32_t)cid_pad);
+    return BIAS == Bias::kRing ? (int)((word & (kRingIds - 1)) + (word >> 15)) : (int)min(word, (uint32_t)cid_pad);
 }
 __device__ __forceinline__ bool has_edge(uint32_t word) { return word < 0x8000u; }
-constexpr float kMaxStart = 0.5f * kNegBig;
+constexpr float kMaxStart = -3.0e38f;
 template <Bias BIAS>
 __device__ __forceinline__ void mask_bias(const TileArgs& a, float* bias_s, int t0, int len, int g, int j, int c0, int c1) {
     const int t = t0 + j;
@@ -505,6 +510,7 @@ __global__ void __launch_bounds__(kTileThreads, 2) fwd_tile_kernel(const TileArg
             l_part = 0.f;
 #pragma unroll
             for (int f = 0; f < 4; ++f) o[f] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+            bias_s[j * bias_stride + mask_column<BIAS>(a.cid_pad)] = kMaskBias;
             // bias^T = Rel x Q^T, kept in LDS as [token][compact id]
             if (!kFromMemory) staged_bias(a, rel_s, bias_s, qb0, qb1, g, j);
             if (!kFromMemory && a.seq_len) {   // uniform
@@ -556,12 +562,12 @@ __global__ void __launch_bounds__(kTileThreads, 2) fwd_tile_kernel(const TileArg
             s4[c] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(*reinterpret_cast<const bf16x8_t*>(krow + 8), qb1, s4[c], 0, 0, 0);
         }
         // online softmax over the pair's 32 columns
-        float sc[2][4], gm = kNegBig;
+        float sc[2][4], gm = kMaxStart;
 #pragma unroll
         for (int c = 0; c < 2; ++c)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-                sc[c][r] = has_edge(word[c][r]) ? (s4[c][r] + bv[c][r]) * qscale : kNegBig;
+                sc[c][r] = (s4[c][r] + bv[c][r]) * qscale;
                 gm = fmaxf(gm, sc[c][r]);
             }
         gm = fmaxf(gm, __shfl_xor(gm, 16));
@@ -578,6 +584,16 @@ __global__ void __launch_bounds__(kTileThreads, 2) fwd_tile_kernel(const TileArg
                 sc[c][r] = fast_exp2(sc[c][r] - mn);
                 psum += sc[c][r];
             }
+        if (__any(psum != psum)) {   // a score that is not finite
+            psum = 0.f;
+#pragma unroll
+            for (int c = 0; c < 2; ++c)
+#pragma unroll
+                for (int r = 0; r < 4; ++r) {
+                    sc[c][r] = has_edge(word[c][r]) ? sc[c][r] : 0.f;
+                    psum += sc[c][r];
+                }
+        }
         l_part = l_part * corr + psum;
         // the accumulators hold out^T, C[m = feature][n = token]: all four values of a lane belong to its token j
 #pragma unroll
