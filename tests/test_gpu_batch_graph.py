@@ -346,46 +346,107 @@ def test_a_batch_of_32_sentences():
     run_attention_case("bf16", 512, 4, False, 2, lengths)
 
 
-@pytest.mark.parametrize("graphs,streams,captured", [(3, 1, False), (24, 1, False), (24, 3, False), (6, 1, True)])
-def test_graphs_destroyed_while_their_work_runs(graphs, streams, captured):
+def batch_graph_call(kind, lengths, seed):
+    """(run(graph) -> tensors) of a call on a graph of these lengths over trees of 512 tokens: attention, forward and
+    backward, or a stack of one layer with its readout, forward and backward."""
+    rows = bpt.bpt_build_batch_graph_on(batch_graph_call.tree, lengths)
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+    randn = lambda *s: torch.randn(*s, device="cuda", generator=gen)
+    bf = lambda *s: randn(*s).to(torch.bfloat16)
+    rel = bf(rows.num_levels, rows.rel_width, 64)
+    if kind == "attention":
+        q, dout = bf(1, 2, rows.num_nodes, 64), bf(1, 2, rows.num_nodes, 64)
+        fws, bws = (torch.empty(max(256, n), dtype=torch.uint8, device="cuda") for n in bpt.workspace_bytes(rows, q))
+        out, lse = torch.empty_like(q), torch.empty(q.shape[:3], dtype=torch.float32, device="cuda")
+        grads = tuple(torch.empty_like(q) for _ in range(3)) + (torch.empty(rel.shape, dtype=torch.float32, device="cuda"),)
+
+        def run(g):
+            bpt.bpt_attn_fwd(g, q, q, q, rel, out=out, lse=lse, workspace=fws)
+            bpt.bpt_attn_bwd(g, q, q, q, rel, lse, dout, grads=grads, workspace=bws)
+            return (out, lse) + grads
+    else:
+        d, d_ff = 64, 64
+        p = {w: (randn(d, d) * d ** -0.5).to(torch.bfloat16) for w in ("Wq", "Wk", "Wv", "Wo", "W1", "W2")}
+        p.update({v: randn(d) * 0.1 + (v[0] == "g") for v in ("b1", "b2", "g1", "beta1", "g2", "beta2")})
+        E, d_root = bf(1, int(lengths.sum()), d), bf(len(lengths), d)
+        fws, bws = (torch.empty(n + 256, dtype=torch.uint8, device="cuda") for n in bpt.stack_workspace_bytes(rows, 1, 1, d_ff, 1))
+
+        def run(g):
+            root, tokens = bpt.bpt_stack_fwd(g, E, [rel], [p], 1, workspace=fws)
+            dE, d_rels, grads = bpt.bpt_stack_bwd(g, E, [rel], [p], 1, fws, d_root, None, workspace=bws)
+            return (root, tokens, dE, d_rels[0]) + tuple(grads[0].values())
+    rows.destroy()
+    return run
+
+
+def busy():
+    """ordinary work on the current stream: at 137 GFLOP each, more than 10 milliseconds of it"""
+    a = torch.zeros(4096, 4096, device="cuda", dtype=torch.bfloat16)
+    b = torch.empty_like(a)
+    for _ in range(200):
+        torch.mm(a, a, out=b)
+
+
+@pytest.mark.parametrize("graphs,streams", [(3, 1), (24, 1), (24, 3)])
+def test_graphs_destroyed_while_their_work_runs(graphs, streams):
     # the tables of a batch graph lie in a block of the tree's that the next graph takes over: graphs made and destroyed
-    # with their calls still queued (more of them than there are blocks, on several streams, or called inside a stream
-    # capture that is replayed later) have to give the bits of graphs that are alone on the device
-    tree = bpt.bpt_build_graph(512, 4, False)
+    # with their calls still queued behind other work (more of them than there are blocks, on several streams) have to
+    # give the bits of graphs that are alone on the device.  Whatever tables a kernel found instead would be those of a
+    # batch of other lengths.
+    tree = batch_graph_call.tree = bpt.bpt_build_graph(512, 4, False)
     side = [torch.cuda.Stream() for _ in range(streams)]
     rng = np.random.default_rng(5)
     cases = []
     for i in range(graphs):
-        lengths = rng.integers(1, 513, size=8 if i % 5 else 200).astype(np.int32)
+        # (a batch's lengths in another order: as many rows, so that no table takes a kernel out of its tensors)
+        lengths = rng.permutation(np.r_[np.arange(1, 513, 37), [512, 300, 1]]).astype(np.int32)
+        run = batch_graph_call("attention" if i % 2 else "stack", lengths, i)
         g = bpt.bpt_build_batch_graph_on(tree, lengths)
-        gen = torch.Generator(device="cuda").manual_seed(i)
-        q = torch.randn(1, 2, g.num_nodes, 64, device="cuda", generator=gen).to(torch.bfloat16)
-        rel = torch.randn(g.num_levels, g.rel_width, 64, device="cuda", generator=gen).to(torch.bfloat16)
-        ws = torch.empty(max(256, bpt.workspace_bytes(g, q)[0]), dtype=torch.uint8, device="cuda")
-        want, _ = bpt.bpt_attn_fwd(g, q, q, q, rel, workspace=ws)
+        want = tuple(t.clone() for t in run(g))
         torch.cuda.synchronize()
         g.destroy()
-        cases.append((lengths, q, rel, ws, want, torch.zeros_like(q), torch.zeros(q.shape[:3], dtype=torch.float32, device="cuda")))
+        cases.append((lengths, run, want))
+    busy()
     torch.cuda.synchronize()
-    captures, kept = [], []
-    for i, (lengths, q, rel, ws, _, out, lse) in enumerate(cases):
-        g = bpt.bpt_build_batch_graph_on(tree, lengths)
-        if captured:
-            cg = torch.cuda.CUDAGraph()
-            with torch.cuda.graph(cg):
-                bpt.bpt_attn_fwd(g, q, q, q, rel, out=out, lse=lse, workspace=ws)
-            captures.append(cg)
-            kept.append(g)
-            continue
+    got, pending = [], 0
+    for i, (lengths, run, _) in enumerate(cases):
         with torch.cuda.stream(side[i % streams]):
-            for _ in range(4):
-                bpt.bpt_attn_fwd(g, q, q, q, rel, out=out, lse=lse, workspace=ws)
-        g.destroy()
-    for cg in captures + captures:
-        cg.replay()
+            busy()
+            g = bpt.bpt_build_batch_graph_on(tree, lengths)
+            got.append(run(g))
+            done = torch.cuda.Event()
+            done.record()
+            g.destroy()
+            pending += not done.query()
     torch.cuda.synchronize()
-    for _, _, _, _, want, out, _ in cases:
-        assert torch.equal(out, want)
-    for g in kept:
-        g.destroy()
+    assert pending == graphs   # every graph went while its calls were still queued
+    for (_, _, want), have in zip(cases, got):
+        assert all(torch.equal(x, y) for x, y in zip(want, have))
+    tree.destroy()
+
+
+def test_a_captured_graph_keeps_its_tables():
+    # calls on a batch graph inside a stream capture: graphs made and destroyed between the replays do not get its tables
+    tree = batch_graph_call.tree = bpt.bpt_build_graph(512, 4, False)
+    lengths = np.array([512, 77, 300, 1, 130], np.int32)
+    run = batch_graph_call("attention", lengths, 1)
+    g = bpt.bpt_build_batch_graph_on(tree, lengths)
+    want = tuple(t.clone() for t in run(g))
+    torch.cuda.synchronize()
+    cg = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(cg):
+        out = run(g)
+    other = batch_graph_call("attention", lengths[::-1].copy(), 2)
+    for _ in range(3):
+        for t in out:
+            t.zero_()
+        cg.replay()
+        for _ in range(10):
+            h = bpt.bpt_build_batch_graph_on(tree, lengths[::-1].copy())
+            other(h)
+            h.destroy()
+        torch.cuda.synchronize()
+        assert all(torch.equal(x, y) for x, y in zip(want, out))
+    del cg
+    g.destroy()
     tree.destroy()

@@ -43,7 +43,7 @@ def make_stack(n, k, causal, B, heads, d_ff, seed, decisive):
 
 
 CASES = [(64, 2, False, 2, 1, 64, None), (256, 4, True, 2, 2, 256, None), (512, 4, False, 3, 4, 512, [512, 300, 77]),
-         (1024, 8, True, 1, 8, 2048, None)]
+         (1024, 8, True, 1, 8, 2048, None), (2048, 4, True, 1, 2, 128, None), (4096, 2, False, 2, 1, 64, [4096, 2500])]
 
 
 @pytest.mark.parametrize("n,k,causal,B,heads,d_ff,lengths", CASES)
