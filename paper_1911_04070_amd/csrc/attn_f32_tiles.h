@@ -12,8 +12,8 @@
 // tile: every wavefront takes a quarter of the chunks and the partial sums meet in LDS at the end.  The gather kernels
 // spend about 70 vector instructions per 8 edges and side on dot products across lanes, online softmax per edge and index
 // arithmetic, at half of the vector unit's time, the rest waiting.
-// n = 2048, k = 8, causal, 16 (batch, head)s, gather kernels -> these (us): forward 71 -> 38, query side with d_rel 112 -> 73, key
-// side 101 -> 39, step 315 -> 166; n = 512, k = 4, one head, forward 15.2 -> 7.6.  The matrix cores are busy for a fifth of
+// n = 2048, k = 8, causal, 16 (batch, head)s, gather kernels -> these (us): forward 71 -> 37, query side with d_rel 112 -> 73, key
+// side 101 -> 40, step 315 -> 167; n = 512, k = 4, one head, forward 15.2 -> 7.8.  The matrix cores are busy for a fifth of
 // that (7, 16 and 11 us); the rest is the chain ids -> rows -> products -> sums of a tile at two to four wavefronts per SIMD,
 // and the span rows' vector code (15 and 19 us by themselves; in a launch of their own the step was no shorter).
 #pragma once

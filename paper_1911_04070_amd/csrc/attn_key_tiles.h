@@ -398,7 +398,9 @@ __global__ void __launch_bounds__(kTileThreads, 2) bwd_kv_tile_kernel(const KeyA
 // for the staging area.
 // With two chunks of ids (NBC == 2) only tasks of the token level look into the second: above it the ids are orders, nearly
 // always below 16 (KeyArgs.one_chunk_level), and the LDS unit, which serves the exchange, is the busiest one here (8192
-// tokens, k = 8, 32 heads: 188 -> 183 us; packed, lengths up to 8192: 189 -> 178).
+// tokens, k = 8, 32 heads: 188 -> 183 us; packed, lengths up to 8192: 189 -> 178).  The variants with dropout spill 2 registers
+// for it (8 with bf16 gradients) and are faster all the same: 512 tokens, k = 4, 256 heads 107 -> 102 and 106 -> 102 us, 8192
+// tokens, k = 8, 32 heads 195 -> 186 and 186 -> 180.
 // G16: dK and dV leave rounded to bf16 (a compile-time switch: the stores sit inside the pipelined loop)
 template <int NBC, bool DROP, bool G16, bool PACKED = false>
 __global__ void __launch_bounds__(kTileThreads, 2) bwd_kv_chain_kernel(const KeyArgs a) {

@@ -488,9 +488,12 @@ int launch_bwd_q_merge(const Schedule& sc, const AttnArgs& a, hipStream_t st) {
 }
 
 // fp32 tensors on the matrix cores (attn_f32_tiles.h): one tree, every sequence of n tokens, no dropout.  They are the faster
-// ones over all sizes (fp32, forward + backward, gather kernels / these, us: n = 64, k = 3, 2 x 2 heads 37.8 / 36.6; n = 256, k =
-// 1, 32 x 4 180 / 112; n = 1024, k = 12, 4 heads 95 / 54; n = 4096, k = 2, one head 121 / 58; n = 4096, k = 16, 8 heads 687 /
-// 301).  The gather kernels keep lengths, dropout and batch graphs, and the backward of graphs with more than kF32MaxIds ids.
+// ones wherever they apply (us, gather kernels / these; n, k, ids in use, (batch, head)s: forward, backward): 128, 16, 105, 16
+// 12.7 / 12.3, 41 / 28; 512, 8 causal, 54, 1 16 / 13, 42 / 36; 512, 48, 337, 1 20 / 13, 63 / 53; 1024, 24, 267, 16 90 / 36, 265 / 126; 2048, 8
+// causal, 72, 16 73 / 41, 213 / 118; 2048, 64 causal, 327, 16 242 / 70, 709 / 238; 4096, 24, 367, 1 56 / 19, 190 / 78; 4096, 32, 461, 16 688 /
+// 166, backward on the gather kernels 2022.  (The forward's table takes LDS by the ids, up to one workgroup per compute unit, also from
+// the span rows' workgroups in its launch; it wins there as well: 2048, 64, 653 ids, 16 474 / 111.)  The gather kernels keep lengths, dropout and
+// batch graphs, and the backward of graphs with more than kF32MaxIds ids; above 192 ids the query side spills 60 registers.
 struct F32Plan {
     bool fwd = false, bwd = false;
     int cid_pad = 0, bias_stride = 0, wp_row = 0;
