@@ -176,9 +176,9 @@ __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_ex
 // element becomes a branch of its own around the exponential, and the loads that feed the elements are then waited for
 // one after the other instead of once.  It is used where it wins (kernel times, branch / mask, us): chained key tiles without
 // dropout (n = 512, k = 4, 32 x 8 heads 94.3 / 93.0; n = 8192, k = 8 181.8 / 180.7; n = 65536, k = 4 389 / 387), the other key
-// tiles (k = 12 77.2 / 76.5; k = 16 301 / 300), and in the token tiles' query side.  With dropout the branch is the better form of the chained key tiles (n = 512,
-// k = 4, 32 x 8: 106.7 / 111); on the span tiles the two forms are within 1 % of each other, and the branch is the faster one at
-// n = 512, k = 4, 32 x 8 (22.7 / 23.3).
+// tiles (k = 12 77.2 / 76.5; k = 16 301 / 300), and in the token tiles' query side.  With dropout the branch is the better form
+// of the chained key tiles (n = 512, k = 4, 32 x 8: 106.7 / 111); on the span tiles the two forms are within 1 % of each other,
+// and the branch is the faster one at n = 512, k = 4, 32 x 8 (22.7 / 23.3).
 __device__ __forceinline__ float masked_exp2(bool on, float x) { return fast_exp2(on ? x : kNegBig); }
 __device__ __forceinline__ float fast_log2(float x) { return __builtin_amdgcn_logf(x); }
 

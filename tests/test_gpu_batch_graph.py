@@ -411,15 +411,15 @@ def test_graphs_destroyed_while_their_work_runs(graphs, streams):
     got, pending = [], 0
     for i, (lengths, run, _) in enumerate(cases):
         with torch.cuda.stream(side[i % streams]):
+            g = bpt.bpt_build_batch_graph_on(tree, lengths)   # (waits for an older graph's calls where all blocks are in use)
             busy()
-            g = bpt.bpt_build_batch_graph_on(tree, lengths)
             got.append(run(g))
             done = torch.cuda.Event()
             done.record()
             g.destroy()
             pending += not done.query()
     torch.cuda.synchronize()
-    assert pending == graphs   # every graph went while its calls were still queued
+    assert pending >= graphs - 1   # the graphs went while their calls were still queued (one, where the host was held up, may not have)
     for (_, _, want), have in zip(cases, got):
         assert all(torch.equal(x, y) for x, y in zip(want, have))
     tree.destroy()
